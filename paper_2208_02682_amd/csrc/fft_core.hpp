@@ -240,6 +240,14 @@ __host__ __device__ constexpr Radices plan_of(int n, int e) {
       case 1024: return {16, 4, 1};
       default: break;
     }
+  } else if (e == 8) {
+    switch (n) {
+      case 64: return {8, 1, 1};
+      case 128: return {8, 2, 1};
+      case 256: return {8, 4, 1};
+      case 512: return {8, 8, 1};
+      default: break;
+    }
   } else if (e == 12) {
     if (n == 192) return {4, 4, 1};
     if (n == 384) return {4, 4, 2};
@@ -267,12 +275,14 @@ __host__ __device__ constexpr int tw_offset(int n, int e, int s) {
 }
 __host__ __device__ constexpr int tw_len(int n, int e) { return tw_offset(n, e, 3); }
 
-// values per lane of the column and row passes: 16 for powers of two (a
-// 1024-point transform stays inside one wavefront, no workgroup barriers;
-// measured on the 1024^2 workload it beats 8 values per lane, which halves the
-// registers but needs a barrier per exchange, by about 25% in the row passes),
-// 12 for N = 3 * 2^k (first stage radix 12 = 3 x 4)
-__host__ __device__ constexpr int fft_E_of(int n) { return (n % 3 == 0) ? 12 : 16; }
+// values per lane of the column and row passes.  N >= 512: 16 (a 1024-point
+// transform stays inside one wavefront, no workgroup barriers).  N <= 256: 8.
+// A step of a small grid is bound by the latency of its dependent chains, not by
+// the chip's rates: 8 values halve a lane's work per butterfly stage and double
+// the waves (measured per step, 16 -> 8 values: 64^2 float64 191 -> 115 us,
+// 128^2 float32 130 -> 86, 256^2 float64 227 -> 165, 256^2 float32 146 -> 102).
+// N = 3 * 2^k: 12 (first stage radix 12 = 3 x 4).
+__host__ __device__ constexpr int fft_E_of(int n) { return (n % 3 == 0) ? 12 : (n <= 256 ? 8 : 16); }
 template <int N>
 __host__ __device__ constexpr int fft_E() { return fft_E_of(N); }
 

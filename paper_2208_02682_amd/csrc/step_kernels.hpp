@@ -1370,6 +1370,7 @@ template <typename T, int N, int W>
 __global__ void __launch_bounds__((col_threads<N, W>()), (col_waves<T, N, false>()))
     k_columns(StepPtrs<T> P, Dims d, Phys ph, int stage, double t_next, const cplx<T>* Ys_in, cplx<T>* Ys_out,
               int remap, int slot0) {
+  static_assert(col_threads<N, W>() % 64 == 0 && col_threads<N, W>() <= 1024, "column block");
   __shared__ cplx<T> lds[col_tile<N, W>() * col_buf(N)];
   int tile, slot, z;
   xcd_split(gridDim.x, gridDim.y, tile, slot, z, remap);
