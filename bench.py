@@ -93,8 +93,9 @@ def algorithmic_bytes(N: int, fp32: bool):
     phys4 = N * N * 4 * rT          # interleaved u, v, eta, zeta
     sp = nkx * nky
     state = sp * (9 * cT + 4 * cD)  # 13 prognostic fields (xi, P in float64)
-    rows_dyn = 4 * rowfield + phys4 + 5 * rowfield
-    rows_rhs = 16 * rowfield + phys4 + 8 * rowfield
+    # rows_dyn: dynamics and strategy 1; rows_rhs: strategy 2
+    rows_dyn = (4 + 8) * rowfield + phys4 + (5 + 4) * rowfield
+    rows_rhs = 8 * rowfield + phys4 + 4 * rowfield
     # columns: 13 row spectra in, 20 column-pass outputs out, state Y read,
     # accumulator read (stages 2-4) and written (stages 1-3), Y written (stage 4),
     # stage values of u, v, h read and written; float32 state also reads and

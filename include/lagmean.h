@@ -161,8 +161,8 @@ lm_status lm_step(lm_run* run, int32_t nsteps);
 /* As lm_step, but every kernel launch is bracketed by a pair of HIP events on
    the run's stream (all enqueued back to back; one synchronisation at the end).
    ms_avg[0..2] receive the average duration in milliseconds of the three
-   hot-path kernels: [0] rows pass of the dynamics, [1] rows pass of the mean
-   right-hand sides, [2] column pass (spectral assembly + RK4).
+   hot-path kernels: [0] rows pass of the dynamics and strategy 1, [1] rows pass
+   of strategy 2, [2] column pass (spectral assembly + RK4).
    1 <= nsteps <= 4096.  Synchronous.  For measurement. */
 lm_status lm_step_profiled(lm_run* run, int32_t nsteps, double* ms_avg);
 

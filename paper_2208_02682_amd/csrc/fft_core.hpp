@@ -5,7 +5,8 @@
 // (e = 0..E-1).  The first Stockham stage is a radix-E DFT done in registers;
 // later stages (radices R dividing E, each lane doing E/R butterflies) exchange
 // data through the group's private LDS buffer.  On exit the spectrum is in the
-// LDS buffer in natural order (padded indexing).  When a group fits in one
+// lanes' registers (lane t: entries t + NT e) or, if asked for, in the LDS
+// buffer in natural order (padded indexing).  When a group fits in one
 // wavefront (NT <= 64) the exchanges only need wavefront-scope ordering;
 // otherwise they use workgroup barriers.
 //
@@ -70,6 +71,17 @@ __device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0
 // over the banks
 __device__ __forceinline__ constexpr int pidx(int i) { return i + (i >> 4); }
 __host__ __device__ constexpr int padded_len(int n) { return n + (n >> 4) + 1; }
+
+// an index made of a lane's part and a constant of the unrolled loops: their
+// padded index is split the same way where the constant is a multiple of the
+// padding period, so that one address register and immediate offsets serve a
+// whole unrolled access
+struct LaneIdx {
+  int v, c;
+};
+__device__ __forceinline__ int pidx(LaneIdx i) {
+  return (i.c % 16 == 0) ? pidx(i.v) + i.c + (i.c >> 4) : pidx(i.v + i.c);
+}
 
 // ---------------------------------------------------------------------------
 // small DFTs, y_q = sum_r v_r exp(DIR * 2 pi i r q / R)
@@ -299,37 +311,70 @@ __device__ __forceinline__ void xsync() {
 template <typename T>
 using gptr = const __attribute__((address_space(1))) cplx<T>*;
 
-// one Stockham stage of radix R after sub-transforms of length Ns (Ns > 1),
-// reading and writing the group's LDS buffer; tw: the stage's twiddle block,
-// TW its pointer type
-template <typename T, int N, int E, int DIR, int Ns, int R, typename TW>
-__device__ __forceinline__ void stockham_stage(cplx<T>* buf, int t, TW tw) {
-  constexpr int NT = N / E;
-  constexpr int NB = E / R;
-  static_assert(E % R == 0, "radix must divide E");
-  cplx<T> v[E];
+// Registers -> the group's buffer -> registers: value i of a lane goes to entry
+// wi(i), and entry ri(i) comes back.  SPLIT: real and imaginary parts one after
+// the other through a buffer of reals, half the LDS for twice the instructions
+// (the bytes are the same).
+template <typename T, int E, int NT, bool SPLIT, typename WI, typename RI>
+__device__ __forceinline__ void exchange(cplx<T> (&v)[E], T* buf, WI wi, RI ri) {
+  if constexpr (!SPLIT) {
+    cplx<T>* cb = reinterpret_cast<cplx<T>*>(buf);
 #pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    const int j = t + b * NT;
+    for (int i = 0; i < E; ++i) cb[pidx(wi(i))] = v[i];
+    xsync<NT>();
 #pragma unroll
-    for (int r = 0; r < R; ++r) v[b * R + r] = buf[pidx(j + r * (N / R))];
+    for (int i = 0; i < E; ++i) v[i] = cb[pidx(ri(i))];
+    xsync<NT>();
+  } else {
+#pragma unroll
+    for (int i = 0; i < E; ++i) buf[pidx(wi(i))] = v[i].x;
+    xsync<NT>();
+#pragma unroll
+    for (int i = 0; i < E; ++i) v[i].x = buf[pidx(ri(i))];
+    xsync<NT>();
+#pragma unroll
+    for (int i = 0; i < E; ++i) buf[pidx(wi(i))] = v[i].y;
+    xsync<NT>();
+#pragma unroll
+    for (int i = 0; i < E; ++i) v[i].y = buf[pidx(ri(i))];
+    xsync<NT>();
   }
-  xsync<NT>();
+}
+
+// one Stockham stage of radix R after sub-transforms of length Ns (Ns > 1) on
+// values in registers, v[b R + r] = entry t + NT b + r N / R; tw: the stage's
+// twiddle block
+template <typename T, int N, int E, int DIR, int Ns, int R>
+__device__ __forceinline__ void stockham_stage(cplx<T> (&v)[E], int t, gptr<T> tw) {
+  constexpr int NT = N / E, NB = E / R;
+  static_assert(E % R == 0, "radix must divide E");
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
-    const int j = t + b * NT;
-    const int k = j % Ns;
+    const int k = (t + b * NT) % Ns;
 #pragma unroll
     for (int r = 1; r < R; ++r) {
       const cplx<T> w = {tw[(r - 1) * Ns + k].x, tw[(r - 1) * Ns + k].y};
       v[b * R + r] = (DIR < 0) ? cmul(v[b * R + r], w) : cmulc(v[b * R + r], w);
+      if (R == 16 && r % 5 == 0) sched_fence();  // five twiddles in flight
     }
     dft<R, DIR>(&v[b * R]);
-    const int base = (j / Ns) * Ns * R + k;
-#pragma unroll
-    for (int r = 0; r < R; ++r) buf[pidx(base + r * Ns)] = v[b * R + r];
   }
-  xsync<NT>();
+}
+
+// entry that stage output i = b R + r of lane t belongs to
+template <int N, int E, int Ns, int R>
+__device__ __forceinline__ LaneIdx stage_out(int i, int t) {
+  constexpr int NT = N / E;
+  const int b = i / R, r = i % R;
+  if constexpr (NT % Ns == 0) return {(t / Ns) * Ns * R + t % Ns, b * NT * R + r * Ns};
+  else if constexpr (Ns % NT == 0) return {t, (b * NT / Ns) * Ns * R + (b * NT) % Ns + r * Ns};
+  const int j = t + b * NT;
+  return {(j / Ns) * Ns * R + j % Ns, r * Ns};
+}
+// entry that a stage of radix R takes as its input i
+template <int N, int E, int R>
+__device__ __forceinline__ LaneIdx stage_in(int i, int t) {
+  return {t, (i / R) * (N / E) + (i % R) * (N / R)};
 }
 
 // swap of 32-bit words between lane rows (16 lanes) of two registers:
@@ -366,23 +411,12 @@ __device__ __forceinline__ void lane_swap(V& a, V& b) {
 // (entry t' + NT m in element m of lane t').  So the exchange is a G x G
 // transpose over q and s among the lanes c + 16 q, done with row swaps, after
 // which x[G a + k] holds element A k + a, which is exactly the last stage's
-// input b G + r for b = a, r = k.  The last stage then writes the spectrum to
-// buf in natural order, as a Stockham stage would.
-template <typename T, int N, int E, int DIR, bool KEEP, typename TW>
-__device__ __forceinline__ void stages_16_then_G(cplx<T>* buf, int t, TW tw, cplx<T> (&out)[E]) {
+// input b G + r for b = a, r = k.
+template <typename T, int N, int E, int DIR>
+__device__ __forceinline__ void stages_16_then_G(cplx<T> (&x)[E], int t, gptr<T> tw) {
   constexpr int NT = N / E, G = N / 256, A = 16 / G;
   static_assert(E == 16 && (G == 2 || G == 4) && NT == 16 * G, "plan 16 x 16 x G");
-  cplx<T> x[16];
-  // radix-16 stage after sub-transforms of length 16
-#pragma unroll
-  for (int r = 0; r < 16; ++r) x[r] = buf[pidx(t + r * (N / 16))];
-  const int k = t % 16;
-#pragma unroll
-  for (int r = 1; r < 16; ++r) {
-    const cplx<T> w = {tw[(r - 1) * 16 + k].x, tw[(r - 1) * 16 + k].y};
-    x[r] = (DIR < 0) ? cmul(x[r], w) : cmulc(x[r], w);
-  }
-  dft<16, DIR>(x);
+  stockham_stage<T, N, E, DIR, 16, 16>(x, t, tw);
   // G x G transpose across the lanes c + 16 q
 #pragma unroll
   for (int a = 0; a < A; ++a) {
@@ -395,67 +429,57 @@ __device__ __forceinline__ void stages_16_then_G(cplx<T>* buf, int t, TW tw, cpl
       lane_swap<16>(x[2 * a + 0], x[2 * a + 1]);
     }
   }
-  // the buffer is rewritten below: every lane's reads above come first
-  xsync<NT>();
-  const TW twB = tw + 15 * 16;  // the radix-G stage's twiddle block
-  // radix-G stage after sub-transforms of length 256: butterfly b of lane t
-  // combines entries j + 256 r, j = t + NT b
-#pragma unroll
-  for (int b = 0; b < A; ++b) {
-    const int j = t + NT * b;
-#pragma unroll
-    for (int r = 1; r < G; ++r) {
-      const cplx<T> w = {twB[(r - 1) * 256 + j].x, twB[(r - 1) * 256 + j].y};
-      x[b * G + r] = (DIR < 0) ? cmul(x[b * G + r], w) : cmulc(x[b * G + r], w);
-    }
-    dft<G, DIR>(&x[b * G]);
-    // entry j + 256 r = t + NT (b + A r)
-#pragma unroll
-    for (int r = 0; r < G; ++r) {
-      if constexpr (KEEP) out[b + A * r] = x[b * G + r];
-      else buf[pidx(j + 256 * r)] = x[b * G + r];
-    }
-  }
-  xsync<NT>();
-}
-
-// whether fft<..., GTW> takes the lane-swap path, which can leave its output in
-// the lanes' registers (KEEP) instead of the buffer
-template <int N, int E, bool GTW>
-__host__ __device__ constexpr bool fft_keeps() {
-  return GTW && E == 16 && Plan<N, E>::R2 == 16 && (Plan<N, E>::R3 == 2 || Plan<N, E>::R3 == 4) &&
-         Plan<N, E>::R4 == 1;
+  stockham_stage<T, N, E, DIR, 256, G>(x, t, tw + 15 * 16);
 }
 
 // Full transform of N points held by NT = N / E lanes.  v: lane t holds
-// x[t + NT e]; buf: the group's LDS buffer (padded_len(N) slots).  On exit the
-// spectrum is in buf in natural order, or, with KEEP (lane-swap plans only), in
-// v with lane t holding entry t + NT e.  DIR = -1: forward (exp(-i...)),
-// DIR = +1: inverse (unnormalised).  GTW: read the twiddles with global loads
-// (else generic ones, which also count against the LDS counter: measured
-// faster in the dynamics row pass's forward transforms, slower elsewhere).
-template <typename T, int N, int E, int DIR, bool GTW = true, bool KEEP = false>
-__device__ __forceinline__ void fft(cplx<T> (&v)[E], cplx<T>* buf, int t, const cplx<T>* __restrict__ tw) {
+// x[t + NT e]; buf: the group's LDS buffer (padded_len(N) complex slots, or as
+// many real ones with SPLIT).  On exit the spectrum is in v, lane t holding entry
+// t + NT e: butterfly b of the last stage (radix R, NB = E / R butterflies per
+// lane) leaves entries t + NT (b + NB r), so the natural order needs no exchange.
+// Without KEEP it is put into buf (in natural order; not with SPLIT).
+// DIR = -1: forward (exp(-i...)), DIR = +1: inverse (unnormalised).
+template <typename T, int N, int E, int DIR, bool KEEP = false, bool SPLIT = false>
+__device__ __forceinline__ void fft(cplx<T> (&v)[E], T* buf, int t, const cplx<T>* __restrict__ tw) {
   using PL = Plan<N, E>;
-  constexpr int NT = N / E;
+  constexpr int NT = N / E, R2 = PL::R2, R3 = PL::R3, R4 = PL::R4;
+  static_assert(R2 > 1, "a transform of one stage");
+  constexpr int RL = R4 > 1 ? R4 : (R3 > 1 ? R3 : R2);  // radix of the last stage
   // a fresh view of the twiddle table for every transform: stops the compiler
   // from keeping twiddles of one transform live until the next one
   asm volatile("" : "+s"(tw));
-  using TW = typename std::conditional<GTW, gptr<T>, const cplx<T>*>::type;
-  const TW ptw = (TW)tw;
+  const gptr<T> ptw = (gptr<T>)tw;
   dft<E, DIR>(v);
-#pragma unroll
-  for (int r = 0; r < E; ++r) buf[pidx(t * E + r)] = v[r];
-  xsync<NT>();
-  if constexpr (fft_keeps<N, E, GTW>()) {
-    stages_16_then_G<T, N, E, DIR, KEEP>(buf, t, ptw, v);
+  exchange<T, E, NT, SPLIT>(v, buf, [&](int i) { return LaneIdx{t * E + i, 0}; },
+                            [&](int i) { return stage_in<N, E, R2>(i, t); });
+  if constexpr (E == 16 && R2 == 16 && (R3 == 2 || R3 == 4) && R4 == 1) {
+    stages_16_then_G<T, N, E, DIR>(v, t, ptw);
   } else {
-    static_assert(!KEEP, "only the lane-swap plans keep their output in registers");
-    if constexpr (PL::R2 > 1) stockham_stage<T, N, E, DIR, E, PL::R2>(buf, t, ptw + tw_offset(N, E, 0));
-    if constexpr (PL::R3 > 1)
-      stockham_stage<T, N, E, DIR, E * PL::R2, PL::R3>(buf, t, ptw + tw_offset(N, E, 1));
-    if constexpr (PL::R4 > 1)
-      stockham_stage<T, N, E, DIR, E * PL::R2 * PL::R3, PL::R4>(buf, t, ptw + tw_offset(N, E, 2));
+    stockham_stage<T, N, E, DIR, E, R2>(v, t, ptw + tw_offset(N, E, 0));
+    if constexpr (R3 > 1) {
+      exchange<T, E, NT, SPLIT>(v, buf, [&](int i) { return stage_out<N, E, E, R2>(i, t); },
+                                [&](int i) { return stage_in<N, E, R3>(i, t); });
+      stockham_stage<T, N, E, DIR, E * R2, R3>(v, t, ptw + tw_offset(N, E, 1));
+    }
+    if constexpr (R4 > 1) {
+      exchange<T, E, NT, SPLIT>(v, buf, [&](int i) { return stage_out<N, E, E * R2, R3>(i, t); },
+                                [&](int i) { return stage_in<N, E, R4>(i, t); });
+      stockham_stage<T, N, E, DIR, E * R2 * R3, R4>(v, t, ptw + tw_offset(N, E, 2));
+    }
+  }
+  constexpr int NB = E / RL;
+  if constexpr (KEEP) {
+    cplx<T> o[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) o[i / RL + NB * (i % RL)] = v[i];
+#pragma unroll
+    for (int i = 0; i < E; ++i) v[i] = o[i];
+  } else {
+    static_assert(!SPLIT, "a split buffer holds no whole spectrum");
+    cplx<T>* cb = reinterpret_cast<cplx<T>*>(buf);
+#pragma unroll
+    for (int i = 0; i < E; ++i) cb[pidx(LaneIdx{t, NT * (i / RL + NB * (i % RL))})] = v[i];
+    xsync<NT>();
   }
 }
 

@@ -12,10 +12,10 @@ template <int N>
 __global__ void __launch_bounds__(64 * ROW_WAVES) k_io_row_forward(IoRowFwd J, Dims d, const cplx<double>* tw) {
   using G = RowGeo<N>;
   constexpr int E = G::E, NT = G::NT;
-  __shared__ cplx<double> lds[G::RPB * G::L];
+  __shared__ __align__(16) double lds[G::RPB * 2 * G::L];
   const int grp = row_group<NT>(), t = threadIdx.x % NT;
   const int y = blockIdx.x * G::RPB + grp;
-  cplx<double>* buf = lds + grp * G::L;
+  double* buf = lds + grp * 2 * G::L;
   const int q = blockIdx.y;
   cplx<double> z[E];
 #pragma unroll
@@ -23,28 +23,22 @@ __global__ void __launch_bounds__(64 * ROW_WAVES) k_io_row_forward(IoRowFwd J, D
     const size_t i = (size_t)y * N + t + NT * e;
     z[e] = {J.a[q][i], J.b[q] ? J.b[q][i] : 0.0};
   }
-  cplx<double>* OA = J.oa[q] + (size_t)y * d.NKXP;
-  if (J.b[q]) {
-    cplx<double>* OB = J.ob[q] + (size_t)y * d.NKXP;
-    forward_row<double, N, true>(z, buf, t, tw, OA, OB);
-  } else {
-    forward_row<double, N, false>(z, buf, t, tw, OA, nullptr);
-  }
+  forward_row<double, N>(z, buf, t, tw, J.oa[q], J.b[q] ? J.ob[q] : nullptr, (unsigned)y * (unsigned)d.NKXP);
 }
 
 template <int N>
 __global__ void __launch_bounds__(64 * ROW_WAVES) k_io_row_inverse(IoRowInv J, Dims d, const cplx<double>* tw) {
   using G = RowGeo<N>;
   constexpr int E = G::E, NT = G::NT;
-  __shared__ cplx<double> lds[G::RPB * G::L];
+  __shared__ __align__(16) double lds[G::RPB * 2 * G::L];
   const int grp = row_group<NT>(), t = threadIdx.x % NT;
   const int y = blockIdx.x * G::RPB + grp;
-  cplx<double>* buf = lds + grp * G::L;
+  double* buf = lds + grp * 2 * G::L;
   const int q = blockIdx.y;
-  const cplx<double>* A = J.a[q] + (size_t)y * d.NKXP;
-  const cplx<double>* B = J.b[q] ? J.b[q] + (size_t)y * d.NKXP : A;
+  const cplx<double>* A = J.a[q];
+  const cplx<double>* B = J.b[q] ? J.b[q] : A;
   cplx<double> z[E];
-  load_pair<double, N, false, false>(z, A, B, t);
+  load_pair<double, N, false, false>(z, A, B, (unsigned)y * (unsigned)d.NKXP, t);
   inverse_row<double, N>(z, buf, t, tw);
 #pragma unroll
   for (int e = 0; e < E; ++e) {

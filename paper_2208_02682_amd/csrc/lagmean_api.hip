@@ -984,11 +984,8 @@ lm_status batch_rebuild(lm_batch* b, const std::vector<int>& active) {
     const Launch& l = launches[li];
     if (e == hipSuccess) e = hipStreamWaitEvent(l.g->fork, b->fork_ev, 0);
     if (e == hipSuccess) {
-      lm::Phys gp{};
-      gp.mom = l.g->mom;
-      gp.gen = l.g->gen;
       LM_DISPATCH_N(l.g->N, lm::launch_batch_step, l.g->fork, l.g->d_desc, l.count, l.g->fp32, l.g->cubic, l.g->mom,
-                    lm::col_groups(gp), scheds[li]);
+                    l.g->gen, scheds[li]);
       e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipEventRecord(l.g->join, l.g->fork);
@@ -1266,12 +1263,9 @@ lm_status lm_batch_step_static(lm_batch* b, int32_t max_steps, int32_t* active_o
     }
     // one RK4 step of every group, launched directly on the batch's stream
     for (int g = 0; g < ngroups; ++g) {
-      lm::Phys gp{};
-      gp.mom = groups[g].mom;
-      gp.gen = groups[g].gen;
       const lm::Sched sc = get_sched(groups[g].N, groups[g].fp32, true);
       LM_DISPATCH_N(groups[g].N, lm::launch_batch_step, b->stream, dev + groups[g].off, groups[g].count,
-                    groups[g].fp32, groups[g].cubic, groups[g].mom, lm::col_groups(gp), sc);
+                    groups[g].fp32, groups[g].cubic, groups[g].mom, groups[g].gen, sc);
     }
     lm::launch_batch_tick(b->stream, d_cnt, m);
     st = check_launch();

@@ -18,14 +18,10 @@ template <int N>
 dim3 row_grid(int tasks) {
   return dim3(N / RowGeo<N>::RPB, tasks);
 }
-// the dynamics rows pass (its block shape depends on the precision)
+// the cooperative rows passes: one block per group of WR rows
 template <typename T, int N>
-dim3 dyn_grid() {
-  return dim3(N / DynGeo<T, N>::RPB);
-}
-template <typename T, int N>
-dim3 dyn_block() {
-  return dim3(DynGeo<T, N>::THREADS);
+dim3 coop_grid() {
+  return dim3(N / CoopGeo<T, N>::WR);
 }
 template <int N, int W = 0>
 dim3 col_grid(const Dims& d, int groups) {
@@ -65,7 +61,7 @@ void launch_columns_part(RunView& r, int stage, int first, int count, hipStream_
   with_tile<T, N>(r.sched.tile, [&](auto w) {
     constexpr int W = decltype(w)::value;
     const dim3 g = col_grid<N, W>(r.d, count), b = col_block<N, W>();
-    hipLaunchKernelGGL((k_columns<T, N, W>), g, b, 0, st, P, r.d, r.ph, stage, t_next, Ys_in, Ys_out,
+    hipLaunchKernelGGL((k_columns<T, N, W>), g, b, 0, st, P, r.ph, stage, t_next, Ys_in, Ys_out,
                        r.sched.remap, first);
   });
 }
@@ -76,29 +72,37 @@ void launch_columns_t(RunView& r, int stage) {
   if (stage >= 0) r.ys_cur ^= 1;
 }
 
-// the rows pass of the mean right-hand sides, and the momentum rows when requested
+// the rows pass of the dynamics and strategy 1
+template <typename T, int N>
+void launch_rows_dyn(RunView& r, const StepPtrs<T>& P, double sval, hipStream_t st) {
+  const dim3 g = coop_grid<T, N>(), b(DynGeo<T, N>::THREADS);
+  const int rm = r.sched.remap;
+  if (r.ph.gen) hipLaunchKernelGGL((k_rows_dyn<T, N, true>), g, b, 0, st, P, r.ph, sval, rm);
+  else hipLaunchKernelGGL((k_rows_dyn<T, N, false>), g, b, 0, st, P, r.ph, sval, rm);
+}
+
+// the rows pass of strategy 2, and the momentum rows when requested
 template <typename T, int N>
 void launch_rows_rhs(RunView& r, const StepPtrs<T>& P, double sval) {
-  const dim3 g = row_grid<N>(rhs_tasks<T, N>()), b(64 * ROW_WAVES);
+  const dim3 g = coop_grid<T, N>(), b(RhsGeo<T, N>::THREADS), bm(64 * ROW_WAVES);
   const int rm = r.sched.remap;
-  const int src = r.ph.gen;  // strategy-1 sources in the rows pass only for other averaged fields
-  if (r.cubic) hipLaunchKernelGGL((k_rows_rhs<T, N, true>), g, b, 0, r.stream, P, r.d, sval, rm, src);
-  else hipLaunchKernelGGL((k_rows_rhs<T, N, false>), g, b, 0, r.stream, P, r.d, sval, rm, src);
+  if (r.cubic) hipLaunchKernelGGL((k_rows_rhs<T, N, true>), g, b, 0, r.stream, P, sval, rm);
+  else hipLaunchKernelGGL((k_rows_rhs<T, N, false>), g, b, 0, r.stream, P, sval, rm);
   if (r.mom) {
     const dim3 gm = row_grid<N>(2);
-    if (r.cubic) hipLaunchKernelGGL((k_rows_mom<T, N, true>), gm, b, 0, r.stream, P, r.d, sval, rm);
-    else hipLaunchKernelGGL((k_rows_mom<T, N, false>), gm, b, 0, r.stream, P, r.d, sval, rm);
+    if (r.cubic) hipLaunchKernelGGL((k_rows_mom<T, N, true>), gm, bm, 0, r.stream, P, sval, rm);
+    else hipLaunchKernelGGL((k_rows_mom<T, N, false>), gm, bm, 0, r.stream, P, sval, rm);
   }
 }
 
 // Two-stream form of the steps.  Per stage the dependencies are
-//   rows_dyn(i)  <- the dynamics column groups of stage i-1 (their outputs),
-//                   rows_rhs(i-1) (it reads the physical fields rows_dyn rewrites)
-//                   and the mean column groups of stage i-1 (the strategy-1
-//                   sources and Eulerian accumulators among them read the stage
-//                   values that the dynamics groups of stage i overwrite),
+//   rows_dyn(i)  <- every column group of stage i-1 but those of strategy 2 (their
+//                   outputs), rows_rhs(i-1) (it reads the physical fields rows_dyn
+//                   rewrites) and the mean column groups of stage i-1 (they read
+//                   the row spectra rows_dyn rewrites, and the stage values that
+//                   the dynamics groups of stage i overwrite),
 //   rows_rhs(i)  <- rows_dyn(i) and the mean column groups of stage i-1,
-//   dynamics column groups(i) <- rows_dyn(i),  mean column groups(i) <- rows_rhs(i),
+//   dynamics column groups(i) <- rows_dyn(i),  mean column groups(i) <- rows_dyn(i), rows_rhs(i),
 // and no pass writes what a pass it may overlap with reads.  The auxiliary
 // stream carries rows_dyn and the dynamics groups, the run's stream rows_rhs
 // and the mean groups, so the dynamics groups overlap rows_rhs and the mean
@@ -119,8 +123,7 @@ hipError_t launch_steps_2s(RunView& r, int nsteps) {
       // next dynamics groups overwrite
       if (s + stage > 0) e = hipStreamWaitEvent(r.aux, rhs, 0);
       if (e != hipSuccess) break;
-      hipLaunchKernelGGL((k_rows_dyn<T, N>), (dyn_grid<T, N>()), (dyn_block<T, N>()), 0, r.aux, P, r.d, r.ph,
-                         r.sched.remap);
+      launch_rows_dyn<T, N>(r, P, sval, r.aux);
       e = hipEventRecord(dyn, r.aux);
       launch_columns_part<T, N>(r, stage, 0, nd, r.aux);
       if (e == hipSuccess) e = hipStreamWaitEvent(r.stream, dyn, 0);
@@ -150,8 +153,7 @@ void launch_steps_t(RunView& r, int nsteps) {
     for (int stage = 0; stage < 4; ++stage) {
       // time since the interval start, from integers
       const double sval = (double(r.n - r.n_tau) + c[stage]) * r.ph.dt;
-      hipLaunchKernelGGL((k_rows_dyn<T, N>), (dyn_grid<T, N>()), (dyn_block<T, N>()), 0, r.stream, P, r.d,
-                         r.ph, r.sched.remap);
+      launch_rows_dyn<T, N>(r, P, sval, r.stream);
       launch_rows_rhs<T, N>(r, P, sval);
       launch_columns_t<T, N>(r, stage);
     }
@@ -185,8 +187,7 @@ hipError_t launch_steps_profiled_t(RunView& r, int nsteps, double* ms) {
       // start marker absorbs the work done at kernel boundaries, so each
       // interval covers one kernel's execution only
       (void)hipEventRecord(ev[e++], r.stream);
-      hipLaunchKernelGGL((k_rows_dyn<T, N>), (dyn_grid<T, N>()), (dyn_block<T, N>()), 0, r.stream, P, r.d,
-                         r.ph, r.sched.remap);
+      launch_rows_dyn<T, N>(r, P, sval, r.stream);
       (void)hipEventRecord(ev[e++], r.stream);
       hipLaunchKernelGGL(k_drain<N>, dim3(1), dim3(64), 0, r.stream);
       (void)hipEventRecord(ev[e++], r.stream);
@@ -219,24 +220,28 @@ hipError_t launch_steps_profiled(RunView& r, int nsteps, double* ms) {
 // one RK4 step of every run of one (N, precision) group: blockIdx.z selects
 // the run's descriptor
 template <typename T, int N>
-void launch_batch_step_t(hipStream_t st, const RunDesc<T>* desc, int nruns, bool cubic, bool mom, int ncg,
+void launch_batch_step_t(hipStream_t st, const RunDesc<T>* desc, int nruns, bool cubic, bool mom, bool gen,
                          const Sched& sc) {
   const Dims d = Dims::make(N);
+  Phys gp{};
+  gp.mom = mom;
+  gp.gen = gen;
+  const int ncg = col_groups(gp);  // column groups per run
   const int rm = sc.remap;
   for (int stage = 0; stage < 4; ++stage) {
-    dim3 g1 = dyn_grid<T, N>();
+    dim3 g1 = coop_grid<T, N>();
     g1.z = nruns;
-    hipLaunchKernelGGL((k_rows_dyn_b<T, N>), g1, (dyn_block<T, N>()), 0, st, desc, rm);
-    dim3 g2 = row_grid<N>(rhs_tasks<T, N>());
-    g2.z = nruns;
-    const dim3 b2(64 * ROW_WAVES);
-    if (cubic) hipLaunchKernelGGL((k_rows_rhs_b<T, N, true>), g2, b2, 0, st, desc, stage, rm);
-    else hipLaunchKernelGGL((k_rows_rhs_b<T, N, false>), g2, b2, 0, st, desc, stage, rm);
+    const dim3 b1(DynGeo<T, N>::THREADS);
+    if (gen) hipLaunchKernelGGL((k_rows_dyn_b<T, N, true>), g1, b1, 0, st, desc, stage, rm);
+    else hipLaunchKernelGGL((k_rows_dyn_b<T, N, false>), g1, b1, 0, st, desc, stage, rm);
+    const dim3 b2(RhsGeo<T, N>::THREADS), bm(64 * ROW_WAVES);
+    if (cubic) hipLaunchKernelGGL((k_rows_rhs_b<T, N, true>), g1, b2, 0, st, desc, stage, rm);
+    else hipLaunchKernelGGL((k_rows_rhs_b<T, N, false>), g1, b2, 0, st, desc, stage, rm);
     if (mom) {
       dim3 gm = row_grid<N>(2);
       gm.z = nruns;
-      if (cubic) hipLaunchKernelGGL((k_rows_mom_b<T, N, true>), gm, b2, 0, st, desc, stage, rm);
-      else hipLaunchKernelGGL((k_rows_mom_b<T, N, false>), gm, b2, 0, st, desc, stage, rm);
+      if (cubic) hipLaunchKernelGGL((k_rows_mom_b<T, N, true>), gm, bm, 0, st, desc, stage, rm);
+      else hipLaunchKernelGGL((k_rows_mom_b<T, N, false>), gm, bm, 0, st, desc, stage, rm);
     }
     with_tile<T, N>(sc.tile, [&](auto w) {
       constexpr int W = decltype(w)::value;
@@ -249,10 +254,10 @@ void launch_batch_step_t(hipStream_t st, const RunDesc<T>* desc, int nruns, bool
 }
 
 template <int N>
-void launch_batch_step(hipStream_t st, const void* desc, int nruns, bool fp32, bool cubic, bool mom, int ncg,
+void launch_batch_step(hipStream_t st, const void* desc, int nruns, bool fp32, bool cubic, bool mom, bool gen,
                        const Sched& sc) {
-  if (fp32) launch_batch_step_t<float, N>(st, (const RunDesc<float>*)desc, nruns, cubic, mom, ncg, sc);
-  else launch_batch_step_t<double, N>(st, (const RunDesc<double>*)desc, nruns, cubic, mom, ncg, sc);
+  if (fp32) launch_batch_step_t<float, N>(st, (const RunDesc<float>*)desc, nruns, cubic, mom, gen, sc);
+  else launch_batch_step_t<double, N>(st, (const RunDesc<double>*)desc, nruns, cubic, mom, gen, sc);
 }
 
 template <int N>
@@ -299,7 +304,7 @@ void launch_io_col_forward(RunView& r, const IoColFwd& J, int count) {
   template void launch_steps_t<T, N>(RunView&, int);                                                     \
   template hipError_t launch_steps_profiled_t<T, N>(RunView&, int, double*);                             \
   template void launch_columns_t<T, N>(RunView&, int);                                                   \
-  template void launch_batch_step_t<T, N>(hipStream_t, const RunDesc<T>*, int, bool, bool, int, const Sched&); \
+  template void launch_batch_step_t<T, N>(hipStream_t, const RunDesc<T>*, int, bool, bool, bool, const Sched&); \
   }
 
 #define LM_EXTERN_T(T, N)                                                                                       \
@@ -307,7 +312,7 @@ void launch_io_col_forward(RunView& r, const IoColFwd& J, int count) {
   extern template void launch_steps_t<T, N>(RunView&, int);                                                     \
   extern template hipError_t launch_steps_profiled_t<T, N>(RunView&, int, double*);                             \
   extern template void launch_columns_t<T, N>(RunView&, int);                                                   \
-  extern template void launch_batch_step_t<T, N>(hipStream_t, const RunDesc<T>*, int, bool, bool, int, const Sched&); \
+  extern template void launch_batch_step_t<T, N>(hipStream_t, const RunDesc<T>*, int, bool, bool, bool, const Sched&); \
   }
 
 #define LM_INSTANTIATE(N)                                                                             \
@@ -315,7 +320,7 @@ void launch_io_col_forward(RunView& r, const IoColFwd& J, int count) {
   LM_EXTERN_T(double, N)                                                                              \
   namespace lm {                                                                                      \
   template void launch_steps<N>(RunView&, int);                                                       \
-  template void launch_batch_step<N>(hipStream_t, const void*, int, bool, bool, bool, int, const Sched&); \
+  template void launch_batch_step<N>(hipStream_t, const void*, int, bool, bool, bool, bool, const Sched&); \
   template hipError_t launch_steps_profiled<N>(RunView&, int, double*);                               \
   template void launch_prologue<N>(RunView&);                                                         \
   template void launch_io_row_forward<N>(RunView&, const IoRowFwd&, int);                             \

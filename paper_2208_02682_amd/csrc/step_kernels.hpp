@@ -5,7 +5,10 @@
 //  rows_dyn   per grid row: inverse row transforms of the column-pass outputs to
 //             physical u, v, eta = h - H, zeta (zeta = dv/dx - du/dy); stores
 //             them interleaved for the gathers; forms zeta v, zeta u,
-//             K = (u^2+v^2)/2, eta u, eta v and forward-transforms them along the row.
+//             K = (u^2+v^2)/2, eta u, eta v and strategy 1's right-hand sides
+//               f - u.grad g-tilde                                   (eq. (4.1)) and
+//               (t-tau) u - u.grad P  (inverse lift map, eq. (3.9) in P form)
+//             and forward-transforms them along the row.
 //
 // The physical passes carry the depth anomaly eta = h - H instead of the total
 // depth h, and the h accumulators of the three averages integrate eta; H is put
@@ -13,14 +16,12 @@
 // accumulators, + H in the float64 outputs).  This is the same arithmetic as the
 // total-depth form up to rounding (each average is linear in the averaged field
 // and exact for constants) but keeps the full float32 precision for eta.
-//  rows_rhs   per grid row and strategy: the Lagrangian-mean right-hand sides
-//             in physical space, then forward row transforms:
-//               S2: u(x+xi) - w - (w.grad) xi  for both components (eq. (4.5a)),
-//                   w = xi/(t-tau), or u/2 at t = tau, and
-//                   f(x+xi) - w.grad g-bar, f in {h, zeta}             (eq. (4.5b));
-//               S1: f - u.grad g-tilde                                 (eq. (4.1)) and
-//                   (t-tau) u - u.grad P  (inverse lift map, eq. (3.9) in P form).
-//             u(x+xi) and f(x+xi) are periodic bilinear interpolants.
+//  rows_rhs   per grid row: strategy 2's right-hand sides in physical space,
+//               u(x+xi) - w - (w.grad) xi  for both components     (eq. (4.5a)),
+//               w = xi/(t-tau), or u/2 at t = tau, and
+//               f(x+xi) - w.grad g-bar, f in {h, zeta}             (eq. (4.5b)),
+//             then forward row transforms.
+//             u(x+xi) and f(x+xi) are periodic bilinear (or cubic) interpolants.
 //  columns    per spectral column kx and prognostic field: forward column
 //             transforms, masked spectral assembly of the right-hand side
 //             (Coriolis, Bernoulli gradient, flux divergence, -nu8 |k|^8), the
@@ -57,6 +58,10 @@ __device__ __forceinline__ int row_group() {
   else return threadIdx.x / NT;
 }
 
+// the sizes of a compiled grid, as constants
+template <int N>
+__host__ __device__ constexpr Dims dims_of() { return Dims::make(N); }
+
 template <int N, int W = 0>
 __host__ __device__ constexpr int col_tile() { return col_tile_of(N, W); }
 template <int N, int W = 0>
@@ -66,63 +71,153 @@ __host__ __device__ constexpr int col_threads() { return col_tile<N, W>() * (N /
 // row helpers
 // --------------------------------------------------------------------------
 
-// Build lane registers of the length-N spectrum Z = A' + i B' of two real rows
-// from their half spectra A, B (kx = 0..K).  A' = i kx A if DXA (likewise B).
-// Index k = t + NT r; negative kx are the conjugate mirror.
-template <typename T, int N, bool DXA, bool DXB>
-__device__ __forceinline__ void load_pair(cplx<T> (&z)[fft_E<N>()], const cplx<T>* __restrict__ A,
-                                          const cplx<T>* __restrict__ B, int t) {
-  constexpr int E = fft_E<N>(), NT = N / E, K = kcut<N>();
-  sched_fence();
-  // branch-free: every lane loads (a clamped index where the mask is empty) and
-  // selects, so the unrolled loop has no lane-divergent control flow
-#pragma unroll
-  for (int r = 0; r < E; ++r) {
+// Element i of an array at a base that is uniform over the wavefront: the base
+// stays in scalar registers and the lane's part is one 32-bit offset, shared by
+// every array read at the same place (all arrays are far below 4 GiB).
+template <typename X>
+__device__ __forceinline__ X at32(const X* __restrict__ base, unsigned i) {
+  return *reinterpret_cast<const X*>(reinterpret_cast<const char*>(base) + i * (unsigned)sizeof(X));
+}
+template <typename X>
+__device__ __forceinline__ void put32(X* base, unsigned i, X v) {
+  *reinterpret_cast<X*>(reinterpret_cast<char*>(base) + i * (unsigned)sizeof(X)) = v;
+}
+
+// Which coefficient |kx| = kk of a half spectrum (kx = 0..K) entry k = t + NT r of
+// a full row takes, and how: entries 0..K as stored, N-K..N-1 (negative kx) the
+// conjugate of N - k, none in between.  For most r one rule holds for every lane;
+// then the place is a lane's offset (t, or NT - t for mirrored entries) plus a
+// constant, which costs no address arithmetic.  Lanes without a coefficient read
+// a clamped place and select zero, so that the unrolled loops have no branches.
+template <int N>
+struct HalfIdx {
+  static constexpr int E = fft_E<N>(), NT = N / E, K = kcut<N>();
+  int t, r;
+  __device__ __forceinline__ bool all_lo() const { return NT * r + NT - 1 <= K; }
+  __device__ __forceinline__ bool all_hi() const { return NT * r >= N - K; }
+  __device__ __forceinline__ bool none() const { return NT * r > K && NT * r + NT - 1 < N - K; }
+  __device__ __forceinline__ bool lo() const { return all_lo() || (!all_hi() && t + NT * r <= K); }
+  __device__ __forceinline__ bool in() const { return all_lo() || all_hi() || t + NT * r <= K || t + NT * r >= N - K; }
+  // kk = lane() + off()
+  __device__ __forceinline__ int lane() const {
+    if (all_lo()) return t;
+    if (all_hi()) return NT - t;
     const int k = t + NT * r;
-    const bool lo = k <= K, hi = k >= N - K;
-    const int kk = min(lo ? k : N - k, K);
-    cplx<T> a = A[kk], b = B[kk];
-    if (DXA) a = {-T(kk) * a.y, T(kk) * a.x};
-    if (DXB) b = {-T(kk) * b.y, T(kk) * b.x};
-    const T sy = (kk == 0) ? T(0) : (hi ? T(-1) : T(1));  // real at kx = 0, conjugate mirror
+    return min(k <= K ? k : N - k, K);
+  }
+  __device__ __forceinline__ int off() const { return all_lo() ? NT * r : (all_hi() ? N - NT * (r + 1) : 0); }
+  __device__ __forceinline__ bool zero() const { return r == 0 && t == 0; }
+};
+
+// entry k of the length-N spectrum of a' + i b' from the coefficients a, b of two
+// real rows at kk (conjugated for negative kx, real at kx = 0)
+template <typename T, int N>
+__device__ __forceinline__ cplx<T> full_entry(const HalfIdx<N>& h, cplx<T> a, cplx<T> b) {
+  if (h.r == 0) {
+    const T sy = h.zero() ? T(0) : T(1);
     a.y *= sy;
     b.y *= sy;
-    z[r] = (lo || hi) ? cplx<T>{a.x - b.y, a.y + b.x} : cplx<T>{T(0), T(0)};
+  }
+  const cplx<T> lo = {a.x - b.y, a.y + b.x}, hi = {a.x + b.y, b.x - a.y};
+  if (h.all_lo()) return lo;
+  if (h.all_hi()) return hi;
+  const cplx<T> z = h.lo() ? lo : hi;
+  return h.in() ? z : cplx<T>{T(0), T(0)};
+}
+
+// Build lane registers of the length-N spectrum Z = A' + i B' of two real rows
+// from their half spectra (kx = 0..K), row .. row + K of the fields A and B.
+// A' = i kx A if DXA (likewise B).  Index k = t + NT r.
+template <typename T, int N, bool DXA, bool DXB>
+__device__ __forceinline__ void load_pair(cplx<T> (&z)[fft_E<N>()], const cplx<T>* __restrict__ A,
+                                          const cplx<T>* __restrict__ B, unsigned row, int t) {
+  constexpr int E = fft_E<N>();
+  sched_fence();
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const HalfIdx<N> h{t, r};
+    if (h.none()) {
+      z[r] = {T(0), T(0)};
+      continue;
+    }
+    cplx<T> a = at32(A + h.off(), row + h.lane()), b = at32(B + h.off(), row + h.lane());
+    const T kk = T(h.lane()) + T(h.off());
+    if (DXA) a = {-kk * a.y, kk * a.x};
+    if (DXB) b = {-kk * b.y, kk * b.x};
+    z[r] = full_entry<T, N>(h, a, b);
+  }
+}
+
+// spectrum of eta + i zeta from the column-pass outputs of h, v and i ky u: the
+// zeta spectrum is i kx C_v - C_uy.  Same layout as load_pair.
+template <typename T, int N>
+__device__ __forceinline__ void load_depth_vorticity(cplx<T> (&z)[fft_E<N>()], const cplx<T>* __restrict__ Ch,
+                                                     const cplx<T>* __restrict__ Cv,
+                                                     const cplx<T>* __restrict__ Cuy, unsigned row, int t) {
+  constexpr int E = fft_E<N>();
+  sched_fence();
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const HalfIdx<N> h{t, r};
+    if (h.none()) {
+      z[r] = {T(0), T(0)};
+      continue;
+    }
+    const unsigned i = row + h.lane();
+    const cplx<T> a = at32(Ch + h.off(), i), cv = at32(Cv + h.off(), i), cu = at32(Cuy + h.off(), i);
+    const T kk = T(h.lane()) + T(h.off());
+    z[r] = full_entry<T, N>(h, a, cplx<T>{-kk * cv.y - cu.x, kk * cv.x - cu.y});
   }
 }
 
 // Inverse-transform a pair and leave lane values p[e] at x = t + NT e.
-template <typename T, int N, bool GTW = true>
-__device__ __forceinline__ void inverse_row(cplx<T> (&z)[fft_E<N>()], cplx<T>* buf, int t,
+template <typename T, int N, bool SPLIT = false>
+__device__ __forceinline__ void inverse_row(cplx<T> (&z)[fft_E<N>()], T* buf, int t,
                                             const cplx<T>* __restrict__ tw) {
-  constexpr int E = fft_E<N>(), NT = N / E;
-  if constexpr (fft_keeps<N, E, GTW>()) {
-    fft<T, N, E, +1, GTW, true>(z, buf, t, tw);
-  } else {
-    fft<T, N, E, +1, GTW>(z, buf, t, tw);
-#pragma unroll
-    for (int e = 0; e < E; ++e) z[e] = buf[pidx(t + NT * e)];
-    xsync<NT>();
-  }
+  fft<T, N, fft_E<N>(), +1, true, SPLIT>(z, buf, t, tw);
   sched_fence();
 }
 
 // Forward-transform z = a + i b (lane values at x = t + NT e) and store the
-// half spectra of a and b (kx = 0..K) to the row pointers OA and OB.
-template <typename T, int N, bool TWO, bool GTW = true>
-__device__ __forceinline__ void forward_row(cplx<T> (&z)[fft_E<N>()], cplx<T>* buf, int t,
-                                            const cplx<T>* __restrict__ tw,
-                                            cplx<T>* __restrict__ OA, cplx<T>* __restrict__ OB) {
-  constexpr int E = fft_E<N>(), NT = N / E, K = kcut<N>();
-  fft<T, N, E, -1, GTW>(z, buf, t, tw);
+// half spectra of a and b (kx = 0..K) to row .. row + K of the fields OA and OB
+// (OB null: a alone).  The mirror entries Z(N - k) come through the buffer.
+template <typename T, int N, bool SPLIT = false>
+__device__ __forceinline__ void forward_row(cplx<T> (&z)[fft_E<N>()], T* buf, int t, const cplx<T>* __restrict__ tw,
+                                            cplx<T>* __restrict__ OA, cplx<T>* __restrict__ OB, unsigned row) {
+  constexpr int E = fft_E<N>(), NT = N / E, K = kcut<N>(), KR = (K + NT) / NT;
+  fft<T, N, E, -1, SPLIT, SPLIT>(z, buf, t, tw);
+  auto put = [&](int r, cplx<T> zk, cplx<T> zm) {
+    put32(OA + NT * r, row + t, cplx<T>{T(0.5) * (zk.x + zm.x), T(0.5) * (zk.y - zm.y)});
+    if (OB) put32(OB + NT * r, row + t, cplx<T>{T(0.5) * (zk.y + zm.y), T(-0.5) * (zk.x - zm.x)});
+  };
+  // the mirror of entry t + NT r: N - t - NT r, and 0 for entry 0
+  auto mirror = [&](int r) -> LaneIdx {
+    if (r == 0) return {t == 0 ? 0 : N - t, 0};
+    return {NT - t, N - NT * (r + 1)};
+  };
+  if constexpr (!SPLIT) {
+    const cplx<T>* cb = reinterpret_cast<const cplx<T>*>(buf);
 #pragma unroll
-  for (int r = 0; r < (K + NT) / NT; ++r) {
-    const int k = t + NT * r;
-    if (k > K) break;
-    const cplx<T> zk = buf[pidx(k)];
-    const cplx<T> zm = buf[pidx(k == 0 ? 0 : N - k)];
-    OA[k] = {T(0.5) * (zk.x + zm.x), T(0.5) * (zk.y - zm.y)};
-    if (TWO) OB[k] = {T(0.5) * (zk.y + zm.y), T(-0.5) * (zk.x - zm.x)};
+    for (int r = 0; r < KR; ++r) {
+      if (t + NT * r > K) break;
+      put(r, cb[pidx(LaneIdx{t, NT * r})], cb[pidx(mirror(r))]);
+    }
+  } else {
+    cplx<T> m[KR];
+#pragma unroll
+    for (int e = 0; e < E; ++e) buf[pidx(LaneIdx{t, NT * e})] = z[e].x;
+    xsync<NT>();
+#pragma unroll
+    for (int r = 0; r < KR; ++r) m[r].x = buf[pidx(mirror(r))];
+    xsync<NT>();
+#pragma unroll
+    for (int e = 0; e < E; ++e) buf[pidx(LaneIdx{t, NT * e})] = z[e].y;
+    xsync<NT>();
+#pragma unroll
+    for (int r = 0; r < KR; ++r) m[r].y = buf[pidx(mirror(r))];
+#pragma unroll
+    for (int r = 0; r < KR; ++r)
+      if (t + NT * r <= K) put(r, z[r], m[r]);
   }
   xsync<NT>();
   sched_fence();
@@ -175,10 +270,10 @@ __device__ __forceinline__ void xcd_split(int nslow, int nfast, int& slow, int& 
 }
 
 // periodic bilinear interpolation at x + xi of one pair of the interleaved
-// physical fields: (u, v) if PAIR == 0, (eta, zeta) if PAIR == 1 (8 bytes per
-// corner instead of the whole 16-byte point)
-template <typename T, int N, int PAIR>
-__device__ __forceinline__ cplx<T> gather2(const P4<T>* __restrict__ F, int x, int y, T xix, T xiy) {
+// physical fields: (u, v) if pair == 0, the averaged fields if pair == 1 (uniform
+// over the wave; 8 bytes per corner instead of the whole 16-byte point)
+template <typename T, int N>
+__device__ __forceinline__ cplx<T> gather2(const P4<T>* __restrict__ F, int pair, int x, int y, T xix, T xiy) {
   const T scl = T(double(N) / 6.283185307179586476925286766559);
   T ox = xix * scl, oy = xiy * scl;
   const T fx = floor(ox), fy = floor(oy);
@@ -187,7 +282,7 @@ __device__ __forceinline__ cplx<T> gather2(const P4<T>* __restrict__ F, int x, i
   const int ix0 = wrap2N<N>(x + cell_mod<N>(fx)), iy0 = wrap2N<N>(y + cell_mod<N>(fy));
   const int ix1 = (ix0 + 1 == N) ? 0 : ix0 + 1, iy1 = (iy0 + 1 == N) ? 0 : iy0 + 1;
   // uniform base plus 32-bit byte offsets (the field is far below 4 GiB)
-  const char* F2 = reinterpret_cast<const char*>(F) + PAIR * sizeof(cplx<T>);
+  const char* F2 = reinterpret_cast<const char*>(F) + pair * sizeof(cplx<T>);
   constexpr unsigned PT = sizeof(P4<T>), ROW = N * sizeof(P4<T>);
   const unsigned r0 = unsigned(iy0) * ROW, r1 = unsigned(iy1) * ROW;
   const unsigned c0 = unsigned(ix0) * PT, c1 = unsigned(ix1) * PT;
@@ -202,11 +297,11 @@ __device__ __forceinline__ cplx<T> gather2(const P4<T>* __restrict__ F, int x, i
 }
 
 // periodic tensor-product cubic (4-point Lagrange) interpolation at x + xi of
-// one pair of the interleaved physical fields, PAIR as in gather2: with
+// one pair of the interleaved physical fields, as gather2: with
 // o = xi / dx, i0 = floor(o), a = o - i0, the nodes i0-1 .. i0+2 carry
 // -a(a-1)(a-2)/6, (a+1)(a-1)(a-2)/2, -(a+1)a(a-2)/2, (a+1)a(a-1)/6
-template <typename T, int N, int PAIR>
-__device__ __forceinline__ cplx<T> gather2_cubic(const P4<T>* __restrict__ F, int x, int y, T xix, T xiy) {
+template <typename T, int N>
+__device__ __forceinline__ cplx<T> gather2_cubic(const P4<T>* __restrict__ F, int pair, int x, int y, T xix, T xiy) {
   const T scl = T(double(N) / 6.283185307179586476925286766559);
   T ox = xix * scl, oy = xiy * scl;
   const T fx = floor(ox), fy = floor(oy);
@@ -216,7 +311,7 @@ __device__ __forceinline__ cplx<T> gather2_cubic(const P4<T>* __restrict__ F, in
   const T wy[4] = {-ay * (ay - T(1)) * (ay - T(2)) / T(6), (ay + T(1)) * (ay - T(1)) * (ay - T(2)) / T(2),
                    -(ay + T(1)) * ay * (ay - T(2)) / T(2), (ay + T(1)) * ay * (ay - T(1)) / T(6)};
   const int bx = wrap2N<N>(x + cell_mod<N>(fx)), by = wrap2N<N>(y + cell_mod<N>(fy));
-  const char* F2 = reinterpret_cast<const char*>(F) + PAIR * sizeof(cplx<T>);
+  const char* F2 = reinterpret_cast<const char*>(F) + pair * sizeof(cplx<T>);
   constexpr unsigned PT = sizeof(P4<T>), ROW = N * sizeof(P4<T>);
   unsigned col[4];
 #pragma unroll
@@ -244,515 +339,445 @@ __device__ __forceinline__ cplx<T> gather2_cubic(const P4<T>* __restrict__ F, in
   return out;
 }
 
-// periodic bilinear interpolation of the interleaved physical fields at x + xi
-template <typename T, int N>
-__device__ __forceinline__ P4<T> gather4(const P4<T>* __restrict__ F, int x, int y, T xix, T xiy) {
-  const T scl = T(double(N) / 6.283185307179586476925286766559);
-  T ox = xix * scl, oy = xiy * scl;
-  const T fx = floor(ox), fy = floor(oy);
-  const T ax = ox - fx, ay = oy - fy;
-  const int ix0 = wrap2N<N>(x + cell_mod<N>(fx)), iy0 = wrap2N<N>(y + cell_mod<N>(fy));
-  const int ix1 = (ix0 + 1 == N) ? 0 : ix0 + 1, iy1 = (iy0 + 1 == N) ? 0 : iy0 + 1;
-  const P4<T> f00 = F[iy0 * N + ix0], f01 = F[iy0 * N + ix1];
-  const P4<T> f10 = F[iy1 * N + ix0], f11 = F[iy1 * N + ix1];
-  const T w00 = (T(1) - ax) * (T(1) - ay), w01 = ax * (T(1) - ay);
-  const T w10 = (T(1) - ax) * ay, w11 = ax * ay;
-  P4<T> g;
-  g.u = w00 * f00.u + w01 * f01.u + w10 * f10.u + w11 * f11.u;
-  g.v = w00 * f00.v + w01 * f01.v + w10 * f10.v + w11 * f11.v;
-  g.h = w00 * f00.h + w01 * f01.h + w10 * f10.h + w11 * f11.h;
-  g.z = w00 * f00.z + w01 * f01.z + w10 * f10.z + w11 * f11.z;
-  return g;
+// the pair of fields at x + xi, by either interpolant
+template <typename T, int N, bool CUB>
+__device__ __forceinline__ cplx<T> gather_pair(const P4<T>* __restrict__ F, int pair, int x, int y, T xix, T xiy) {
+  if constexpr (CUB) return gather2_cubic<T, N>(F, pair, x, y, xix, xiy);
+  else return gather2<T, N>(F, pair, x, y, xix, xiy);
 }
 
 // --------------------------------------------------------------------------
-// rows_dyn
+// the rows passes: blocks of cooperating waves
 // --------------------------------------------------------------------------
-// value of an averaging slot's field at a point (FieldSel)
+// A block holds one group of rows (WR = 64 / NT rows, one per lane group of each
+// wave); its waves share the row's transforms.  They load and inverse-transform
+// pairs of fields side by side, exchange physical values through LDS, form the
+// products and forward-transform them: a row is two or three transforms deep,
+// however many fields it carries, instead of a chain of all of them on one wave
+// (four to seven transforms deep), and strategy 1 shares the physical fields the
+// dynamics form instead of reading them back.  Both passes together, us per stage,
+// chains -> cooperating: 64^2 float64 23.4 -> 12.9, 256^2 float32 19.2 -> 13.8,
+// 512^2 float64 47 -> 28, 1024^2 float32 49.9 -> 44.7, 1024^2 float64 143 -> 81.
+// What bounds them: latency below 512^2 (a block's loads, two or three transforms
+// and a gather in sequence), instruction issue and memory about equally at 1024^2.
+template <typename T, int N>
+struct CoopGeo {
+  static constexpr int E = fft_E<N>(), NT = N / E;
+  static_assert(NT <= 64 && 64 % NT == 0, "row groups within a wave");
+  static constexpr int WR = 64 / NT;  // rows per block
+  // large rows exchange real and imaginary parts in turn: half the LDS per
+  // transform, so that more blocks fit a CU
+  static constexpr bool SPLIT = N >= 1024 || (sizeof(T) == 8 && N >= 512);
+  static constexpr int RB = (SPLIT ? 1 : 2) * padded_len(N);  // a row's buffer, in values of T
+  static_assert(N % WR == 0, "row geometry");
+};
+
+// values of a row shared between the waves: pairs in one buffer, or, split, the
+// second component in a buffer of its own
+template <typename T, bool SPLIT>
+struct SharedPair {
+  T *a, *b;
+  __device__ __forceinline__ void put(int x, cplx<T> v) const {
+    if constexpr (SPLIT) {
+      a[x] = v.x;
+      b[x] = v.y;
+    } else {
+      reinterpret_cast<cplx<T>*>(a)[x] = v;
+    }
+  }
+  __device__ __forceinline__ cplx<T> get(int x) const {
+    if constexpr (SPLIT) return {a[x], b[x]};
+    else return reinterpret_cast<const cplx<T>*>(a)[x];
+  }
+};
+
+// value of an averaging slot's field at a point (FieldSel); selects, no branches,
+// so that the unrolled loops stay one block
 template <typename T>
 __device__ __forceinline__ T field_value(int fs, const cplx<T>& uv, const cplx<T>& hz, const Phys& ph) {
-  switch (fs) {
-    case FS_ETA: return hz.x;
-    case FS_ZETA: return hz.y;
-    case FS_U: return uv.x;
-    case FS_V: return uv.y;
-    default: return (T(ph.f) + hz.y) / (T(ph.H) + hz.x);  // potential vorticity (f + zeta) / h
-  }
+  const T q = (T(ph.f) + hz.y) / (T(ph.H) + hz.x);  // potential vorticity (f + zeta) / h
+  T r = (fs == FS_ETA) ? hz.x : hz.y;
+  r = (fs == FS_U) ? uv.x : r;
+  r = (fs == FS_V) ? uv.y : r;
+  return (fs == FS_Q) ? q : r;
 }
 
+// --------------------------------------------------------------------------
+// rows_dyn: dynamics and strategy 1
+// --------------------------------------------------------------------------
+// Inverse transforms of (u, v), (eta, zeta) and the gradients of g-tilde_0,
+// g-tilde_1, P_x, P_y; from the physical u, v, eta, zeta the products zeta v and
+// zeta u, K = (u^2 + v^2) / 2 and eta u, eta v, -u . grad g-tilde (both fields one
+// pair) and s u - u . grad P (another), forward-transformed.  u, v and the averaged
+// fields are stored for the gathers.  For the default averaged fields (eta, zeta)
+// the source f of eq. (4.1) is added in the column pass from the stage spectra
+// (as the Eulerian accumulators take it), so that only the advection term goes
+// through physical space and float32 rounding; other averaged fields (GEN) take f
+// here, and their own spectra for the Eulerian means.
+//
+// Two shares of this work:
+//   SIX (N < 1024), one inverse transform per wave, two deep:
+//     wave 0 (u, v), then zeta v, zeta u     wave 1 (eta, zeta), then K, eta u
+//     wave 2 grad g~_0, then the g~ pair     wave 3 grad g~_1, then eta v
+//     wave 4 grad P_x, then the P pair       wave 5 grad P_y, then (GEN) f_0, f_1
+//   four waves (N = 1024), three transforms each, one barrier:
+//     wave 0 (u, v), zeta v, zeta u, (GEN) f_0, f_1    wave 1 (eta, zeta), K, eta u, eta v
+//     wave 2 grad g~_0, grad g~_1, the g~ pair         wave 3 grad P_x, grad P_y, the P pair
 template <typename T, int N>
-__device__ __forceinline__ void rows_dyn_body(const StepPtrs<T>& P, const Dims& d, const Phys& ph, int rowblock,
-                                              cplx<T>* lds) {
-  using G = RowGeo<N>;
-  constexpr int E = G::E, NT = G::NT;
-  const int grp = row_group<NT>(), t = threadIdx.x % NT;
-  const int y = rowblock * G::RPB + grp;  // the grid covers the rows exactly
-  cplx<T>* buf = lds + grp * G::L;
-  const size_t rf = d.rowfield_elems();
-  const cplx<T>* ICr = P.IC + (size_t)y * d.NKXP;
-  constexpr int K = kcut<N>();
+struct DynGeo : CoopGeo<T, N> {
+  using G = CoopGeo<T, N>;
+  static constexpr bool SIX = N < 1024;
+  static constexpr int WAVES = SIX ? 6 : 4, THREADS = 64 * WAVES;
+  // six: shared pairs overlay their waves' buffers (split: second components apart);
+  // four: shared pairs apart from the transform buffers
+  static constexpr int BUFS = SIX ? (G::SPLIT ? 8 : 6) : (G::SPLIT ? 8 : 6);
+  static constexpr int LDS = BUFS * G::WR * G::RB;
+  // registers for this many resident waves per SIMD
+  static constexpr int MIN_WAVES = SIX ? 3 : (sizeof(T) == 4 ? 4 : 2);
+};
 
-  cplx<T> uv[E], hz[E];
-  load_pair<T, N, false, false>(uv, ICr + IC_U * rf, ICr + IC_V * rf, t);
-  inverse_row<T, N>(uv, buf, t, P.tw);
-  // (eta + i zeta): zeta spectrum = i kx C_v - C_uy
-  {
-    const cplx<T>* Ch = ICr + IC_H * rf;
-    const cplx<T>* Cv = ICr + IC_V * rf;
-    const cplx<T>* Cuy = ICr + IC_UY * rf;
-    sched_fence();
-#pragma unroll
-    for (int r = 0; r < E; ++r) {
-      const int k = t + NT * r;
-      const bool lo = k <= K, hi = k >= N - K;
-      const int kk = min(lo ? k : N - k, K);
-      cplx<T> a = Ch[kk];
-      const cplx<T> cv = Cv[kk], cu = Cuy[kk];
-      cplx<T> b = {-T(kk) * cv.y - cu.x, T(kk) * cv.x - cu.y};
-      const T sy = (kk == 0) ? T(0) : (hi ? T(-1) : T(1));
-      a.y *= sy;
-      b.y *= sy;
-      hz[r] = (lo || hi) ? cplx<T>{a.x - b.y, a.y + b.x} : cplx<T>{T(0), T(0)};
-    }
-  }
-  inverse_row<T, N>(hz, buf, t, P.tw);
-
-  // u, v and the two averaged fields, interleaved for the gathers
-  P4<T>* out = P.uvhz + (size_t)y * N;
-  cplx<T>* RSr = P.RS + (size_t)y * d.NKXP;
-  cplx<T> z[E];
-  if (ph.fs0 == FS_ETA && ph.fs1 == FS_ZETA) {
-#pragma unroll
-    for (int e = 0; e < E; ++e) out[t + NT * e] = P4<T>{uv[e].x, uv[e].y, hz[e].x, hz[e].y};
-  } else {
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      z[e] = {field_value<T>(ph.fs0, uv[e], hz[e], ph), field_value<T>(ph.fs1, uv[e], hz[e], ph)};
-      out[t + NT * e] = P4<T>{uv[e].x, uv[e].y, z[e].x, z[e].y};
-    }
-    // their spectra, for the Eulerian means
-    if (ph.gen) forward_row<T, N, true, false>(z, buf, t, P.tw, RSr + RS_F0 * rf, RSr + RS_F1 * rf);
-  }
-  if (ph.kin) return;  // prescribed flow: no dynamics
-
-
-#pragma unroll
-  for (int e = 0; e < E; ++e) z[e] = {hz[e].y * uv[e].y, hz[e].y * uv[e].x};  // zeta v, zeta u
-  forward_row<T, N, true, false>(z, buf, t, P.tw, RSr + RS_ZV * rf, RSr + RS_ZU * rf);
-#pragma unroll
-  for (int e = 0; e < E; ++e)
-    z[e] = {T(0.5) * (uv[e].x * uv[e].x + uv[e].y * uv[e].y), hz[e].x * uv[e].x};  // K, eta u
-  forward_row<T, N, true, false>(z, buf, t, P.tw, RSr + RS_K * rf, RSr + RS_HU * rf);
-#pragma unroll
-  for (int e = 0; e < E; ++e) z[e] = {hz[e].x * uv[e].y, T(0)};  // eta v
-  forward_row<T, N, false, false>(z, buf, t, P.tw, RSr + RS_HV * rf, nullptr);
-}
-
-// The dynamics rows pass of float runs: a block of three waves shares one
-// group of rows (WR = 64 / NT rows, one per lane group).  Wave 0 inverse-
-// transforms (u, v) and wave 1 (eta, zeta) into their LDS buffers; after a
-// barrier every wave forms its products from the shared physical values (wave
-// 0 also stores them for the gathers) -- wave 0 zeta v, zeta u; wave 1 K,
-// eta u; wave 2 eta v and, for other averaged fields, their values -- and
-// after a second barrier each forward-transforms its products in its own
-// buffer.  Five transforms per row, two deep, instead of five in a row on one
-// wave; the products and transforms are the same.
-template <typename T, int N>
-__device__ __forceinline__ void rows_dyn_coop(const StepPtrs<T>& P, const Dims& d, const Phys& ph, int rowblock,
-                                              cplx<T>* lds) {
-  using G = RowGeo<N>;
-  constexpr int E = G::E, NT = G::NT, L = G::L, WR = 64 / NT;
-  constexpr int K = kcut<N>();
+template <typename T, int N, bool GEN>
+__device__ __forceinline__ void rows_dyn_four(const StepPtrs<T>& P, const Phys& ph, double s,
+                                              int rowblock, T* lds) {
+  using G = DynGeo<T, N>;
+  constexpr int E = G::E, NT = G::NT, WR = G::WR, RB = G::RB;
+  constexpr bool SPLIT = G::SPLIT;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);  // the wave's role
   const int lane = threadIdx.x % 64;
   const int g = lane / NT, t = lane % NT;
   const int y = rowblock * WR + g;
-  cplx<T>* b0 = lds + (0 * WR + g) * L;  // (u, v) after the first phase
-  cplx<T>* b1 = lds + (1 * WR + g) * L;  // (eta, zeta)
-  cplx<T>* bw = lds + (w * WR + g) * L;  // this wave's transform buffer afterwards
-  const size_t rf = d.rowfield_elems();
-  const cplx<T>* ICr = P.IC + (size_t)y * d.NKXP;
-  cplx<T>* RSr = P.RS + (size_t)y * d.NKXP;
+  auto buf = [&](int i) { return lds + (i * WR + g) * RB; };
+  const SharedPair<T, SPLIT> UV{buf(4), buf(SPLIT ? 5 : 4)}, HZ{buf(SPLIT ? 6 : 5), buf(SPLIT ? 7 : 5)};
+  T* mine = buf(w);
+  constexpr Dims d = dims_of<N>();
+  constexpr size_t rf = d.rowfield_elems();
+  const unsigned row = (unsigned)y * (unsigned)d.NKXP;
+  const cplx<T>* A = P.IC + (w == 2 ? IC_GTH : IC_PX) * rf;  // waves 2, 3: their first field
+
   cplx<T> z[E];
   if (w == 0) {
-    load_pair<T, N, false, false>(z, ICr + IC_U * rf, ICr + IC_V * rf, t);
-    inverse_row<T, N>(z, b0, t, P.tw);
-#pragma unroll
-    for (int e = 0; e < E; ++e) b0[pidx(t + NT * e)] = z[e];
+    load_pair<T, N, false, false>(z, P.IC + IC_U * rf, P.IC + IC_V * rf, row, t);
   } else if (w == 1) {
-    // (eta + i zeta): zeta spectrum = i kx C_v - C_uy
-    const cplx<T>* Ch = ICr + IC_H * rf;
-    const cplx<T>* Cv = ICr + IC_V * rf;
-    const cplx<T>* Cuy = ICr + IC_UY * rf;
-    sched_fence();
+    load_depth_vorticity<T, N>(z, P.IC + IC_H * rf, P.IC + IC_V * rf, P.IC + IC_UY * rf, row, t);
+  } else {
+    load_pair<T, N, true, false>(z, A, A + rf, row, t);
+  }
+  inverse_row<T, N, SPLIT>(z, mine, t, P.tw);
+  if (w < 2) {
+    const SharedPair<T, SPLIT> S{w == 0 ? UV.a : HZ.a, w == 0 ? UV.b : HZ.b};
 #pragma unroll
-    for (int r = 0; r < E; ++r) {
-      const int k = t + NT * r;
-      const bool lo = k <= K, hi = k >= N - K;
-      const int kk = min(lo ? k : N - k, K);
-      cplx<T> a = Ch[kk];
-      const cplx<T> cv = Cv[kk], cu = Cuy[kk];
-      cplx<T> b = {-T(kk) * cv.y - cu.x, T(kk) * cv.x - cu.y};
-      const T sy = (kk == 0) ? T(0) : (hi ? T(-1) : T(1));
-      a.y *= sy;
-      b.y *= sy;
-      z[r] = (lo || hi) ? cplx<T>{a.x - b.y, a.y + b.x} : cplx<T>{T(0), T(0)};
-    }
-    inverse_row<T, N>(z, b1, t, P.tw);
-#pragma unroll
-    for (int e = 0; e < E; ++e) b1[pidx(t + NT * e)] = z[e];
+    for (int e = 0; e < E; ++e) S.put(t + NT * e, z[e]);
   }
   __syncthreads();
-  const bool dyn = !ph.kin;  // a prescribed flow needs the physical fields only
-  cplx<T> zf[E];             // wave 2: the averaged fields (other than eta, zeta)
+  if (w < 2) {
+    const unsigned at = (unsigned)(y * N + t);
+    if (w == 0) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const cplx<T> uv = z[e], hz = HZ.get(t + NT * e);
+        if constexpr (!GEN) put32(P.uvhz + NT * e, at, P4<T>{uv.x, uv.y, hz.x, hz.y});
+        else put32(P.uvhz + NT * e, at, P4<T>{uv.x, uv.y, field_value<T>(ph.fs0, uv, hz, ph), field_value<T>(ph.fs1, uv, hz, ph)});
+        z[e] = {hz.y * uv.y, hz.y * uv.x};
+        if (e % 4 == 3) sched_fence();
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const cplx<T> uv = UV.get(t + NT * e), hz = z[e];
+        z[e] = {T(0.5) * (uv.x * uv.x + uv.y * uv.y), hz.x * uv.x};
+        if (e % 4 == 3) sched_fence();
+      }
+    }
+    if (!ph.kin) {
+      cplx<T>* OA = P.RS + (w == 0 ? RS_ZV : RS_K) * rf;
+      cplx<T>* OB = P.RS + (w == 0 ? RS_ZU : RS_HU) * rf;
+      forward_row<T, N, SPLIT>(z, mine, t, P.tw, OA, OB, row);
+    }
+    if (w == 0) {
+      if constexpr (GEN) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const cplx<T> uv = UV.get(t + NT * e), hz = HZ.get(t + NT * e);
+          z[e] = {field_value<T>(ph.fs0, uv, hz, ph), field_value<T>(ph.fs1, uv, hz, ph)};
+          if (e % 4 == 3) sched_fence();
+        }
+        forward_row<T, N, SPLIT>(z, mine, t, P.tw, P.RS + RS_F0 * rf, P.RS + RS_F1 * rf, row);
+      }
+    } else if (!ph.kin) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int x = t + NT * e;
+        z[e] = {HZ.get(x).x * UV.get(x).y, T(0)};
+        if (e % 4 == 3) sched_fence();
+      }
+      forward_row<T, N, SPLIT>(z, mine, t, P.tw, P.RS + RS_HV * rf, nullptr, row);
+    }
+    return;
+  }
+  // f - u . grad of the wave's two fields: f = s u, s v for P, 0 or the averaged
+  // fields for g-tilde
+  const bool isP = w == 3;
+  const T sT = T(s);
+  cplx<T> a[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int x = t + NT * e;
+    const cplx<T> uv = UV.get(x);
+    T f = isP ? sT * uv.x : T(0);
+    if constexpr (GEN) f = isP ? f : field_value<T>(ph.fs0, uv, HZ.get(x), ph);
+    a[e].x = f - (uv.x * z[e].x + uv.y * z[e].y);
+    if (e % 4 == 3) sched_fence();
+  }
+  load_pair<T, N, true, false>(z, A + 2 * rf, A + 3 * rf, row, t);
+  inverse_row<T, N, SPLIT>(z, mine, t, P.tw);
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int x = t + NT * e;
+    const cplx<T> uv = UV.get(x);
+    T f = isP ? sT * uv.y : T(0);
+    if constexpr (GEN) f = isP ? f : field_value<T>(ph.fs1, uv, HZ.get(x), ph);
+    a[e].y = f - (uv.x * z[e].x + uv.y * z[e].y);
+    if (e % 4 == 3) sched_fence();
+  }
+  cplx<T>* OA = P.RS + (isP ? RS_PX : RS_GTH) * rf;
+  forward_row<T, N, SPLIT>(a, mine, t, P.tw, OA, OA + rf, row);
+}
+
+template <typename T, int N, bool GEN>
+__device__ __forceinline__ void rows_dyn_six(const StepPtrs<T>& P, const Phys& ph, double s,
+                                              int rowblock, T* lds) {
+  using G = DynGeo<T, N>;
+  constexpr int E = G::E, NT = G::NT, WR = G::WR, RB = G::RB;
+  constexpr bool SPLIT = G::SPLIT;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);  // the wave's role
+  const int lane = threadIdx.x % 64;
+  const int g = lane / NT, t = lane % NT;
+  const int y = rowblock * WR + g;
+  auto buf = [&](int i) { return lds + (i * WR + g) * RB; };
+  const SharedPair<T, SPLIT> UV{buf(0), buf(SPLIT ? 6 : 0)}, HZ{buf(1), buf(SPLIT ? 7 : 1)};
+  T* mine = buf(w);
+  constexpr Dims d = dims_of<N>();
+  constexpr size_t rf = d.rowfield_elems();
+  const unsigned row = (unsigned)y * (unsigned)d.NKXP;
+
+  cplx<T> z[E];
   if (w == 0) {
-    // u, v and the two averaged fields, interleaved for the gathers; zeta v, zeta u
-    P4<T>* out = P.uvhz + (size_t)y * N;
-    const bool plain = (ph.fs0 == FS_ETA && ph.fs1 == FS_ZETA);
+    load_pair<T, N, false, false>(z, P.IC + IC_U * rf, P.IC + IC_V * rf, row, t);
+  } else if (w == 1) {
+    load_depth_vorticity<T, N>(z, P.IC + IC_H * rf, P.IC + IC_V * rf, P.IC + IC_UY * rf, row, t);
+  } else {
+    const cplx<T>* A = P.IC + (IC_GTH + 2 * (w - 2)) * rf;  // g-tilde_0, g-tilde_1, P_x, P_y
+    load_pair<T, N, true, false>(z, A, A + rf, row, t);
+  }
+  inverse_row<T, N, SPLIT>(z, mine, t, P.tw);
+  if (w < 2) {
+    const SharedPair<T, SPLIT> S{w == 0 ? UV.a : HZ.a, w == 0 ? UV.b : HZ.b};
+#pragma unroll
+    for (int e = 0; e < E; ++e) S.put(t + NT * e, z[e]);
+  }
+  __syncthreads();
+  cplx<T>*OA = nullptr, *OB = nullptr;
+  if (w == 0) {
+    const unsigned at = (unsigned)(y * N + t);
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      const cplx<T> uv = b0[pidx(t + NT * e)], hz = b1[pidx(t + NT * e)];
-      if (plain) out[t + NT * e] = P4<T>{uv.x, uv.y, hz.x, hz.y};
-      else out[t + NT * e] = P4<T>{uv.x, uv.y, field_value<T>(ph.fs0, uv, hz, ph), field_value<T>(ph.fs1, uv, hz, ph)};
+      const cplx<T> uv = z[e], hz = HZ.get(t + NT * e);
+      if constexpr (!GEN) put32(P.uvhz + NT * e, at, P4<T>{uv.x, uv.y, hz.x, hz.y});
+      else put32(P.uvhz + NT * e, at, P4<T>{uv.x, uv.y, field_value<T>(ph.fs0, uv, hz, ph), field_value<T>(ph.fs1, uv, hz, ph)});
       z[e] = {hz.y * uv.y, hz.y * uv.x};
+      if (e % 4 == 3) sched_fence();
     }
+    if (!ph.kin) OA = P.RS + RS_ZV * rf, OB = P.RS + RS_ZU * rf;
   } else if (w == 1) {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      const cplx<T> uv = b0[pidx(t + NT * e)], hz = b1[pidx(t + NT * e)];
-      z[e] = {T(0.5) * (uv.x * uv.x + uv.y * uv.y), hz.x * uv.x};  // K, eta u
+      const cplx<T> uv = UV.get(t + NT * e), hz = z[e];
+      z[e] = {T(0.5) * (uv.x * uv.x + uv.y * uv.y), hz.x * uv.x};
+      if (e % 4 == 3) sched_fence();
     }
+    if (!ph.kin) OA = P.RS + RS_K * rf, OB = P.RS + RS_HU * rf;
   } else {
+    // f - u . grad (one field per wave): f = s u or s v for P, 0 or the averaged
+    // field for g-tilde
+    const bool isP = w >= 4;
+    const T sT = T(s);
+    T* pair = buf(w & ~1);  // the even wave's buffer takes the odd wave's values
+    const int fs = (w == 2) ? ph.fs0 : ph.fs1;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      const cplx<T> uv = b0[pidx(t + NT * e)], hz = b1[pidx(t + NT * e)];
-      z[e] = {hz.x * uv.y, T(0)};  // eta v
-      if (ph.gen) zf[e] = {field_value<T>(ph.fs0, uv, hz, ph), field_value<T>(ph.fs1, uv, hz, ph)};
+      const int x = t + NT * e;
+      const cplx<T> uv = UV.get(x);
+      T f = isP ? sT * ((w & 1) ? uv.y : uv.x) : T(0);
+      if constexpr (GEN) f = isP ? f : field_value<T>(fs, uv, HZ.get(x), ph);
+      z[e].x = f - (uv.x * z[e].x + uv.y * z[e].y);
+      if (e % 4 == 3) sched_fence();
+    }
+    if (w & 1) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) pair[t + NT * e] = z[e].x;
+      if (w == 3) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const int x = t + NT * e;
+          z[e] = {HZ.get(x).x * UV.get(x).y, T(0)};
+          if (e % 4 == 3) sched_fence();
+        }
+        if (!ph.kin) OA = P.RS + RS_HV * rf;
+      } else if constexpr (GEN) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const cplx<T> uv = UV.get(t + NT * e), hz = HZ.get(t + NT * e);
+          z[e] = {field_value<T>(ph.fs0, uv, hz, ph), field_value<T>(ph.fs1, uv, hz, ph)};
+          if (e % 4 == 3) sched_fence();
+        }
+        OA = P.RS + RS_F0 * rf, OB = P.RS + RS_F1 * rf;
+      }
+    } else {
+      OA = P.RS + (w == 2 ? RS_GTH : RS_PX) * rf, OB = OA + rf;
     }
   }
   __syncthreads();
-  if (w == 0) {
-    if (dyn) forward_row<T, N, true, false>(z, bw, t, P.tw, RSr + RS_ZV * rf, RSr + RS_ZU * rf);
-  } else if (w == 1) {
-    if (dyn) forward_row<T, N, true, false>(z, bw, t, P.tw, RSr + RS_K * rf, RSr + RS_HU * rf);
-  } else {
-    // the averaged fields' spectra, for the Eulerian means
-    if (ph.gen) forward_row<T, N, true, false>(zf, bw, t, P.tw, RSr + RS_F0 * rf, RSr + RS_F1 * rf);
-    if (dyn) forward_row<T, N, false, false>(z, bw, t, P.tw, RSr + RS_HV * rf, nullptr);
+  if (!OA) return;
+  if (w == 2 || w == 4) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) z[e].y = mine[t + NT * e];
+    xsync<NT>();
   }
+  forward_row<T, N, SPLIT>(z, mine, t, P.tw, OA, OB, row);
 }
 
-// Geometry of the dynamics rows pass: float runs take blocks of three waves
-// sharing one group of rows; float64 (whose registers leave room for one wave
-// per SIMD) blocks of ROW_WAVES waves, one row group each, every product on
-// the row's own wave.
-template <typename T, int N>
-struct DynGeo {
-  static constexpr bool COOP = sizeof(T) == 4;
-  static constexpr int WR = 64 / RowGeo<N>::NT;  // rows per wave
-  static constexpr int THREADS = COOP ? 3 * 64 : 64 * ROW_WAVES;
-  static constexpr int RPB = COOP ? WR : RowGeo<N>::RPB;  // rows per block
-  static constexpr int LDS = (COOP ? 3 * WR : RowGeo<N>::RPB) * RowGeo<N>::L;
-  static_assert(RowGeo<N>::NT <= 64 && 64 % RowGeo<N>::NT == 0, "row groups within a wave");
-};
-
-// float: three resident waves per SIMD (at most 168 registers): one block of
-// the cooperative form on each
-template <typename T>
-__host__ __device__ constexpr int dyn_waves() {
-  return sizeof(T) == 4 ? 3 : 1;
+template <typename T, int N, bool GEN>
+__device__ __forceinline__ void rows_dyn_body(const StepPtrs<T>& P, const Phys& ph, double s,
+                                              int rowblock, T* lds) {
+  if constexpr (DynGeo<T, N>::SIX) rows_dyn_six<T, N, GEN>(P, ph, s, rowblock, lds);
+  else rows_dyn_four<T, N, GEN>(P, ph, s, rowblock, lds);
 }
 
-template <typename T, int N>
-__global__ void __launch_bounds__((DynGeo<T, N>::THREADS), (dyn_waves<T>())) k_rows_dyn(StepPtrs<T> P, Dims d,
-                                                                                       Phys ph, int remap) {
-  __shared__ cplx<T> lds[DynGeo<T, N>::LDS];
+// GEN: averaged fields other than (eta, zeta)
+template <typename T, int N, bool GEN>
+__global__ void __launch_bounds__((DynGeo<T, N>::THREADS), (DynGeo<T, N>::MIN_WAVES))
+    k_rows_dyn(StepPtrs<T> P, Phys ph, double s, int remap) {
+  __shared__ __align__(16) T lds[DynGeo<T, N>::LDS];
   int rowblock, unused, z;
   xcd_split(gridDim.x, 1, rowblock, unused, z, remap);
-  if constexpr (DynGeo<T, N>::COOP) rows_dyn_coop<T, N>(P, d, ph, rowblock, lds);
-  else rows_dyn_body<T, N>(P, d, ph, rowblock, lds);
+  rows_dyn_body<T, N, GEN>(P, ph, s, rowblock, lds);
 }
 
 // --------------------------------------------------------------------------
-// rows_rhs
+// rows_rhs: strategy 2
 // --------------------------------------------------------------------------
-// Tasks, one wavefront per row and task.  Float runs of N >= 512 take two:
-//   RT_S2  strategy 2: both xi components (eq. (4.5a)) and g-bar of eta and
-//          zeta (eq. (4.5b)), from one transform of xi and one gather
-//   RT_S1  strategy 1: g-tilde of eta and zeta (eq. (4.1); their sources are
-//          added in the column pass) and both P components (eq. (3.9) in P form)
-// (each wave holds two output pairs; the rows' 2N waves at two per SIMD run in
-// one round).  Smaller grids and float64, where more, shorter waves pay
-// better, take four: RT4_XI (xi), RT4_GB (g-bar), RT4_GT (g-tilde), RT4_P (P),
-// the two strategy-2 tasks each transforming xi and gathering at x + xi.
+// Four waves, the pairs (xi_x, xi_y) and (g-bar_0, g-bar_1) of two waves each.
+// Wave 0 inverse-transforms xi and shares it, waves 1, 2 and 3 the gradients of
+// xi_x, xi_y and g-bar_0; then wave 0 the gradient of g-bar_1 while waves 1 and 3
+// gather their pair at x + xi.  Waves 2 and 0 hand their half of the pair's
+//   u(x+xi) - w - (w . grad) xi   (both components, eq. (4.5a)),
+//   f(x+xi) - w . grad g-bar      (eq. (4.5b))
+// to waves 1 and 3, which forward-transform it.  w = xi / (t - tau) is the
+// partial-mean velocity (u / 2 at t = tau).
+template <typename T, int N>
+struct RhsGeo : CoopGeo<T, N> {
+  using G = CoopGeo<T, N>;
+  static constexpr int WAVES = 4, THREADS = 64 * WAVES;
+  static constexpr int BUFS = G::SPLIT ? 6 : 5;  // four transform buffers, then xi
+  static constexpr int LDS = BUFS * G::WR * G::RB;
+  static constexpr int MIN_WAVES = sizeof(T) == 4 ? 4 : 2;
+};
 
-// The mean right-hand-side rows pass, two tasks per row.
-// Task 0, strategy 2: with w = xi / (t - tau) the partial-mean velocity (u / 2
-// at t = tau, SPOS false), the gathered terms at x + xi less w . grad of
-// (xi_x, xi_y) and of (g-bar_h, g-bar_zeta): one transform of xi serves both,
-// and one gather of the interleaved point serves all four fields.
 template <typename T, int N, bool CUB, bool SPOS>
-__device__ __forceinline__ void rows_rhs_s2(const StepPtrs<T>& P, const Dims& d, double s, int y, int t,
-                                            cplx<T>* buf, cplx<T>* xs) {
-  using G = RowGeo<N>;
-  constexpr int E = G::E, NT = G::NT;
-  const size_t rf = d.rowfield_elems();
-  const cplx<T>* ICr = P.IC + (size_t)y * d.NKXP;
-  cplx<T>* RSr = P.RS + (size_t)y * d.NKXP;
-  const P4<T>* F = P.uvhz;
-  const P4<T>* Fr = P.uvhz + (size_t)y * N;
+__device__ __forceinline__ void rhs_products(const P4<T>* __restrict__ F, double s, int y, int t, int w,
+                                             const SharedPair<T, CoopGeo<T, N>::SPLIT>& XI,
+                                             cplx<T> (&z)[fft_E<N>()], T* pair) {
+  constexpr int E = fft_E<N>(), NT = N / E;
+  constexpr int GG = CUB ? 1 : 4;  // points with their loads in flight together
+  static_assert(E % GG == 0, "gather groups");
   const T inv_s = SPOS ? T(1.0 / s) : T(0);
-  // w at point e from xi
-  auto wof = [&](int e, cplx<T> xi) -> cplx<T> {
+  const unsigned at = (unsigned)(y * N);
+  auto velocity = [&](int x, cplx<T> xi) -> cplx<T> {
     if constexpr (SPOS) {
       return {xi.x * inv_s, xi.y * inv_s};
     } else {
-      const P4<T> q = Fr[t + NT * e];
+      const P4<T> q = at32(F, at + x);
       return {T(0.5) * q.u, T(0.5) * q.v};
     }
   };
-  cplx<T> a[E], guv[E], ghz[E], b[E];
-  // displacement xi, kept in the row's second LDS buffer (xs) after the gathers
-  load_pair<T, N, false, false>(a, ICr + IC_XIX * rf, ICr + IC_XIY * rf, t);
-  inverse_row<T, N>(a, buf, t, P.tw);
-#pragma unroll
-  for (int e = 0; e < E; ++e) xs[pidx(t + NT * e)] = a[e];
-  // gathered (u, v) less w, and (eta, zeta), at x + xi
-  if constexpr (CUB) {
-    // cubic gathers: 16 corners per point, one point in flight at a time
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const cplx<T> w = wof(e, a[e]);
-      const cplx<T> g = gather2_cubic<T, N, 0>(F, t + NT * e, y, a[e].x, a[e].y);
-      guv[e] = {g.x - w.x, g.y - w.y};
-      ghz[e] = gather2_cubic<T, N, 1>(F, t + NT * e, y, a[e].x, a[e].y);
-      sched_fence();
-    }
-  } else {
-    constexpr int GG = 4;  // points with their loads in flight together
-    static_assert(E % GG == 0, "gather groups");
+  if (w & 1) {
 #pragma unroll
     for (int e0 = 0; e0 < E; e0 += GG) {
 #pragma unroll
       for (int e = e0; e < e0 + GG; ++e) {
-        const cplx<T> w = wof(e, a[e]);
-        const P4<T> g = gather4<T, N>(F, t + NT * e, y, a[e].x, a[e].y);
-        guv[e] = {g.u - w.x, g.v - w.y};
-        ghz[e] = {g.h, g.z};
+        const int x = t + NT * e;
+        const cplx<T> xi = XI.get(x), v = velocity(x, xi);
+        const cplx<T> g = gather_pair<T, N, CUB>(F, w >> 1, x, y, xi.x, xi.y);
+        const T wx = (w == 1) ? v.x : T(0);
+        z[e] = {g.x - wx - (v.x * z[e].x + v.y * z[e].y), g.y};
       }
       sched_fence();
     }
-  }
-  // less w . grad of each component (a rolled loop: unrolled, the compiler
-  // interleaves the four transforms and runs out of registers)
-#pragma unroll 2
-  for (int c = 0; c < 4; ++c) {
-    const int f = (c == 0) ? IC_XIX : (c == 1) ? IC_XIY : (c == 2) ? IC_GBH : IC_GBZ;
-    load_pair<T, N, true, false>(b, ICr + f * rf, ICr + (f + 1) * rf, t);
-    inverse_row<T, N>(b, buf, t, P.tw);
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const cplx<T> w = wof(e, xs[pidx(t + NT * e)]);
-      const T dw = w.x * b[e].x + w.y * b[e].y;
-      if (c == 0) guv[e].x = guv[e].x - dw;
-      else if (c == 1) guv[e].y = guv[e].y - dw;
-      else if (c == 2) ghz[e].x = ghz[e].x - dw;
-      else ghz[e].y = ghz[e].y - dw;
-    }
-    sched_fence();
-  }
-  forward_row<T, N, true>(guv, buf, t, P.tw, RSr + RS_XIX * rf, RSr + RS_XIY * rf);
-  forward_row<T, N, true>(ghz, buf, t, P.tw, RSr + RS_GBH * rf, RSr + RS_GBZ * rf);
-}
-
-// Task 1, strategy 1 and the Lagrangian-mean velocity: f - u . grad g-tilde
-// and (t - tau) u - u . grad P; the velocity is re-read where it is used.  For
-// the default pair (eta, zeta), src = 0: the source f is added in the column
-// pass from the stage spectra (as the Eulerian accumulators take it), so that
-// only the advection term goes through physical space and float32 rounding;
-// other averaged fields (src = 1) take f here.
-template <typename T, int N>
-__device__ __forceinline__ void rows_rhs_s1(const StepPtrs<T>& P, const Dims& d, double s, int y, int t,
-                                            cplx<T>* buf, int src) {
-  using G = RowGeo<N>;
-  constexpr int E = G::E, NT = G::NT;
-  const size_t rf = d.rowfield_elems();
-  const cplx<T>* ICr = P.IC + (size_t)y * d.NKXP;
-  cplx<T>* RSr = P.RS + (size_t)y * d.NKXP;
-  const P4<T>* Fr = P.uvhz + (size_t)y * N;
-  const T sT = T(s), fs = src ? T(1) : T(0);
-  cplx<T> agt[E], apx[E], b[E];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const int f = (c == 0) ? IC_GTH : (c == 1) ? IC_GTZ : (c == 2) ? IC_PX : IC_PY;
-    load_pair<T, N, true, false>(b, ICr + f * rf, ICr + (f + 1) * rf, t);
-    inverse_row<T, N>(b, buf, t, P.tw);
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const P4<T> q = Fr[t + NT * e];
-      const T f = (c == 0) ? fs * q.h : (c == 1) ? fs * q.z : (c == 2) ? sT * q.u : sT * q.v;
-      const T r = f - (q.u * b[e].x + q.v * b[e].y);
-      if (c == 0) agt[e].x = r;
-      else if (c == 1) agt[e].y = r;
-      else if (c == 2) apx[e].x = r;
-      else apx[e].y = r;
-    }
-    sched_fence();
-  }
-  forward_row<T, N, true>(agt, buf, t, P.tw, RSr + RS_GTH * rf, RSr + RS_GTZ * rf);
-  forward_row<T, N, true>(apx, buf, t, P.tw, RSr + RS_PX * rf, RSr + RS_PY * rf);
-}
-
-template <typename T, int N, bool CUB>
-__device__ __forceinline__ void rows_rhs_body4(const StepPtrs<T>& P, const Dims& d, double s, int rowblock,
-                                              int task, cplx<T>* lds, int src) {
-  using G = RowGeo<N>;
-  constexpr int E = G::E, NT = G::NT;
-  const int grp = row_group<NT>(), t = threadIdx.x % NT;
-  const int y = rowblock * G::RPB + grp;  // the grid covers the rows exactly
-  cplx<T>* buf = lds + grp * G::L;
-  const size_t rf = d.rowfield_elems();
-  const cplx<T>* ICr = P.IC + (size_t)y * d.NKXP;
-  cplx<T>* RSr = P.RS + (size_t)y * d.NKXP;
-  const P4<T>* F = P.uvhz;
-  const P4<T>* Fr = P.uvhz + (size_t)y * N;
-  constexpr int K = kcut<N>();
-
-  cplx<T> a[E], b[E];
-  if (task == RT4_XI || task == RT4_GB) {
-    // displacement xi, partial-mean velocity w = xi / (t - tau) (u/2 at t = tau)
-    load_pair<T, N, false, false>(a, ICr + IC_XIX * rf, ICr + IC_XIY * rf, t);
-    inverse_row<T, N>(a, buf, t, P.tw);
-    cplx<T> w[E];
-    if (s > 0.0) {
-      const T inv_s = T(1.0 / s);
-#pragma unroll
-      for (int e = 0; e < E; ++e) w[e] = {a[e].x * inv_s, a[e].y * inv_s};
-    } else {
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const P4<T> q = Fr[t + NT * e];
-        w[e] = {T(0.5) * q.u, T(0.5) * q.v};
-      }
-    }
-    sched_fence();
-    // gathered terms at x + xi, in groups of GG points (bounds loads in flight)
-    constexpr int GG = 4;
-    static_assert(E % GG == 0, "gather groups");
-    const bool xi_task = (task == RT4_XI);
-    if constexpr (CUB) {
-      // cubic gathers: 16 corners per point, one point in flight at a time
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        if (xi_task) {
-          const cplx<T> g = gather2_cubic<T, N, 0>(F, t + NT * e, y, a[e].x, a[e].y);
-          a[e] = {g.x - w[e].x, g.y - w[e].y};
-        } else {
-          a[e] = gather2_cubic<T, N, 1>(F, t + NT * e, y, a[e].x, a[e].y);
-        }
-        sched_fence();
-      }
-    } else if (xi_task) {
-#pragma unroll
-      for (int e0 = 0; e0 < E; e0 += GG) {
-#pragma unroll
-        for (int e = e0; e < e0 + GG; ++e) {
-          const cplx<T> g = gather2<T, N, 0>(F, t + NT * e, y, a[e].x, a[e].y);
-          a[e] = {g.x - w[e].x, g.y - w[e].y};
-        }
-        sched_fence();
-      }
-    } else {
-#pragma unroll
-      for (int e0 = 0; e0 < E; e0 += GG) {
-#pragma unroll
-        for (int e = e0; e < e0 + GG; ++e) a[e] = gather2<T, N, 1>(F, t + NT * e, y, a[e].x, a[e].y);
-        sched_fence();
-      }
-    }
-    // minus w . grad of (xi_x, xi_y) or of (g-bar_h, g-bar_zeta)
-    const int f1 = xi_task ? IC_XIX : IC_GBH, f2 = xi_task ? IC_XIY : IC_GBZ;
-    load_pair<T, N, true, false>(b, ICr + f1 * rf, ICr + (f1 + 1) * rf, t);
-    inverse_row<T, N>(b, buf, t, P.tw);
-#pragma unroll
-    for (int e = 0; e < E; ++e) a[e].x = a[e].x - (w[e].x * b[e].x + w[e].y * b[e].y);
-    load_pair<T, N, true, false>(b, ICr + f2 * rf, ICr + (f2 + 1) * rf, t);
-    inverse_row<T, N>(b, buf, t, P.tw);
-#pragma unroll
-    for (int e = 0; e < E; ++e) a[e].y = a[e].y - (w[e].x * b[e].x + w[e].y * b[e].y);
-    const int o = xi_task ? RS_XIX : RS_GBH;
-    forward_row<T, N, true>(a, buf, t, P.tw, RSr + o * rf, RSr + (o + 1) * rf);
   } else {
-    // f - u . grad g-tilde (f only when src: see rows_rhs_s1), or (t - tau) u - u . grad P
-    const bool gt = (task == RT4_GT);
-    const T sT = T(s), fs = src ? T(1) : T(0);
-    cplx<T> uv[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      const P4<T> q = Fr[t + NT * e];
-      uv[e] = {q.u, q.v};
+      const int x = t + NT * e;
+      const cplx<T> v = velocity(x, XI.get(x));
+      const T wy = (w == 2) ? v.y : T(0);
+      pair[x] = -wy - (v.x * z[e].x + v.y * z[e].y);
+      if (e % 4 == 3) sched_fence();
     }
-    const int f1 = gt ? IC_GTH : IC_PX, f2 = gt ? IC_GTZ : IC_PY;
-    load_pair<T, N, true, false>(b, ICr + f1 * rf, ICr + (f1 + 1) * rf, t);
-    inverse_row<T, N>(b, buf, t, P.tw);
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const T f = gt ? fs * Fr[t + NT * e].h : sT * uv[e].x;
-      a[e].x = f - (uv[e].x * b[e].x + uv[e].y * b[e].y);
-    }
-    load_pair<T, N, true, false>(b, ICr + f2 * rf, ICr + (f2 + 1) * rf, t);
-    inverse_row<T, N>(b, buf, t, P.tw);
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const T f = gt ? fs * Fr[t + NT * e].z : sT * uv[e].y;
-      a[e].y = f - (uv[e].x * b[e].x + uv[e].y * b[e].y);
-    }
-    const int o = gt ? RS_GTH : RS_PX;
-    forward_row<T, N, true>(a, buf, t, P.tw, RSr + o * rf, RSr + (o + 1) * rf);
   }
 }
 
 template <typename T, int N, bool CUB>
-__device__ __forceinline__ void rows_rhs_body(const StepPtrs<T>& P, const Dims& d, double s, int rowblock,
-                                              int task, cplx<T>* lds, int src) {
-  using G = RowGeo<N>;
-  constexpr int NT = G::NT;
-  if constexpr (!rhs_merged<T, N>()) {
-    rows_rhs_body4<T, N, CUB>(P, d, s, rowblock, task, lds, src);
-    return;
-  }
-  const int grp = row_group<NT>(), t = threadIdx.x % NT;
-  const int y = rowblock * G::RPB + grp;  // the grid covers the rows exactly
-  cplx<T>* buf = lds + grp * G::L;
-  if (task == RT_S2) {
-    cplx<T>* xs = lds + (G::RPB + grp) * G::L;
-    if (s > 0.0) rows_rhs_s2<T, N, CUB, true>(P, d, s, y, t, buf, xs);
-    else rows_rhs_s2<T, N, CUB, false>(P, d, s, y, t, buf, xs);
+__device__ __forceinline__ void rows_rhs_body(const StepPtrs<T>& P, double s, int rowblock, T* lds) {
+  using G = RhsGeo<T, N>;
+  constexpr int E = G::E, NT = G::NT, WR = G::WR, RB = G::RB;
+  constexpr bool SPLIT = G::SPLIT;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);  // the wave's role
+  const int lane = threadIdx.x % 64;
+  const int g = lane / NT, t = lane % NT;
+  const int y = rowblock * WR + g;
+  auto buf = [&](int i) { return lds + (i * WR + g) * RB; };
+  const SharedPair<T, SPLIT> XI{buf(4), buf(SPLIT ? 5 : 4)};
+  T* mine = buf(w);
+  constexpr Dims d = dims_of<N>();
+  constexpr size_t rf = d.rowfield_elems();
+  const unsigned row = (unsigned)y * (unsigned)d.NKXP;
+
+  cplx<T> z[E];
+  if (w == 0) {
+    load_pair<T, N, false, false>(z, P.IC + IC_XIX * rf, P.IC + IC_XIY * rf, row, t);
   } else {
-    rows_rhs_s1<T, N>(P, d, s, y, t, buf, src);
+    const cplx<T>* A = P.IC + (IC_XIX + 2 * (w - 1)) * rf;  // xi_x, xi_y, g-bar_0
+    load_pair<T, N, true, false>(z, A, A + rf, row, t);
   }
+  inverse_row<T, N, SPLIT>(z, mine, t, P.tw);
+  if (w == 0) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) XI.put(t + NT * e, z[e]);
+  }
+  __syncthreads();
+  if (w == 0) {
+    load_pair<T, N, true, false>(z, P.IC + IC_GBZ * rf, P.IC + (IC_GBZ + 1) * rf, row, t);
+    inverse_row<T, N, SPLIT>(z, mine, t, P.tw);
+  }
+  T* pair = buf(w == 0 ? 3 : 1);  // the transform buffer of the pair's other wave
+  if (s > 0.0) rhs_products<T, N, CUB, true>(P.uvhz, s, y, t, w, XI, z, pair);
+  else rhs_products<T, N, CUB, false>(P.uvhz, s, y, t, w, XI, z, pair);
+  __syncthreads();
+  if (!(w & 1)) return;
+#pragma unroll
+  for (int e = 0; e < E; ++e) z[e].y = z[e].y + mine[t + NT * e];
+  xsync<NT>();
+  cplx<T>* OA = P.RS + (w == 1 ? RS_XIX : RS_GBH) * rf;
+  forward_row<T, N, SPLIT>(z, mine, t, P.tw, OA, OA + rf, row);
 }
 
-// two-task form: two resident waves per SIMD, as many as its two LDS buffers
-// per row allow, so that every row's two tasks are resident at once
-template <typename T, int N>
-__host__ __device__ constexpr int rhs_waves() {
-  return rhs_merged<T, N>() ? 2 : 1;
-}
-template <typename T, int N>
-__host__ __device__ constexpr int rhs_lds() {
-  return (rhs_merged<T, N>() ? 2 : 1) * RowGeo<N>::RPB * RowGeo<N>::L;
-}
-
-// CUB: cubic instead of bilinear strategy-2 gathers; src: the strategy-1
-// sources are formed here (other averaged fields) rather than in the column pass
+// CUB: cubic instead of bilinear strategy-2 gathers
 template <typename T, int N, bool CUB>
-__global__ void __launch_bounds__(64 * ROW_WAVES, (rhs_waves<T, N>())) k_rows_rhs(StepPtrs<T> P, Dims d, double s,
-                                                                              int remap, int src) {
-  __shared__ cplx<T> lds[rhs_lds<T, N>()];  // transform buffers (and xi, two-task form)
-  int rowblock, task, z;
-  xcd_split(gridDim.x, gridDim.y, rowblock, task, z, remap);  // grid = (row blocks, tasks)
-  rows_rhs_body<T, N, CUB>(P, d, s, rowblock, task, lds, src);
+__global__ void __launch_bounds__((RhsGeo<T, N>::THREADS), (RhsGeo<T, N>::MIN_WAVES))
+    k_rows_rhs(StepPtrs<T> P, double s, int remap) {
+  __shared__ __align__(16) T lds[RhsGeo<T, N>::LDS];
+  int rowblock, unused, z;
+  xcd_split(gridDim.x, 1, rowblock, unused, z, remap);
+  rows_rhs_body<T, N, CUB>(P, s, rowblock, lds);
 }
 
 // --------------------------------------------------------------------------
@@ -764,27 +789,26 @@ __global__ void __launch_bounds__(64 * ROW_WAVES, (rhs_waves<T, N>())) k_rows_rh
 // Order of work keeps at most three lane arrays live beside a transform.
 // --------------------------------------------------------------------------
 template <typename T, int N, bool CUB>
-__device__ __forceinline__ void rows_mom_body(const StepPtrs<T>& P, const Dims& d, double s, int rowblock,
-                                              int task, cplx<T>* lds) {
+__device__ __forceinline__ void rows_mom_body(const StepPtrs<T>& P, double s, int rowblock,
+                                              int task, T* lds) {
   using G = RowGeo<N>;
   constexpr int E = G::E, NT = G::NT;
   const int grp = row_group<NT>(), t = threadIdx.x % NT;
   const int y = rowblock * G::RPB + grp;
-  cplx<T>* buf = lds + grp * G::L;
-  const size_t rf = d.rowfield_elems();
-  const cplx<T>* ICr = P.IC + (size_t)y * d.NKXP;
-  cplx<T>* RSr = P.RS + (size_t)y * d.NKXP;
+  T* buf = lds + grp * 2 * G::L;
+  constexpr Dims d = dims_of<N>();
+  constexpr size_t rf = d.rowfield_elems();
+  const unsigned row = (unsigned)y * (unsigned)d.NKXP;
   const P4<T>* F = P.uvhz;
-  const P4<T>* Fr = P.uvhz + (size_t)y * N;
   const bool ix = (task == 0);
   cplx<T> a[E], b[E], c[E];
   // d_i xi_x, d_i xi_y: i kx in the row pass for i = x, the column pass's i ky versions for i = y
-  if (ix) load_pair<T, N, true, true>(b, ICr + IC_XIX * rf, ICr + IC_XIY * rf, t);
-  else load_pair<T, N, false, false>(b, ICr + IC_XIX_Y * rf, ICr + IC_XIY_Y * rf, t);
+  if (ix) load_pair<T, N, true, true>(b, P.IC + IC_XIX * rf, P.IC + IC_XIY * rf, row, t);
+  else load_pair<T, N, false, false>(b, P.IC + IC_XIX_Y * rf, P.IC + IC_XIY_Y * rf, row, t);
   inverse_row<T, N>(b, buf, t, P.tw);
   // stretching: a.x = -(g_x d_i xi_x + g_y d_i xi_y) / s
   if (s > 0.0) {
-    load_pair<T, N, false, false>(c, ICr + IC_GMX * rf, ICr + IC_GMY * rf, t);
+    load_pair<T, N, false, false>(c, P.IC + IC_GMX * rf, P.IC + IC_GMY * rf, row, t);
     inverse_row<T, N>(c, buf, t, P.tw);
     const T inv_s = T(1.0 / s);
 #pragma unroll
@@ -794,13 +818,13 @@ __device__ __forceinline__ void rows_mom_body(const StepPtrs<T>& P, const Dims& 
     for (int e = 0; e < E; ++e) a[e] = {T(0), T(0)};
   }
   // xi (kept until the gathers consume it)
-  load_pair<T, N, false, false>(c, ICr + IC_XIX * rf, ICr + IC_XIY * rf, t);
+  load_pair<T, N, false, false>(c, P.IC + IC_XIX * rf, P.IC + IC_XIY * rf, row, t);
   inverse_row<T, N>(c, buf, t, P.tw);
   // advection: a.x -= w . grad g_i with w = xi / s (u / 2 at s = 0), formed on the fly
   {
     cplx<T> dg[E];
     const int gi = ix ? IC_GMX : IC_GMY;
-    load_pair<T, N, true, false>(dg, ICr + gi * rf, ICr + (gi + 1) * rf, t);
+    load_pair<T, N, true, false>(dg, P.IC + gi * rf, P.IC + (gi + 1) * rf, row, t);
     inverse_row<T, N>(dg, buf, t, P.tw);
     if (s > 0.0) {
       const T inv_s = T(1.0 / s);
@@ -809,7 +833,7 @@ __device__ __forceinline__ void rows_mom_body(const StepPtrs<T>& P, const Dims& 
     } else {
 #pragma unroll
       for (int e = 0; e < E; ++e) {
-        const P4<T> q = Fr[t + NT * e];
+        const P4<T> q = at32(F, (unsigned)(y * N + t) + NT * e);
         a[e].x = a[e].x - (T(0.5) * q.u * dg[e].x + T(0.5) * q.v * dg[e].y);
       }
     }
@@ -819,7 +843,7 @@ __device__ __forceinline__ void rows_mom_body(const StepPtrs<T>& P, const Dims& 
   if constexpr (CUB) {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      const cplx<T> g = gather2_cubic<T, N, 0>(F, t + NT * e, y, c[e].x, c[e].y);
+      const cplx<T> g = gather2_cubic<T, N>(F, 0, t + NT * e, y, c[e].x, c[e].y);
       a[e].x = a[e].x + (g.x * (dxi + b[e].x) + g.y * (dyi + b[e].y));
       sched_fence();
     }
@@ -829,21 +853,21 @@ __device__ __forceinline__ void rows_mom_body(const StepPtrs<T>& P, const Dims& 
     for (int e0 = 0; e0 < E; e0 += GG) {
 #pragma unroll
       for (int e = e0; e < e0 + GG; ++e) {
-        const cplx<T> g = gather2<T, N, 0>(F, t + NT * e, y, c[e].x, c[e].y);
+        const cplx<T> g = gather2<T, N>(F, 0, t + NT * e, y, c[e].x, c[e].y);
         a[e].x = a[e].x + (g.x * (dxi + b[e].x) + g.y * (dyi + b[e].y));
       }
       sched_fence();
     }
   }
-  forward_row<T, N, false>(a, buf, t, P.tw, RSr + (ix ? RS_GMX : RS_GMY) * rf, nullptr);
+  forward_row<T, N>(a, buf, t, P.tw, P.RS + (ix ? RS_GMX : RS_GMY) * rf, nullptr, row);
 }
 
 template <typename T, int N, bool CUB>
-__global__ void __launch_bounds__(64 * ROW_WAVES) k_rows_mom(StepPtrs<T> P, Dims d, double s, int remap) {
-  __shared__ cplx<T> lds[RowGeo<N>::RPB * RowGeo<N>::L];
+__global__ void __launch_bounds__(64 * ROW_WAVES) k_rows_mom(StepPtrs<T> P, double s, int remap) {
+  __shared__ __align__(16) T lds[RowGeo<N>::RPB * 2 * RowGeo<N>::L];
   int rowblock, task, z;
   xcd_split(gridDim.x, gridDim.y, rowblock, task, z, remap);  // grid = (row blocks, 2 components)
-  rows_mom_body<T, N, CUB>(P, d, s, rowblock, task, lds);
+  rows_mom_body<T, N, CUB>(P, s, rowblock, task, lds);
 }
 
 // --------------------------------------------------------------------------
@@ -904,21 +928,21 @@ __device__ __forceinline__ cplx<TS> rk4v(int stage, cplx<TS>& y, cplx<TS>& lo, c
 // writes back (a at stages 0-2, y and lo at stage 3)
 template <typename TS>
 __device__ __forceinline__ void rk4_load(int stage, const cplx<TS>* Yp, const cplx<TS>* Lp, const cplx<TS>* Ap,
-                                         cplx<TS>& y, cplx<TS>& lo, cplx<TS>& a) {
-  y = *Yp;
-  if (stage >= 1) a = *Ap;
+                                         unsigned j, cplx<TS>& y, cplx<TS>& lo, cplx<TS>& a) {
+  y = at32(Yp, j);
+  if (stage >= 1) a = at32(Ap, j);
   if constexpr (std::is_same<TS, float>::value) {
-    if (stage == 3) lo = *Lp;
+    if (stage == 3) lo = at32(Lp, j);
   }
 }
 template <typename TS>
-__device__ __forceinline__ void rk4_store(int stage, cplx<TS>* Yp, cplx<TS>* Lp, cplx<TS>* Ap, const cplx<TS>& y,
-                                          const cplx<TS>& lo, const cplx<TS>& a) {
+__device__ __forceinline__ void rk4_store(int stage, cplx<TS>* Yp, cplx<TS>* Lp, cplx<TS>* Ap, unsigned j,
+                                          const cplx<TS>& y, const cplx<TS>& lo, const cplx<TS>& a) {
   if (stage <= 2) {
-    *Ap = a;
+    put32(Ap, j, a);
   } else {
-    *Yp = y;
-    if constexpr (std::is_same<TS, float>::value) *Lp = lo;
+    put32(Yp, j, y);
+    if constexpr (std::is_same<TS, float>::value) put32(Lp, j, lo);
   }
 }
 
@@ -961,7 +985,7 @@ __device__ __forceinline__ void tile_load(const ColCtx<T, N, C>& cx, const cplx<
 #pragma unroll
   for (int k = 0; k < E; ++k) val[k] = buffer_cplx<T>(rs, voff, (unsigned)k * dy);
 #pragma unroll
-  for (int k = 0; k < E; ++k) dstl[pidx(y0 + NT * k)] = in ? val[k] : cplx<T>{T(0), T(0)};
+  for (int k = 0; k < E; ++k) dstl[pidx(LaneIdx{y0, NT * k})] = in ? val[k] : cplx<T>{T(0), T(0)};
   __syncthreads();
 }
 
@@ -973,14 +997,14 @@ __device__ __forceinline__ void tile_store(const ColCtx<T, N, C>& cx, cplx<T>* _
                                            const Dims& d) {
   constexpr int LC = ColCtx<T, N, C>::LC;
   constexpr int NTH = C * (N / fft_E<N>());
-  static_assert((N * C) % NTH == 0, "tile store rounds");
+  static_assert((N * C) % NTH == 0 && NTH % C == 0, "tile store rounds");
   __syncthreads();
+  const int c = (int)threadIdx.x % C, y0 = (int)threadIdx.x / C;
+  const unsigned at = (unsigned)(y0 * d.NKXP + cx.kx0 + c);
+  if (cx.kx0 + c <= kcut<N>()) {
 #pragma unroll
-  for (int i0 = 0; i0 < N * C; i0 += NTH) {
-    const int i = i0 + (int)threadIdx.x;
-    const int c = i % C, y = i / C;
-    const int kx = cx.kx0 + c;
-    if (kx <= kcut<N>()) dst[(size_t)y * d.NKXP + kx] = cx.lds[c * LC + pidx(y)];
+    for (int k = 0; k < N * C / NTH; ++k)
+      put32(dst + (size_t)(NTH / C) * k * d.NKXP, at, cx.lds[c * LC + pidx(LaneIdx{y0, (NTH / C) * k})]);
   }
   __syncthreads();
 }
@@ -994,9 +1018,9 @@ __device__ __forceinline__ void column_forward_lds(const ColCtx<T, N, C>& cx, co
   tile_load<T, N, C>(cx, src, d);
   cplx<T> v[E];
 #pragma unroll
-  for (int r = 0; r < E; ++r) v[r] = cx.buf[pidx(cx.t + NT * r)];
+  for (int r = 0; r < E; ++r) v[r] = cx.buf[pidx(LaneIdx{cx.t, NT * r})];
   xsync<NT>();
-  fft<T, N, fft_E<N>(), -1>(v, cx.buf, cx.t, tw);
+  fft<T, N, fft_E<N>(), -1>(v, reinterpret_cast<T*>(cx.buf), cx.t, tw);
 }
 
 // the masked, 1/N^2-normalised right-hand-side value at k = t + NT r from the
@@ -1005,7 +1029,7 @@ template <typename T, int N, int C>
 __device__ __forceinline__ cplx<T> column_value(const ColCtx<T, N, C>& cx, int r) {
   constexpr int NT = N / fft_E<N>();
   const T inv = T(1.0 / (double(N) * double(N)));
-  const cplx<T> q = cx.buf[pidx(cx.t + NT * r)];
+  const cplx<T> q = cx.buf[pidx(LaneIdx{cx.t, NT * r})];
   return {q.x * inv, q.y * inv};
 }
 
@@ -1021,16 +1045,16 @@ __device__ __forceinline__ void column_forward_dx(const ColCtx<T, N, C>& cx, con
   tile_load<T, N, C>(cx, srcA, d);
   cplx<T> v[E];
 #pragma unroll
-  for (int r = 0; r < E; ++r) v[r] = cx.buf[pidx(cx.t + NT * r)];
+  for (int r = 0; r < E; ++r) v[r] = cx.buf[pidx(LaneIdx{cx.t, NT * r})];
   tile_load<T, N, C>(cx, srcB, d);  // its opening barrier: every wave has read A
   const T kxT = T(cx.kx);
 #pragma unroll
   for (int r = 0; r < E; ++r) {
-    const cplx<T> b = cx.buf[pidx(cx.t + NT * r)];
+    const cplx<T> b = cx.buf[pidx(LaneIdx{cx.t, NT * r})];
     v[r] = {v[r].x + kxT * b.y, v[r].y - kxT * b.x};
   }
   xsync<NT>();
-  fft<T, N, fft_E<N>(), -1>(v, cx.buf, cx.t, tw);
+  fft<T, N, fft_E<N>(), -1>(v, reinterpret_cast<T*>(cx.buf), cx.t, tw);
 #pragma unroll
   for (int r = 0; r < E; ++r) out[r] = column_value<T, N, C>(cx, r);
 }
@@ -1063,7 +1087,7 @@ __device__ __forceinline__ void column_inverse(const ColCtx<T, N, C>& cx, const 
   }
   // no barrier: since the last block-wide tile access (which ends with one)
   // only this wavefront has touched its buffer
-  fft<T, N, fft_E<N>(), +1>(v, cx.buf, cx.t, tw);
+  fft<T, N, fft_E<N>(), +1>(v, reinterpret_cast<T*>(cx.buf), cx.t, tw);
   tile_store<T, N, C>(cx, dst, d);
 }
 
@@ -1160,7 +1184,7 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
     if constexpr (std::is_same<TS, float>::value) YL = reinterpret_cast<cplx<TS>*>(P.Yl) + sr * sp;
     A = reinterpret_cast<cplx<TS>*>(P.Ar) + sr * sp;
   }
-  const size_t col = (size_t)cx.kx * d.NKY;
+  const unsigned col = (unsigned)cx.kx * (unsigned)d.NKY;
   const T fT = T(ph.f), gT = T(ph.g), HT = T(ph.H);
 
   cplx<TS> S[E];
@@ -1176,18 +1200,18 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
       else { ky = 0; in = false; }
       S[r] = {TS(0), TS(0)};
       if (!(in && cx.valid)) continue;
-      const size_t j = col + (size_t)(ky + K);
+      const unsigned j = col + (unsigned)(ky + K);
       if constexpr (DYN) {
         if (ph.kin) {
           // the next stage input is the prescribed flow at t_next
           const cplx<double> c = kin_coef<G>(cx.kx, ky, t_next, ph);
           S[r] = {TS(c.x), TS(c.y)};
-          Ys_out[(G - CG_U) * sp + j] = S[r];
+          put32(Ys_out + (G - CG_U) * sp, j, S[r]);
           continue;
         }
       }
-      S[r] = Y[j];
-      if constexpr (DYN) Ys_out[(G - CG_U) * sp + j] = S[r];
+      S[r] = at32(Y, j);
+      if constexpr (DYN) put32(Ys_out + (G - CG_U) * sp, j, S[r]);
     }
   } else {
     // RK4 stage.  The coefficients are taken in batches of RB: every load of a
@@ -1228,26 +1252,26 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
         ok[q] = in && cx.valid;
         kyv[q] = ky;
         if (!ok[q]) continue;
-        const size_t j = col + (size_t)(ky + K);
+        const unsigned j = col + (unsigned)(ky + K);
         if constexpr (DYN) {
-          su[q] = Ys_in[0 * sp + j];
-          sv[q] = Ys_in[1 * sp + j];
-          sh[q] = Ys_in[2 * sp + j];
+          su[q] = at32(Ys_in + 0 * sp, j);
+          sv[q] = at32(Ys_in + 1 * sp, j);
+          sh[q] = at32(Ys_in + 2 * sp, j);
         }
-        rk4_load<TS>(stage, Y + j, YL + j, A + j, y[q], lo[q], a[q]);
+        rk4_load<TS>(stage, Y, YL, A, j, y[q], lo[q], a[q]);
         if constexpr (EULA || EULB) {
           const bool acc = (r0i + q) % 2 == EPAR;
           if (eul && (SRCG || acc)) {
             if constexpr (EULA) {
-              sh[q] = Ys_in[2 * sp + j];
+              sh[q] = at32(Ys_in + 2 * sp, j);
             } else {
-              su[q] = Ys_in[0 * sp + j];
-              sv[q] = Ys_in[1 * sp + j];
+              su[q] = at32(Ys_in + 0 * sp, j);
+              sv[q] = at32(Ys_in + 1 * sp, j);
             }
           }
           if (eul && acc) {
             constexpr int se = EULA ? SF_EH : SF_EZ;
-            rk4_load<T>(stage, P.Yr + se * sp + j, P.Yl + se * sp + j, P.Ar + se * sp + j, ey[q], el[q], ea[q]);
+            rk4_load<T>(stage, P.Yr + se * sp, P.Yl + se * sp, P.Ar + se * sp, j, ey[q], el[q], ea[q]);
           }
         }
       }
@@ -1257,7 +1281,7 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
         S[r] = {TS(0), TS(0)};
         if (!ok[q]) continue;
         const int ky = kyv[q];
-        const size_t j = col + (size_t)(ky + K);
+        const unsigned j = col + (unsigned)(ky + K);
         const T kxT = T(cx.kx), kyT = T(ky);
         cplx<T> fsrc = {T(0), T(0)};  // f = eta or zeta from the stage spectra
         if constexpr (EULA || EULB) {
@@ -1274,7 +1298,7 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
           if (eul && acc) {
             constexpr int se = EULA ? SF_EH : SF_EZ;
             rk4v<T>(stage, ey[q], el[q], ea[q], fsrc, ph.dt);
-            rk4_store<T>(stage, P.Yr + se * sp + j, P.Yl + se * sp + j, P.Ar + se * sp + j, ey[q], el[q], ea[q]);
+            rk4_store<T>(stage, P.Yr + se * sp, P.Yl + se * sp, P.Ar + se * sp, j, ey[q], el[q], ea[q]);
           }
         }
         const double k2 = double(cx.kx) * cx.kx + double(ky) * ky;
@@ -1305,8 +1329,8 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
         }
         const cplx<TS> Rk = {TS(R.x), TS(R.y)};
         S[r] = rk4v<TS>(stage, y[q], lo[q], a[q], Rk, ph.dt);
-        rk4_store<TS>(stage, Y + j, YL + j, A + j, y[q], lo[q], a[q]);
-        if constexpr (DYN) Ys_out[(G - CG_U) * sp + j] = S[r];
+        rk4_store<TS>(stage, Y, YL, A, j, y[q], lo[q], a[q]);
+        if constexpr (DYN) put32(Ys_out + (G - CG_U) * sp, j, S[r]);
       }
     }
   }
@@ -1368,51 +1392,53 @@ __host__ __device__ constexpr int col_waves() {
 // slot0: the first group slot of this launch (grid = (column tiles, group slots))
 template <typename T, int N, int W>
 __global__ void __launch_bounds__((col_threads<N, W>()), (col_waves<T, N, false>()))
-    k_columns(StepPtrs<T> P, Dims d, Phys ph, int stage, double t_next, const cplx<T>* Ys_in, cplx<T>* Ys_out,
+    k_columns(StepPtrs<T> P, Phys ph, int stage, double t_next, const cplx<T>* Ys_in, cplx<T>* Ys_out,
               int remap, int slot0) {
   static_assert(col_threads<N, W>() % 64 == 0 && col_threads<N, W>() <= 1024, "column block");
   __shared__ cplx<T> lds[col_tile<N, W>() * col_buf(N)];
   int tile, slot, z;
   xcd_split(gridDim.x, gridDim.y, tile, slot, z, remap);
-  columns_body<T, N, col_tile<N, W>()>(P, d, ph, stage, t_next, Ys_in, Ys_out, tile, slot0 + slot, lds);
+  columns_body<T, N, col_tile<N, W>()>(P, dims_of<N>(), ph, stage, t_next, Ys_in, Ys_out, tile, slot0 + slot, lds);
 }
 
 // --------------------------------------------------------------------------
 // batched entry points: blockIdx.z selects a run of one (N, precision) group
 // --------------------------------------------------------------------------
 
-template <typename T, int N>
-__global__ void __launch_bounds__((DynGeo<T, N>::THREADS), (dyn_waves<T>())) k_rows_dyn_b(
-    const RunDesc<T>* __restrict__ runs, int remap) {
-  __shared__ cplx<T> lds[DynGeo<T, N>::LDS];
+// time since the interval start at a stage, from integers (as the single-run path)
+template <typename T>
+__device__ __forceinline__ double batch_s(const RunDesc<T>& R, int stage) {
+  const double c = (stage == 0) ? 0.0 : ((stage == 3) ? 1.0 : 0.5);
+  return (double(*R.counter) + c) * R.ph.dt;
+}
+
+template <typename T, int N, bool GEN>
+__global__ void __launch_bounds__((DynGeo<T, N>::THREADS), (DynGeo<T, N>::MIN_WAVES))
+    k_rows_dyn_b(const RunDesc<T>* __restrict__ runs, int stage, int remap) {
+  __shared__ __align__(16) T lds[DynGeo<T, N>::LDS];
   int rowblock, unused, z;
   xcd_split(gridDim.x, 1, rowblock, unused, z, remap);
-  if constexpr (DynGeo<T, N>::COOP) rows_dyn_coop<T, N>(runs[z].P, Dims::make(N), runs[z].ph, rowblock, lds);
-  else rows_dyn_body<T, N>(runs[z].P, Dims::make(N), runs[z].ph, rowblock, lds);
+  const RunDesc<T>& R = runs[z];
+  rows_dyn_body<T, N, GEN>(R.P, R.ph, batch_s(R, stage), rowblock, lds);
 }
 
 template <typename T, int N, bool CUB>
-__global__ void __launch_bounds__(64 * ROW_WAVES, (rhs_waves<T, N>())) k_rows_rhs_b(const RunDesc<T>* __restrict__ runs,
-                                                                                int stage, int remap) {
-  __shared__ cplx<T> lds[rhs_lds<T, N>()];  // transform buffers (and xi, two-task form)
-  int rowblock, task, z;
-  xcd_split(gridDim.x, gridDim.y, rowblock, task, z, remap);
+__global__ void __launch_bounds__((RhsGeo<T, N>::THREADS), (RhsGeo<T, N>::MIN_WAVES))
+    k_rows_rhs_b(const RunDesc<T>* __restrict__ runs, int stage, int remap) {
+  __shared__ __align__(16) T lds[RhsGeo<T, N>::LDS];
+  int rowblock, unused, z;
+  xcd_split(gridDim.x, 1, rowblock, unused, z, remap);
   const RunDesc<T>& R = runs[z];
-  // time since the interval start, from integers (as the single-run path)
-  const double c = (stage == 0) ? 0.0 : ((stage == 3) ? 1.0 : 0.5);
-  const double s = (double(*R.counter) + c) * R.ph.dt;
-  rows_rhs_body<T, N, CUB>(R.P, Dims::make(N), s, rowblock, task, lds, R.ph.gen);
+  rows_rhs_body<T, N, CUB>(R.P, batch_s(R, stage), rowblock, lds);
 }
 
 template <typename T, int N, bool CUB>
 __global__ void __launch_bounds__(64 * ROW_WAVES) k_rows_mom_b(const RunDesc<T>* __restrict__ runs, int stage, int remap) {
-  __shared__ cplx<T> lds[RowGeo<N>::RPB * RowGeo<N>::L];
+  __shared__ __align__(16) T lds[RowGeo<N>::RPB * 2 * RowGeo<N>::L];
   int rowblock, task, z;
   xcd_split(gridDim.x, gridDim.y, rowblock, task, z, remap);
   const RunDesc<T>& R = runs[z];
-  const double c = (stage == 0) ? 0.0 : ((stage == 3) ? 1.0 : 0.5);
-  const double s = (double(*R.counter) + c) * R.ph.dt;
-  rows_mom_body<T, N, CUB>(R.P, Dims::make(N), s, rowblock, task, lds);
+  rows_mom_body<T, N, CUB>(R.P, batch_s(R, stage), rowblock, task, lds);
 }
 
 // stage parity selects the stage-value buffers: between steps the current
@@ -1429,7 +1455,7 @@ __global__ void __launch_bounds__((col_threads<N, W>()), (col_waves<T, N, true>(
   // time of the next stage input, from integers (as the single-run path)
   const double cn = (stage <= 1) ? 0.5 : 1.0;
   const double t_next = (double(R.n_tau + *R.counter) + cn) * R.ph.dt;
-  columns_body<T, N, col_tile<N, W>()>(R.P, Dims::make(N), R.ph, stage, t_next, Ys_in, Ys_out, tile, group, lds);
+  columns_body<T, N, col_tile<N, W>()>(R.P, dims_of<N>(), R.ph, stage, t_next, Ys_in, Ys_out, tile, group, lds);
 }
 
 }  // namespace lm

@@ -1,0 +1,40 @@
+"""The cooperative rows passes at every grid size and precision: each size has its
+own share of rows per wave (1 to 8), of waves per block (six or four for the
+dynamics and strategy 1) and of LDS (whole or split exchanges), and each option
+its own kernels.  Two steps reach every stage, the t = tau limit included.
+
+Bars: those of the whole-run tests, 1e-12 in float64 and 1e-5 on the mixed path."""
+
+from __future__ import annotations
+
+import pytest
+
+from gpu_util import compare_value, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("prec,tol", [("fp64", 1e-12), ("fp32", 1e-5)])
+@pytest.mark.parametrize("N", [64, 128, 192, 256, 384, 512, 1024])
+@pytest.mark.parametrize("fields,interp", [(("h", "zeta"), "bilinear"), (("u", "q"), "cubic")])
+def test_two_steps_match_the_oracle(N, prec, tol, fields, interp):
+    from oracle.lagmean import Params, Run as OracleRun
+    from paper_2208_02682_amd import Run, make_config
+    from synth.workloads import scaled_run
+    say(f"rows passes N={N} {prec} {fields} {interp}")
+    w = scaled_run(N, Ro=0.1, ratio=1.0, periods=1.0, seeds=(70, 71), precision=prec)
+    u, v, h = w.initial_state()
+    o = OracleRun(Params(N=N, dt=w.dt, nu8=w.nu8, fields=fields, interp=interp), u, v, h)
+    o.begin_interval()
+    o.step(2)
+    ref = o.end_interval()
+    with Run(make_config(N, precision=prec, dt=w.dt, nu8=w.nu8, fields=fields, interp=interp)) as run:
+        run.set_state(u, v, h)
+        run.begin_interval()
+        run.step(2)
+        run.end_interval()
+        got = run.field_outputs()
+    assert set(got) == set(ref)
+    for k in ref:
+        err = compare_value(k, got[k], ref[k])
+        assert err < tol, (k, err)
