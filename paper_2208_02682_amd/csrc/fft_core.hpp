@@ -260,6 +260,13 @@ __host__ __device__ constexpr Radices plan_of(int n, int e) {
       case 512: return {8, 8, 1};
       default: break;
     }
+  } else if (e == 4) {
+    switch (n) {
+      case 64: return {4, 4, 1};
+      case 128: return {4, 4, 2};
+      case 256: return {4, 4, 4};
+      default: break;
+    }
   } else if (e == 12) {
     if (n == 192) return {4, 4, 1};
     if (n == 384) return {4, 4, 2};
@@ -312,40 +319,44 @@ template <typename T>
 using gptr = const __attribute__((address_space(1))) cplx<T>*;
 
 // Registers -> the group's buffer -> registers: value i of a lane goes to entry
-// wi(i), and entry ri(i) comes back.  SPLIT: real and imaginary parts one after
-// the other through a buffer of reals, half the LDS for twice the instructions
-// (the bytes are the same).
-template <typename T, int E, int NT, bool SPLIT, typename WI, typename RI>
-__device__ __forceinline__ void exchange(cplx<T> (&v)[E], T* buf, WI wi, RI ri) {
+// wi(i), and entry ri(i) comes back, for M transforms side by side (a buffer
+// each).  SPLIT: real and imaginary parts one after the other through a buffer of
+// reals, half the LDS for twice the instructions (the bytes are the same).
+template <typename T, int E, int NT, bool SPLIT, int M, typename WI, typename RI>
+__device__ __forceinline__ void exchange(cplx<T> (&v)[M][E], T* const (&buf)[M], WI wi, RI ri) {
   if constexpr (!SPLIT) {
-    cplx<T>* cb = reinterpret_cast<cplx<T>*>(buf);
 #pragma unroll
-    for (int i = 0; i < E; ++i) cb[pidx(wi(i))] = v[i];
+    for (int m = 0; m < M; ++m)
+#pragma unroll
+      for (int i = 0; i < E; ++i) reinterpret_cast<cplx<T>*>(buf[m])[pidx(wi(i))] = v[m][i];
     xsync<NT>();
 #pragma unroll
-    for (int i = 0; i < E; ++i) v[i] = cb[pidx(ri(i))];
+    for (int m = 0; m < M; ++m)
+#pragma unroll
+      for (int i = 0; i < E; ++i) v[m][i] = reinterpret_cast<const cplx<T>*>(buf[m])[pidx(ri(i))];
     xsync<NT>();
   } else {
+    static_assert(M == 1, "split exchanges are made one transform at a time");
 #pragma unroll
-    for (int i = 0; i < E; ++i) buf[pidx(wi(i))] = v[i].x;
+    for (int i = 0; i < E; ++i) buf[0][pidx(wi(i))] = v[0][i].x;
     xsync<NT>();
 #pragma unroll
-    for (int i = 0; i < E; ++i) v[i].x = buf[pidx(ri(i))];
+    for (int i = 0; i < E; ++i) v[0][i].x = buf[0][pidx(ri(i))];
     xsync<NT>();
 #pragma unroll
-    for (int i = 0; i < E; ++i) buf[pidx(wi(i))] = v[i].y;
+    for (int i = 0; i < E; ++i) buf[0][pidx(wi(i))] = v[0][i].y;
     xsync<NT>();
 #pragma unroll
-    for (int i = 0; i < E; ++i) v[i].y = buf[pidx(ri(i))];
+    for (int i = 0; i < E; ++i) v[0][i].y = buf[0][pidx(ri(i))];
     xsync<NT>();
   }
 }
 
 // one Stockham stage of radix R after sub-transforms of length Ns (Ns > 1) on
-// values in registers, v[b R + r] = entry t + NT b + r N / R; tw: the stage's
-// twiddle block
-template <typename T, int N, int E, int DIR, int Ns, int R>
-__device__ __forceinline__ void stockham_stage(cplx<T> (&v)[E], int t, gptr<T> tw) {
+// values in registers, v[b R + r] = entry t + NT b + r N / R, of M transforms
+// side by side; tw: the stage's twiddle block
+template <typename T, int N, int E, int DIR, int Ns, int R, int M>
+__device__ __forceinline__ void stockham_stage(cplx<T> (&v)[M][E], int t, gptr<T> tw) {
   constexpr int NT = N / E, NB = E / R;
   static_assert(E % R == 0, "radix must divide E");
 #pragma unroll
@@ -354,10 +365,12 @@ __device__ __forceinline__ void stockham_stage(cplx<T> (&v)[E], int t, gptr<T> t
 #pragma unroll
     for (int r = 1; r < R; ++r) {
       const cplx<T> w = {tw[(r - 1) * Ns + k].x, tw[(r - 1) * Ns + k].y};
-      v[b * R + r] = (DIR < 0) ? cmul(v[b * R + r], w) : cmulc(v[b * R + r], w);
+#pragma unroll
+      for (int m = 0; m < M; ++m) v[m][b * R + r] = (DIR < 0) ? cmul(v[m][b * R + r], w) : cmulc(v[m][b * R + r], w);
       if (R == 16 && r % 5 == 0) sched_fence();  // five twiddles in flight
     }
-    dft<R, DIR>(&v[b * R]);
+#pragma unroll
+    for (int m = 0; m < M; ++m) dft<R, DIR>(&v[m][b * R]);
   }
 }
 
@@ -412,24 +425,28 @@ __device__ __forceinline__ void lane_swap(V& a, V& b) {
 // transpose over q and s among the lanes c + 16 q, done with row swaps, after
 // which x[G a + k] holds element A k + a, which is exactly the last stage's
 // input b G + r for b = a, r = k.
-template <typename T, int N, int E, int DIR>
-__device__ __forceinline__ void stages_16_then_G(cplx<T> (&x)[E], int t, gptr<T> tw) {
+template <typename T, int N, int E, int DIR, int M>
+__device__ __forceinline__ void stages_16_then_G(cplx<T> (&v)[M][E], int t, gptr<T> tw) {
   constexpr int NT = N / E, G = N / 256, A = 16 / G;
   static_assert(E == 16 && (G == 2 || G == 4) && NT == 16 * G, "plan 16 x 16 x G");
-  stockham_stage<T, N, E, DIR, 16, 16>(x, t, tw);
+  stockham_stage<T, N, E, DIR, 16, 16, M>(v, t, tw);
   // G x G transpose across the lanes c + 16 q
 #pragma unroll
-  for (int a = 0; a < A; ++a) {
-    if constexpr (G == 4) {
-      lane_swap<32>(x[4 * a + 0], x[4 * a + 2]);
-      lane_swap<32>(x[4 * a + 1], x[4 * a + 3]);
-      lane_swap<16>(x[4 * a + 0], x[4 * a + 1]);
-      lane_swap<16>(x[4 * a + 2], x[4 * a + 3]);
-    } else {
-      lane_swap<16>(x[2 * a + 0], x[2 * a + 1]);
+  for (int m = 0; m < M; ++m) {
+    cplx<T>(&x)[E] = v[m];
+#pragma unroll
+    for (int a = 0; a < A; ++a) {
+      if constexpr (G == 4) {
+        lane_swap<32>(x[4 * a + 0], x[4 * a + 2]);
+        lane_swap<32>(x[4 * a + 1], x[4 * a + 3]);
+        lane_swap<16>(x[4 * a + 0], x[4 * a + 1]);
+        lane_swap<16>(x[4 * a + 2], x[4 * a + 3]);
+      } else {
+        lane_swap<16>(x[2 * a + 0], x[2 * a + 1]);
+      }
     }
   }
-  stockham_stage<T, N, E, DIR, 256, G>(x, t, tw + 15 * 16);
+  stockham_stage<T, N, E, DIR, 256, G, M>(v, t, tw + 15 * 16);
 }
 
 // Full transform of N points held by NT = N / E lanes.  v: lane t holds
@@ -439,8 +456,10 @@ __device__ __forceinline__ void stages_16_then_G(cplx<T> (&x)[E], int t, gptr<T>
 // lane) leaves entries t + NT (b + NB r), so the natural order needs no exchange.
 // Without KEEP it is put into buf (in natural order; not with SPLIT).
 // DIR = -1: forward (exp(-i...)), DIR = +1: inverse (unnormalised).
-template <typename T, int N, int E, int DIR, bool KEEP = false, bool SPLIT = false>
-__device__ __forceinline__ void fft(cplx<T> (&v)[E], T* buf, int t, const cplx<T>* __restrict__ tw) {
+// M transforms side by side (a buffer each) share the twiddles and the waits.
+template <typename T, int N, int E, int DIR, bool KEEP, bool SPLIT, int M>
+__device__ __forceinline__ void fft_side_by_side(cplx<T> (&v)[M][E], T* const (&buf)[M], int t,
+                                                 const cplx<T>* __restrict__ tw) {
   using PL = Plan<N, E>;
   constexpr int NT = N / E, R2 = PL::R2, R3 = PL::R3, R4 = PL::R4;
   static_assert(R2 > 1, "a transform of one stage");
@@ -449,38 +468,48 @@ __device__ __forceinline__ void fft(cplx<T> (&v)[E], T* buf, int t, const cplx<T
   // from keeping twiddles of one transform live until the next one
   asm volatile("" : "+s"(tw));
   const gptr<T> ptw = (gptr<T>)tw;
-  dft<E, DIR>(v);
-  exchange<T, E, NT, SPLIT>(v, buf, [&](int i) { return LaneIdx{t * E + i, 0}; },
-                            [&](int i) { return stage_in<N, E, R2>(i, t); });
+#pragma unroll
+  for (int m = 0; m < M; ++m) dft<E, DIR>(v[m]);
+  exchange<T, E, NT, SPLIT, M>(v, buf, [&](int i) { return LaneIdx{t * E + i, 0}; },
+                               [&](int i) { return stage_in<N, E, R2>(i, t); });
   if constexpr (E == 16 && R2 == 16 && (R3 == 2 || R3 == 4) && R4 == 1) {
-    stages_16_then_G<T, N, E, DIR>(v, t, ptw);
+    stages_16_then_G<T, N, E, DIR, M>(v, t, ptw);
   } else {
-    stockham_stage<T, N, E, DIR, E, R2>(v, t, ptw + tw_offset(N, E, 0));
+    stockham_stage<T, N, E, DIR, E, R2, M>(v, t, ptw + tw_offset(N, E, 0));
     if constexpr (R3 > 1) {
-      exchange<T, E, NT, SPLIT>(v, buf, [&](int i) { return stage_out<N, E, E, R2>(i, t); },
-                                [&](int i) { return stage_in<N, E, R3>(i, t); });
-      stockham_stage<T, N, E, DIR, E * R2, R3>(v, t, ptw + tw_offset(N, E, 1));
+      exchange<T, E, NT, SPLIT, M>(v, buf, [&](int i) { return stage_out<N, E, E, R2>(i, t); },
+                                   [&](int i) { return stage_in<N, E, R3>(i, t); });
+      stockham_stage<T, N, E, DIR, E * R2, R3, M>(v, t, ptw + tw_offset(N, E, 1));
     }
     if constexpr (R4 > 1) {
-      exchange<T, E, NT, SPLIT>(v, buf, [&](int i) { return stage_out<N, E, E * R2, R3>(i, t); },
-                                [&](int i) { return stage_in<N, E, R4>(i, t); });
-      stockham_stage<T, N, E, DIR, E * R2 * R3, R4>(v, t, ptw + tw_offset(N, E, 2));
+      exchange<T, E, NT, SPLIT, M>(v, buf, [&](int i) { return stage_out<N, E, E * R2, R3>(i, t); },
+                                   [&](int i) { return stage_in<N, E, R4>(i, t); });
+      stockham_stage<T, N, E, DIR, E * R2 * R3, R4, M>(v, t, ptw + tw_offset(N, E, 2));
     }
   }
   constexpr int NB = E / RL;
-  if constexpr (KEEP) {
-    cplx<T> o[E];
 #pragma unroll
-    for (int i = 0; i < E; ++i) o[i / RL + NB * (i % RL)] = v[i];
+  for (int m = 0; m < M; ++m) {
+    if constexpr (KEEP) {
+      cplx<T> o[E];
 #pragma unroll
-    for (int i = 0; i < E; ++i) v[i] = o[i];
-  } else {
-    static_assert(!SPLIT, "a split buffer holds no whole spectrum");
-    cplx<T>* cb = reinterpret_cast<cplx<T>*>(buf);
+      for (int i = 0; i < E; ++i) o[i / RL + NB * (i % RL)] = v[m][i];
 #pragma unroll
-    for (int i = 0; i < E; ++i) cb[pidx(LaneIdx{t, NT * (i / RL + NB * (i % RL))})] = v[i];
-    xsync<NT>();
+      for (int i = 0; i < E; ++i) v[m][i] = o[i];
+    } else {
+      static_assert(!SPLIT, "a split buffer holds no whole spectrum");
+      cplx<T>* cb = reinterpret_cast<cplx<T>*>(buf[m]);
+#pragma unroll
+      for (int i = 0; i < E; ++i) cb[pidx(LaneIdx{t, NT * (i / RL + NB * (i % RL))})] = v[m][i];
+    }
   }
+  if constexpr (!KEEP) xsync<NT>();
+}
+
+template <typename T, int N, int E, int DIR, bool KEEP = false, bool SPLIT = false>
+__device__ __forceinline__ void fft(cplx<T> (&v)[E], T* buf, int t, const cplx<T>* __restrict__ tw) {
+  T* const b[1] = {buf};
+  fft_side_by_side<T, N, E, DIR, KEEP, SPLIT, 1>(reinterpret_cast<cplx<T>(&)[1][E]>(v), b, t, tw);
 }
 
 }  // namespace lm

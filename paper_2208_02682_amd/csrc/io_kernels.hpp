@@ -126,7 +126,7 @@ __global__ void __launch_bounds__(col_threads<N>())
       S[r] = reinterpret_cast<const cplx<double>*>(J.src[q])[j];
     }
   }
-  column_inverse<double, N, C, double, false>(cx, S, J.dst[q], d, tw);
+  column_inverse<double, N, C, double, false>(cx, S, J.dst[q], nullptr, d, tw);
 }
 
 }  // namespace lm

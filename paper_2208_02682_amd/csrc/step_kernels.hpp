@@ -953,6 +953,30 @@ struct ColCtx {
   cplx<T>* buf;     // this group's buffer
   int c, t, kx0, kx;
   bool valid;       // kx <= K
+  unsigned ky0;     // index of ky = 0 in the column's state (columns past K: of column K)
+};
+
+// Coefficient ky that entry k = t + NT r of a column transform stands for:
+// k <= K: ky = k, k >= N - K: ky = k - N, none in between.  Most r are the same
+// for every lane; their place in the state is then the lane's offset plus a
+// constant.  Lanes without a coefficient read a valid place (ky = 0) and are
+// dropped at the store.
+template <int N>
+struct ColIdx {
+  static constexpr int E = fft_E<N>(), NT = N / E, K = kcut<N>();
+  int t, r;
+  __device__ __forceinline__ bool all_lo() const { return NT * r + NT - 1 <= K; }
+  __device__ __forceinline__ bool all_hi() const { return NT * r >= N - K; }
+  __device__ __forceinline__ bool none() const { return NT * r > K && NT * r + NT - 1 < N - K; }
+  __device__ __forceinline__ bool in() const { return all_lo() || all_hi() || t + NT * r <= K || t + NT * r >= N - K; }
+  // ky = lane() + off()
+  __device__ __forceinline__ int lane() const {
+    if (all_lo() || all_hi()) return t;
+    const int k = t + NT * r;
+    return k <= K ? k : (k >= N - K ? k - N : 0);
+  }
+  __device__ __forceinline__ int off() const { return all_lo() ? NT * r : (all_hi() ? NT * r - N : 0); }
+  __device__ __forceinline__ int ky() const { return lane() + off(); }
 };
 
 // one complex value of a buffer-resource load (8 or 16 bytes)
@@ -989,24 +1013,23 @@ __device__ __forceinline__ void tile_load(const ColCtx<T, N, C>& cx, const cplx<
   __syncthreads();
 }
 
-// block-wide: the C buffers to rows of a [N][NKXP] field (columns kx0..).  The
-// block is C * N / E threads, a compile-time count, so the loop unrolls and all
-// of a thread's LDS reads are issued before its stores.
+// block-wide: the C buffers at lds to rows of a [N][NKXP] field (columns kx0..),
+// between barriers of the caller.  The block is C * N / E threads, a compile-time
+// count, so the loop unrolls and all of a thread's LDS reads are issued before
+// its stores.
 template <typename T, int N, int C>
-__device__ __forceinline__ void tile_store(const ColCtx<T, N, C>& cx, cplx<T>* __restrict__ dst,
+__device__ __forceinline__ void tile_store(const ColCtx<T, N, C>& cx, const cplx<T>* lds, cplx<T>* __restrict__ dst,
                                            const Dims& d) {
   constexpr int LC = ColCtx<T, N, C>::LC;
   constexpr int NTH = C * (N / fft_E<N>());
   static_assert((N * C) % NTH == 0 && NTH % C == 0, "tile store rounds");
-  __syncthreads();
   const int c = (int)threadIdx.x % C, y0 = (int)threadIdx.x / C;
   const unsigned at = (unsigned)(y0 * d.NKXP + cx.kx0 + c);
   if (cx.kx0 + c <= kcut<N>()) {
 #pragma unroll
     for (int k = 0; k < N * C / NTH; ++k)
-      put32(dst + (size_t)(NTH / C) * k * d.NKXP, at, cx.lds[c * LC + pidx(LaneIdx{y0, (NTH / C) * k})]);
+      put32(dst + (size_t)(NTH / C) * k * d.NKXP, at, lds[c * LC + pidx(LaneIdx{y0, (NTH / C) * k})]);
   }
-  __syncthreads();
 }
 
 // forward column transform of one row-spectrum field; the spectrum is left in
@@ -1033,6 +1056,24 @@ __device__ __forceinline__ cplx<T> column_value(const ColCtx<T, N, C>& cx, int r
   return {q.x * inv, q.y * inv};
 }
 
+// forward transform of v, masked, 1/N^2-normalised values at k = t + NT r in v.
+// With 16 values per lane they come back through the buffer: kept in registers
+// across the last stage, the float kernels spill under their 128 registers.
+template <typename T, int N, int C>
+__device__ __forceinline__ void column_fft_out(const ColCtx<T, N, C>& cx, cplx<T> (&v)[fft_E<N>()],
+                                               const cplx<T>* __restrict__ tw) {
+  constexpr int E = fft_E<N>();
+  fft<T, N, E, -1, (E < 16)>(v, reinterpret_cast<T*>(cx.buf), cx.t, tw);
+  if constexpr (E < 16) {
+    const T inv = T(1.0 / (double(N) * double(N)));
+#pragma unroll
+    for (int r = 0; r < E; ++r) v[r] = {v[r].x * inv, v[r].y * inv};
+  } else {
+#pragma unroll
+    for (int r = 0; r < E; ++r) v[r] = column_value<T, N, C>(cx, r);
+  }
+}
+
 // forward column transform of A - i kx B for two row-spectrum fields: a
 // column's kx is fixed, so the x-derivative of B joins A before one transform
 // (the transform is linear).  Returns the masked, 1/N^2-normalised values at
@@ -1054,9 +1095,9 @@ __device__ __forceinline__ void column_forward_dx(const ColCtx<T, N, C>& cx, con
     v[r] = {v[r].x + kxT * b.y, v[r].y - kxT * b.x};
   }
   xsync<NT>();
-  fft<T, N, fft_E<N>(), -1>(v, reinterpret_cast<T*>(cx.buf), cx.t, tw);
+  column_fft_out<T, N, C>(cx, v, tw);
 #pragma unroll
-  for (int r = 0; r < E; ++r) out[r] = column_value<T, N, C>(cx, r);
+  for (int r = 0; r < E; ++r) out[r] = v[r];
 }
 
 // forward column transform of one row-spectrum field; returns the masked,
@@ -1064,31 +1105,64 @@ __device__ __forceinline__ void column_forward_dx(const ColCtx<T, N, C>& cx, con
 template <typename T, int N, int C>
 __device__ __forceinline__ void column_forward(const ColCtx<T, N, C>& cx, const cplx<T>* src, const Dims& d,
                                                const cplx<T>* __restrict__ tw, cplx<T> (&out)[fft_E<N>()]) {
-  constexpr int E = fft_E<N>();
-  column_forward_lds<T, N, C>(cx, src, d, tw);
+  constexpr int E = fft_E<N>(), NT = N / E;
+  tile_load<T, N, C>(cx, src, d);
 #pragma unroll
-  for (int r = 0; r < E; ++r) out[r] = column_value<T, N, C>(cx, r);
+  for (int r = 0; r < E; ++r) out[r] = cx.buf[pidx(LaneIdx{cx.t, NT * r})];
+  xsync<NT>();
+  column_fft_out<T, N, C>(cx, out, tw);
 }
 
-// inverse column transform of values S at k = t + NT r (already zero outside
-// the mask), optionally times i ky, stored to an intermediate field
-template <typename T, int N, int C, typename TS, bool DY>
+// whether a block's two inverse transforms (a field and its i ky version) run side
+// by side in two sets of buffers: on the grids whose columns are bound by latency,
+// where a second set leaves room for two blocks per CU
+template <typename T, int N, int C>
+__host__ __device__ constexpr bool col_dual() {
+  return fft_E<N>() <= 12 && 2 * C * col_buf(N) * sizeof(cplx<T>) <= 80 * 1024;
+}
+
+// inverse column transforms of values S at k = t + NT r (already zero outside
+// the mask) to the intermediate field dst and, with WITH_DY, of i ky S to dst_dy
+template <typename T, int N, int C, typename TS, bool WITH_DY>
 __device__ __forceinline__ void column_inverse(const ColCtx<T, N, C>& cx, const cplx<TS> (&S)[fft_E<N>()],
-                                               cplx<T>* dst, const Dims& d, const cplx<T>* __restrict__ tw) {
+                                               cplx<T>* dst, cplx<T>* dst_dy, const Dims& d,
+                                               const cplx<T>* __restrict__ tw) {
   constexpr int E = fft_E<N>(), NT = N / E;
-  cplx<T> v[E];
-#pragma unroll
-  for (int r = 0; r < E; ++r) {
+  auto value = [&](int r, bool dy) -> cplx<T> {
+    const cplx<T> q = {T(S[r].x), T(S[r].y)};
+    if (!dy) return q;
     const int k = cx.t + NT * r;
     const int ky = (k <= N / 2) ? k : k - N;
-    cplx<T> q = {T(S[r].x), T(S[r].y)};
-    if (DY) q = {-T(ky) * q.y, T(ky) * q.x};
-    v[r] = q;
-  }
+    return {-T(ky) * q.y, T(ky) * q.x};
+  };
   // no barrier: since the last block-wide tile access (which ends with one)
   // only this wavefront has touched its buffer
-  fft<T, N, fft_E<N>(), +1>(v, reinterpret_cast<T*>(cx.buf), cx.t, tw);
-  tile_store<T, N, C>(cx, dst, d);
+  if constexpr (WITH_DY && col_dual<T, N, C>()) {
+    cplx<T> v[2][E];
+#pragma unroll
+    for (int r = 0; r < E; ++r) v[0][r] = value(r, false), v[1][r] = value(r, true);
+    constexpr int SECOND = C * ColCtx<T, N, C>::LC;
+    T* const b[2] = {reinterpret_cast<T*>(cx.buf), reinterpret_cast<T*>(cx.buf + SECOND)};
+    fft_side_by_side<T, N, E, +1, false, false, 2>(v, b, cx.t, tw);
+    __syncthreads();
+    tile_store<T, N, C>(cx, cx.lds, dst, d);
+    tile_store<T, N, C>(cx, cx.lds + SECOND, dst_dy, d);
+  } else {
+    cplx<T> v[E];
+#pragma unroll
+    for (int r = 0; r < E; ++r) v[r] = value(r, false);
+    fft<T, N, E, +1>(v, reinterpret_cast<T*>(cx.buf), cx.t, tw);
+    __syncthreads();
+    tile_store<T, N, C>(cx, cx.lds, dst, d);
+    if constexpr (WITH_DY) {
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < E; ++r) v[r] = value(r, true);
+      fft<T, N, E, +1>(v, reinterpret_cast<T*>(cx.buf), cx.t, tw);
+      __syncthreads();
+      tile_store<T, N, C>(cx, cx.lds, dst_dy, d);
+    }
+  }
 }
 
 // Fourier coefficient (the stored kx >= 0 half, 1/N^2-normalised) of u, v or h
@@ -1141,7 +1215,6 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
   using TS = typename std::conditional<DBL, double, T>::type;
   const size_t sp = d.spec_elems();
   const size_t rf = d.rowfield_elems();
-  constexpr int K = kcut<N>();
   if constexpr (EUL) {
     if (stage < 0) return;  // not an input of the rows passes
   }
@@ -1154,19 +1227,6 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
                    : (G == CG_PX) ? RS_PX : (G == CG_PY) ? RS_PY : (G == CG_GMX) ? RS_GMX
                    : (G == CG_GMY) ? RS_GMY : (G == CG_EF0) ? RS_F0 : RS_F1;
   constexpr int F1 = (G == CG_U || G == CG_V) ? RS_K : RS_HV;
-  // the first input's values in registers; the second one's (dynamics groups)
-  // stay in the wave's buffer until the stage update reads them
-  cplx<T> r0[E];
-  // a kinematic run has no dynamics right-hand sides
-  if (stage >= 0 && !(DYN && ph.kin)) {
-    if constexpr (G == CG_U) {
-      // zeta v - i kx K in one transform
-      column_forward_dx<T, N, C>(cx, P.RS + F0 * rf, P.RS + F1 * rf, d, P.tw, r0);
-    } else {
-      column_forward<T, N, C>(cx, P.RS + F0 * rf, d, P.tw, r0);
-      if constexpr (NF == 2) column_forward_lds<T, N, C>(cx, P.RS + F1 * rf, d, P.tw);
-    }
-  }
 
   // state of this group
   cplx<TS>* Y;
@@ -1184,41 +1244,38 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
     if constexpr (std::is_same<TS, float>::value) YL = reinterpret_cast<cplx<TS>*>(P.Yl) + sr * sp;
     A = reinterpret_cast<cplx<TS>*>(P.Ar) + sr * sp;
   }
-  const unsigned col = (unsigned)cx.kx * (unsigned)d.NKY;
   const T fT = T(ph.f), gT = T(ph.g), HT = T(ph.H);
 
   cplx<TS> S[E];
   if (stage < 0 || (DYN && ph.kin)) {
-    // prologue (the current state's transforms) or a prescribed flow
+    // prologue (the current state's transforms) or a prescribed flow (a kinematic
+    // run has no dynamics right-hand sides)
 #pragma unroll
     for (int r = 0; r < E; ++r) {
-      const int k = cx.t + NT * r;
-      int ky;
-      bool in = true;
-      if (k <= K) ky = k;
-      else if (k >= N - K) ky = k - N;
-      else { ky = 0; in = false; }
+      const ColIdx<N> ix{cx.t, r};
       S[r] = {TS(0), TS(0)};
-      if (!(in && cx.valid)) continue;
-      const unsigned j = col + (unsigned)(ky + K);
+      if (ix.none() || !(ix.in() && cx.valid)) continue;
+      const unsigned j = cx.ky0 + ix.lane();
       if constexpr (DYN) {
         if (ph.kin) {
           // the next stage input is the prescribed flow at t_next
-          const cplx<double> c = kin_coef<G>(cx.kx, ky, t_next, ph);
+          const cplx<double> c = kin_coef<G>(cx.kx, ix.ky(), t_next, ph);
           S[r] = {TS(c.x), TS(c.y)};
-          put32(Ys_out + (G - CG_U) * sp, j, S[r]);
+          put32(Ys_out + (G - CG_U) * sp + ix.off(), j, S[r]);
           continue;
         }
       }
-      S[r] = at32(Y, j);
-      if constexpr (DYN) put32(Ys_out + (G - CG_U) * sp, j, S[r]);
+      S[r] = at32(Y + ix.off(), j);
+      if constexpr (DYN) put32(Ys_out + (G - CG_U) * sp + ix.off(), j, S[r]);
     }
   } else {
     // RK4 stage.  The coefficients are taken in batches of RB: every load of a
     // batch (stage values, state, accumulator) is issued before its first
     // store, so the batch's loads are in flight together (stores to the state
     // could alias later loads as far as the compiler knows, which would
-    // otherwise serialise the coefficients).
+    // otherwise serialise the coefficients).  On the smaller grids one batch takes
+    // all of a lane's coefficients, and its loads are issued before the forward
+    // transforms (PRE): they wait for memory once, not twice.
     // For the default averaged fields (eta, zeta) the g-tilde groups take their
     // source f from the stage spectra, f = eta (h less H at k = 0) for g-tilde_h
     // and f = i kx v - i ky u for g-tilde_zeta (eq. (4.1): the rows pass formed
@@ -1231,57 +1288,68 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
     constexpr bool SRCG = (G == CG_GTH || G == CG_GTZ);
     constexpr int EPAR = SRCG ? 0 : 1;
     const bool eul = (EULA || EULB) && !ph.gen;
+    constexpr bool PRE = E <= 8;
     constexpr int RB0 = (DBL || DYN || EULA || EULB) ? 4 : 8;
-    constexpr int RB = (E % RB0 == 0) ? RB0 : 4;
+    constexpr int RB = PRE ? E : ((E % RB0 == 0) ? RB0 : 4);
     static_assert(E % RB == 0, "coefficient batches");
-#pragma unroll
-    for (int r0i = 0; r0i < E; r0i += RB) {
-      bool ok[RB];
-      int kyv[RB];
-      cplx<T> su[RB], sv[RB], sh[RB];
-      cplx<TS> y[RB], lo[RB], a[RB];
-      cplx<T> ey[RB], el[RB], ea[RB];  // Eulerian accumulator
+    cplx<T> su[RB], sv[RB], sh[RB];
+    cplx<TS> y[RB], lo[RB], a[RB];
+    cplx<T> ey[RB], el[RB], ea[RB];  // Eulerian accumulator
+    auto load = [&](int r0i) {
 #pragma unroll
       for (int q = 0; q < RB; ++q) {
-        const int k = cx.t + NT * (r0i + q);
-        int ky;
-        bool in = true;
-        if (k <= K) ky = k;
-        else if (k >= N - K) ky = k - N;
-        else { ky = 0; in = false; }
-        ok[q] = in && cx.valid;
-        kyv[q] = ky;
-        if (!ok[q]) continue;
-        const unsigned j = col + (unsigned)(ky + K);
+        const ColIdx<N> ix{cx.t, r0i + q};
+        if (ix.none()) continue;
+        const unsigned j = cx.ky0 + ix.lane();
+        const int o = ix.off();
         if constexpr (DYN) {
-          su[q] = at32(Ys_in + 0 * sp, j);
-          sv[q] = at32(Ys_in + 1 * sp, j);
-          sh[q] = at32(Ys_in + 2 * sp, j);
+          su[q] = at32(Ys_in + 0 * sp + o, j);
+          sv[q] = at32(Ys_in + 1 * sp + o, j);
+          sh[q] = at32(Ys_in + 2 * sp + o, j);
         }
-        rk4_load<TS>(stage, Y, YL, A, j, y[q], lo[q], a[q]);
+        rk4_load<TS>(stage, Y + o, YL + o, A + o, j, y[q], lo[q], a[q]);
         if constexpr (EULA || EULB) {
           const bool acc = (r0i + q) % 2 == EPAR;
           if (eul && (SRCG || acc)) {
             if constexpr (EULA) {
-              sh[q] = at32(Ys_in + 2 * sp, j);
+              sh[q] = at32(Ys_in + 2 * sp + o, j);
             } else {
-              su[q] = at32(Ys_in + 0 * sp, j);
-              sv[q] = at32(Ys_in + 1 * sp, j);
+              su[q] = at32(Ys_in + 0 * sp + o, j);
+              sv[q] = at32(Ys_in + 1 * sp + o, j);
             }
           }
           if (eul && acc) {
             constexpr int se = EULA ? SF_EH : SF_EZ;
-            rk4_load<T>(stage, P.Yr + se * sp, P.Yl + se * sp, P.Ar + se * sp, j, ey[q], el[q], ea[q]);
+            rk4_load<T>(stage, P.Yr + se * sp + o, P.Yl + se * sp + o, P.Ar + se * sp + o, j, ey[q], el[q], ea[q]);
           }
         }
       }
+    };
+    if constexpr (PRE) {
+      load(0);
+      sched_fence();
+    }
+    // the first input's values in registers; the second one's (dynamics groups)
+    // stay in the wave's buffer until the stage update reads them
+    cplx<T> r0[E];
+    if constexpr (G == CG_U) {
+      // zeta v - i kx K in one transform
+      column_forward_dx<T, N, C>(cx, P.RS + F0 * rf, P.RS + F1 * rf, d, P.tw, r0);
+    } else {
+      column_forward<T, N, C>(cx, P.RS + F0 * rf, d, P.tw, r0);
+      if constexpr (NF == 2) column_forward_lds<T, N, C>(cx, P.RS + F1 * rf, d, P.tw);
+    }
+#pragma unroll
+    for (int r0i = 0; r0i < E; r0i += RB) {
+      if constexpr (!PRE) load(r0i);
 #pragma unroll
       for (int q = 0; q < RB; ++q) {
         const int r = r0i + q;
+        const ColIdx<N> ix{cx.t, r};
         S[r] = {TS(0), TS(0)};
-        if (!ok[q]) continue;
-        const int ky = kyv[q];
-        const unsigned j = col + (unsigned)(ky + K);
+        if (ix.none() || !(ix.in() && cx.valid)) continue;
+        const int ky = ix.ky(), o = ix.off();
+        const unsigned j = cx.ky0 + ix.lane();
         const T kxT = T(cx.kx), kyT = T(ky);
         cplx<T> fsrc = {T(0), T(0)};  // f = eta or zeta from the stage spectra
         if constexpr (EULA || EULB) {
@@ -1298,7 +1366,7 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
           if (eul && acc) {
             constexpr int se = EULA ? SF_EH : SF_EZ;
             rk4v<T>(stage, ey[q], el[q], ea[q], fsrc, ph.dt);
-            rk4_store<T>(stage, P.Yr + se * sp, P.Yl + se * sp, P.Ar + se * sp, j, ey[q], el[q], ea[q]);
+            rk4_store<T>(stage, P.Yr + se * sp + o, P.Yl + se * sp + o, P.Ar + se * sp + o, j, ey[q], el[q], ea[q]);
           }
         }
         const double k2 = double(cx.kx) * cx.kx + double(ky) * ky;
@@ -1329,28 +1397,26 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
         }
         const cplx<TS> Rk = {TS(R.x), TS(R.y)};
         S[r] = rk4v<TS>(stage, y[q], lo[q], a[q], Rk, ph.dt);
-        rk4_store<TS>(stage, Y, YL, A, j, y[q], lo[q], a[q]);
-        if constexpr (DYN) put32(Ys_out + (G - CG_U) * sp, j, S[r]);
+        rk4_store<TS>(stage, Y + o, YL + o, A + o, j, y[q], lo[q], a[q]);
+        if constexpr (DYN) put32(Ys_out + (G - CG_U) * sp + o, j, S[r]);
       }
     }
   }
 
   // inverse column transforms of the next stage input
   if constexpr (G == CG_U) {
-    column_inverse<T, N, C, TS, false>(cx, S, P.IC + IC_U * rf, d, P.tw);
-    column_inverse<T, N, C, TS, true>(cx, S, P.IC + IC_UY * rf, d, P.tw);
+    column_inverse<T, N, C, TS, true>(cx, S, P.IC + IC_U * rf, P.IC + IC_UY * rf, d, P.tw);
   } else if constexpr (G == CG_V) {
-    column_inverse<T, N, C, TS, false>(cx, S, P.IC + IC_V * rf, d, P.tw);
+    column_inverse<T, N, C, TS, false>(cx, S, P.IC + IC_V * rf, nullptr, d, P.tw);
   } else if constexpr (G == CG_H) {
     // the rows passes work with eta = h - H: drop H from the mean (k = 0, lane 0)
     if (cx.kx == 0 && cx.t == 0) S[0].x -= TS(ph.H);
-    column_inverse<T, N, C, TS, false>(cx, S, P.IC + IC_H * rf, d, P.tw);
+    column_inverse<T, N, C, TS, false>(cx, S, P.IC + IC_H * rf, nullptr, d, P.tw);
   } else if constexpr (!EUL) {
     constexpr int o = (G == CG_XIX) ? IC_XIX : (G == CG_XIY) ? IC_XIY : (G == CG_GBH) ? IC_GBH
                     : (G == CG_GBZ) ? IC_GBZ : (G == CG_GTH) ? IC_GTH : (G == CG_GTZ) ? IC_GTZ
                     : (G == CG_PX) ? IC_PX : (G == CG_PY) ? IC_PY : (G == CG_GMX) ? IC_GMX : IC_GMY;
-    column_inverse<T, N, C, TS, false>(cx, S, P.IC + o * rf, d, P.tw);
-    column_inverse<T, N, C, TS, true>(cx, S, P.IC + (o + 1) * rf, d, P.tw);
+    column_inverse<T, N, C, TS, true>(cx, S, P.IC + o * rf, P.IC + (o + 1) * rf, d, P.tw);
   }
 }
 
@@ -1359,7 +1425,7 @@ template <typename T, int N, int C>
 __device__ __forceinline__ void columns_body(const StepPtrs<T>& P, const Dims& d, const Phys& ph, int stage,
                                              double t_next, const cplx<T>* Ys_in, cplx<T>* Ys_out, int tile,
                                              int slot, cplx<T>* lds) {
-  constexpr int E = fft_E<N>(), NT = N / E, LC = col_buf(N);
+  constexpr int NT = N / fft_E<N>(), LC = col_buf(N);
   ColCtx<T, N, C> cx;
   cx.lds = lds;
   cx.c = threadIdx.x / NT;
@@ -1368,7 +1434,7 @@ __device__ __forceinline__ void columns_body(const StepPtrs<T>& P, const Dims& d
   cx.kx0 = tile * C;
   cx.kx = cx.kx0 + cx.c;
   cx.valid = cx.kx <= kcut<N>();
-  (void)E;
+  cx.ky0 = (unsigned)(min(cx.kx, kcut<N>()) * d.NKY + d.K);
 #define LM_CG(g) \
   case g: column_group<T, N, C, g>(cx, P, d, ph, stage, t_next, Ys_in, Ys_out); break
   switch (col_group_of(ph, slot)) {
@@ -1380,22 +1446,30 @@ __device__ __forceinline__ void columns_body(const StepPtrs<T>& P, const Dims& d
 #undef LM_CG
 }
 
-// float32: ask for 4 resident waves per SIMD (at most 128 registers), which
-// every size reaches without spilling more than a few words; float64 is out of
-// its reach
-template <typename T, int N, bool BATCHED>
+// resident waves per SIMD asked for.  16 (or 12) values per lane in float32: 4 (at
+// most 128 registers).  8 values per lane: the whole column's state is in
+// registers during the transforms, and the grids are too small to fill the chip:
+// 2.  float64: 1.
+template <typename T, int N>
 __host__ __device__ constexpr int col_waves() {
-  return sizeof(T) == 4 ? 4 : 1;
+  return sizeof(T) == 4 ? (fft_E<N>() <= 8 ? 2 : 4) : 1;
+}
+
+// buffers of a column block: one set, or two for side-by-side inverse transforms
+template <typename T, int N, int W>
+__host__ __device__ constexpr int col_lds() {
+  constexpr int C = col_tile<N, W>();
+  return (col_dual<T, N, C>() ? 2 : 1) * C * col_buf(N);
 }
 
 // W: column tile width (col_tile<N, W>)
 // slot0: the first group slot of this launch (grid = (column tiles, group slots))
 template <typename T, int N, int W>
-__global__ void __launch_bounds__((col_threads<N, W>()), (col_waves<T, N, false>()))
+__global__ void __launch_bounds__((col_threads<N, W>()), (col_waves<T, N>()))
     k_columns(StepPtrs<T> P, Phys ph, int stage, double t_next, const cplx<T>* Ys_in, cplx<T>* Ys_out,
               int remap, int slot0) {
   static_assert(col_threads<N, W>() % 64 == 0 && col_threads<N, W>() <= 1024, "column block");
-  __shared__ cplx<T> lds[col_tile<N, W>() * col_buf(N)];
+  __shared__ cplx<T> lds[col_lds<T, N, W>()];
   int tile, slot, z;
   xcd_split(gridDim.x, gridDim.y, tile, slot, z, remap);
   columns_body<T, N, col_tile<N, W>()>(P, dims_of<N>(), ph, stage, t_next, Ys_in, Ys_out, tile, slot0 + slot, lds);
@@ -1444,9 +1518,9 @@ __global__ void __launch_bounds__(64 * ROW_WAVES) k_rows_mom_b(const RunDesc<T>*
 // stage parity selects the stage-value buffers: between steps the current
 // stage input is always Ys0 (four swaps per step)
 template <typename T, int N, int W>
-__global__ void __launch_bounds__((col_threads<N, W>()), (col_waves<T, N, true>()))
+__global__ void __launch_bounds__((col_threads<N, W>()), (col_waves<T, N>()))
     k_columns_b(const RunDesc<T>* __restrict__ runs, int stage, int remap) {
-  __shared__ cplx<T> lds[col_tile<N, W>() * col_buf(N)];
+  __shared__ cplx<T> lds[col_lds<T, N, W>()];
   int tile, group, z;
   xcd_split(gridDim.x, gridDim.y, tile, group, z, remap);
   const RunDesc<T>& R = runs[z];
