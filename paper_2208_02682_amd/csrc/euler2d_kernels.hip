@@ -39,16 +39,23 @@ __device__ double bilinear_at(const double* __restrict__ F, int N, int jx, int j
          (1.0 - ax) * ay * F[iy1 * N + ix0] + ax * ay * F[iy1 * N + ix1];
 }
 
+__device__ __forceinline__ void cubic_weights(double a, double (&w)[4]) {
+  const double p = a + 1.0, q = a - 1.0, r = a - 2.0;
+  w[0] = -(a * q) * (r * (1.0 / 6.0));
+  w[1] = (p * q) * (r * 0.5);
+  w[2] = -(p * a) * (r * 0.5);
+  w[3] = (p * a) * (q * (1.0 / 6.0));
+}
+
 // periodic tensor-product cubic (4-point Lagrange) interpolant, same conventions
 __device__ double cubic_at(const double* __restrict__ F, int N, int jx, int jy, double xi_x, double xi_y,
                            double dx) {
   const double ox = xi_x / dx, oy = xi_y / dx;
   const double fx = floor(ox), fy = floor(oy);
   const double ax = ox - fx, ay = oy - fy;
-  const double wx[4] = {-ax * (ax - 1.0) * (ax - 2.0) / 6.0, (ax + 1.0) * (ax - 1.0) * (ax - 2.0) / 2.0,
-                        -(ax + 1.0) * ax * (ax - 2.0) / 2.0, (ax + 1.0) * ax * (ax - 1.0) / 6.0};
-  const double wy[4] = {-ay * (ay - 1.0) * (ay - 2.0) / 6.0, (ay + 1.0) * (ay - 1.0) * (ay - 2.0) / 2.0,
-                        -(ay + 1.0) * ay * (ay - 2.0) / 2.0, (ay + 1.0) * ay * (ay - 1.0) / 6.0};
+  double wx[4], wy[4];
+  cubic_weights(ax, wx);
+  cubic_weights(ay, wy);
   int bx = jx + cell_mod(fx, N), by = jy + cell_mod(fy, N);  // in [0, 2N)
   bx = bx >= N ? bx - N : bx;
   by = by >= N ? by - N : by;

@@ -294,14 +294,17 @@ __host__ __device__ constexpr int tw_offset(int n, int e, int s) {
 }
 __host__ __device__ constexpr int tw_len(int n, int e) { return tw_offset(n, e, 3); }
 
-// values per lane of the column and row passes.  N >= 512: 16 (a 1024-point
-// transform stays inside one wavefront, no workgroup barriers).  N <= 256: 8.
-// A step of a small grid is bound by the latency of its dependent chains, not by
-// the chip's rates: 8 values halve a lane's work per butterfly stage and double
-// the waves (measured per step, 16 -> 8 values: 64^2 float64 191 -> 115 us,
-// 128^2 float32 130 -> 86, 256^2 float64 227 -> 165, 256^2 float32 146 -> 102).
-// N = 3 * 2^k: 12 (first stage radix 12 = 3 x 4).
-__host__ __device__ constexpr int fft_E_of(int n) { return (n % 3 == 0) ? 12 : (n <= 256 ? 8 : 16); }
+// values per lane of the column and row passes.  A step of a small grid is bound
+// by the latency of its dependent chains, not by the chip's rates: fewer values
+// shorten a lane's work per butterfly stage and give more waves, at the price of
+// one more exchange.  N <= 256: 4 (measured per step, 8 -> 4 values: 64^2 float64
+// 67.8 -> 58.8 us, float32 68.2 -> 53.6, 128^2 float32 72.5 -> 62.2, 256^2 float64
+// 114.9 -> 100.5).  N = 512: 8 (16 -> 8: float32 155 -> 131, float64 198 -> 183).
+// N = 1024: 16, so that a transform stays inside one wavefront.  N = 3 * 2^k: 12
+// (first stage radix 12 = 3 x 4; the lanes of a transform have to divide a wave).
+__host__ __device__ constexpr int fft_E_of(int n) {
+  return (n % 3 == 0) ? 12 : (n <= 256 ? 4 : n <= 512 ? 8 : 16);
+}
 template <int N>
 __host__ __device__ constexpr int fft_E() { return fft_E_of(N); }
 

@@ -84,14 +84,13 @@ void launch_rows_dyn(RunView& r, const StepPtrs<T>& P, double sval, hipStream_t 
 // the rows pass of strategy 2, and the momentum rows when requested
 template <typename T, int N>
 void launch_rows_rhs(RunView& r, const StepPtrs<T>& P, double sval) {
-  const dim3 g = coop_grid<T, N>(), b(RhsGeo<T, N>::THREADS), bm(64 * ROW_WAVES);
+  const dim3 g = coop_grid<T, N>(), b(RhsGeo<T, N>::THREADS), bm(MomGeo<T, N>::THREADS);
   const int rm = r.sched.remap;
   if (r.cubic) hipLaunchKernelGGL((k_rows_rhs<T, N, true>), g, b, 0, r.stream, P, sval, rm);
   else hipLaunchKernelGGL((k_rows_rhs<T, N, false>), g, b, 0, r.stream, P, sval, rm);
   if (r.mom) {
-    const dim3 gm = row_grid<N>(2);
-    if (r.cubic) hipLaunchKernelGGL((k_rows_mom<T, N, true>), gm, bm, 0, r.stream, P, sval, rm);
-    else hipLaunchKernelGGL((k_rows_mom<T, N, false>), gm, bm, 0, r.stream, P, sval, rm);
+    if (r.cubic) hipLaunchKernelGGL((k_rows_mom<T, N, true>), g, bm, 0, r.stream, P, sval, rm);
+    else hipLaunchKernelGGL((k_rows_mom<T, N, false>), g, bm, 0, r.stream, P, sval, rm);
   }
 }
 
@@ -234,14 +233,12 @@ void launch_batch_step_t(hipStream_t st, const RunDesc<T>* desc, int nruns, bool
     const dim3 b1(DynGeo<T, N>::THREADS);
     if (gen) hipLaunchKernelGGL((k_rows_dyn_b<T, N, true>), g1, b1, 0, st, desc, stage, rm);
     else hipLaunchKernelGGL((k_rows_dyn_b<T, N, false>), g1, b1, 0, st, desc, stage, rm);
-    const dim3 b2(RhsGeo<T, N>::THREADS), bm(64 * ROW_WAVES);
+    const dim3 b2(RhsGeo<T, N>::THREADS), bm(MomGeo<T, N>::THREADS);
     if (cubic) hipLaunchKernelGGL((k_rows_rhs_b<T, N, true>), g1, b2, 0, st, desc, stage, rm);
     else hipLaunchKernelGGL((k_rows_rhs_b<T, N, false>), g1, b2, 0, st, desc, stage, rm);
     if (mom) {
-      dim3 gm = row_grid<N>(2);
-      gm.z = nruns;
-      if (cubic) hipLaunchKernelGGL((k_rows_mom_b<T, N, true>), gm, bm, 0, st, desc, stage, rm);
-      else hipLaunchKernelGGL((k_rows_mom_b<T, N, false>), gm, bm, 0, st, desc, stage, rm);
+      if (cubic) hipLaunchKernelGGL((k_rows_mom_b<T, N, true>), g1, bm, 0, st, desc, stage, rm);
+      else hipLaunchKernelGGL((k_rows_mom_b<T, N, false>), g1, bm, 0, st, desc, stage, rm);
     }
     with_tile<T, N>(sc.tile, [&](auto w) {
       constexpr int W = decltype(w)::value;

@@ -300,16 +300,23 @@ __device__ __forceinline__ cplx<T> gather2(const P4<T>* __restrict__ F, int pair
 // one pair of the interleaved physical fields, as gather2: with
 // o = xi / dx, i0 = floor(o), a = o - i0, the nodes i0-1 .. i0+2 carry
 // -a(a-1)(a-2)/6, (a+1)(a-1)(a-2)/2, -(a+1)a(a-2)/2, (a+1)a(a-1)/6
+template <typename T>
+__device__ __forceinline__ void cubic_weights(T a, T (&w)[4]) {
+  const T p = a + T(1), q = a - T(1), r = a - T(2), sixth = T(1.0 / 6.0);  // no divisions
+  w[0] = -(a * q) * (r * sixth);
+  w[1] = (p * q) * (r * T(0.5));
+  w[2] = -(p * a) * (r * T(0.5));
+  w[3] = (p * a) * (q * sixth);
+}
 template <typename T, int N>
 __device__ __forceinline__ cplx<T> gather2_cubic(const P4<T>* __restrict__ F, int pair, int x, int y, T xix, T xiy) {
   const T scl = T(double(N) / 6.283185307179586476925286766559);
   T ox = xix * scl, oy = xiy * scl;
   const T fx = floor(ox), fy = floor(oy);
   const T ax = ox - fx, ay = oy - fy;
-  const T wx[4] = {-ax * (ax - T(1)) * (ax - T(2)) / T(6), (ax + T(1)) * (ax - T(1)) * (ax - T(2)) / T(2),
-                   -(ax + T(1)) * ax * (ax - T(2)) / T(2), (ax + T(1)) * ax * (ax - T(1)) / T(6)};
-  const T wy[4] = {-ay * (ay - T(1)) * (ay - T(2)) / T(6), (ay + T(1)) * (ay - T(1)) * (ay - T(2)) / T(2),
-                   -(ay + T(1)) * ay * (ay - T(2)) / T(2), (ay + T(1)) * ay * (ay - T(1)) / T(6)};
+  T wx[4], wy[4];
+  cubic_weights(ax, wx);
+  cubic_weights(ay, wy);
   const int bx = wrap2N<N>(x + cell_mod<N>(fx)), by = wrap2N<N>(y + cell_mod<N>(fy));
   const char* F2 = reinterpret_cast<const char*>(F) + pair * sizeof(cplx<T>);
   constexpr unsigned PT = sizeof(P4<T>), ROW = N * sizeof(P4<T>);
@@ -337,6 +344,15 @@ __device__ __forceinline__ cplx<T> gather2_cubic(const P4<T>* __restrict__ F, in
     out.y += wy[j] * row.y;
   }
   return out;
+}
+
+// points of a lane whose corners are loaded together (n points to gather): four,
+// but two of the cubic gathers' sixteen corners at 1024, where a third wave per
+// SIMD is worth more than the registers
+template <int N, bool CUB>
+__host__ __device__ constexpr int gather_points(int n) {
+  const int g = CUB && N >= 1024 ? 2 : 4;
+  return n % g == 0 ? g : (n % 2 == 0 ? 2 : 1);
 }
 
 // the pair of fields at x + xi, by either interpolant
@@ -368,7 +384,8 @@ struct CoopGeo {
   // large rows exchange real and imaginary parts in turn: half the LDS per
   // transform, so that more blocks fit a CU
   static constexpr bool SPLIT = N >= 1024 || (sizeof(T) == 8 && N >= 512);
-  static constexpr int RB = (SPLIT ? 1 : 2) * padded_len(N);  // a row's buffer, in values of T
+  // a row's buffer, in values of T (an even number: pairs are kept there too)
+  static constexpr int RB = SPLIT ? (padded_len(N) + 1) / 2 * 2 : 2 * padded_len(N);
   static_assert(N % WR == 0, "row geometry");
 };
 
@@ -432,8 +449,12 @@ struct DynGeo : CoopGeo<T, N> {
   // four: shared pairs apart from the transform buffers
   static constexpr int BUFS = SIX ? (G::SPLIT ? 8 : 6) : (G::SPLIT ? 8 : 6);
   static constexpr int LDS = BUFS * G::WR * G::RB;
-  // registers for this many resident waves per SIMD
-  static constexpr int MIN_WAVES = SIX ? 3 : (sizeof(T) == 4 ? 4 : 2);
+  // registers for this many resident waves per SIMD; the averaged fields' formulas
+  // (gen) take more of them
+  static constexpr int min_waves(bool gen) {
+    const bool f32 = sizeof(T) == 4;
+    return gen ? (f32 ? 2 : 1) : (SIX ? 3 : (f32 ? 4 : 2));
+  }
 };
 
 template <typename T, int N, bool GEN>
@@ -655,7 +676,7 @@ __device__ __forceinline__ void rows_dyn_body(const StepPtrs<T>& P, const Phys& 
 
 // GEN: averaged fields other than (eta, zeta)
 template <typename T, int N, bool GEN>
-__global__ void __launch_bounds__((DynGeo<T, N>::THREADS), (DynGeo<T, N>::MIN_WAVES))
+__global__ void __launch_bounds__((DynGeo<T, N>::THREADS), (DynGeo<T, N>::min_waves(GEN)))
     k_rows_dyn(StepPtrs<T> P, Phys ph, double s, int remap) {
   __shared__ __align__(16) T lds[DynGeo<T, N>::LDS];
   int rowblock, unused, z;
@@ -668,59 +689,76 @@ __global__ void __launch_bounds__((DynGeo<T, N>::THREADS), (DynGeo<T, N>::MIN_WA
 // --------------------------------------------------------------------------
 // Four waves, the pairs (xi_x, xi_y) and (g-bar_0, g-bar_1) of two waves each.
 // Wave 0 inverse-transforms xi and shares it, waves 1, 2 and 3 the gradients of
-// xi_x, xi_y and g-bar_0; then wave 0 the gradient of g-bar_1 while waves 1 and 3
-// gather their pair at x + xi.  Waves 2 and 0 hand their half of the pair's
+// xi_x, xi_y and g-bar_0, wave 0 then that of g-bar_1.  Of the pair's
 //   u(x+xi) - w - (w . grad) xi   (both components, eq. (4.5a)),
 //   f(x+xi) - w . grad g-bar      (eq. (4.5b))
-// to waves 1 and 3, which forward-transform it.  w = xi / (t - tau) is the
-// partial-mean velocity (u / 2 at t = tau).
+// each wave forms its own component's gradient terms; waves 1 and 3 gather their
+// pair, and with the sixteen corners of the cubic gathers waves 2 and 0 take half of
+// the points (bilinear ones: 128^2 float32 62.6 us per step whole, 64.4 in halves);
+// waves 2 and 0 hand theirs to waves 1 and 3, which forward-transform the pair.
+// w = xi / (t - tau) is the partial-mean velocity (u / 2 at t = tau).
 template <typename T, int N>
 struct RhsGeo : CoopGeo<T, N> {
   using G = CoopGeo<T, N>;
   static constexpr int WAVES = 4, THREADS = 64 * WAVES;
   static constexpr int BUFS = G::SPLIT ? 6 : 5;  // four transform buffers, then xi
   static constexpr int LDS = BUFS * G::WR * G::RB;
-  static constexpr int MIN_WAVES = sizeof(T) == 4 ? 4 : 2;
+  // registers for this many resident waves per SIMD
+  static constexpr int min_waves(bool cub) {
+    return sizeof(T) == 4 ? (cub ? (N < 1024 ? 2 : 3) : 4) : (cub ? 1 : 2);
+  }
 };
 
 template <typename T, int N, bool CUB, bool SPOS>
 __device__ __forceinline__ void rhs_products(const P4<T>* __restrict__ F, double s, int y, int t, int w,
                                              const SharedPair<T, CoopGeo<T, N>::SPLIT>& XI,
-                                             cplx<T> (&z)[fft_E<N>()], T* pair) {
-  constexpr int E = fft_E<N>(), NT = N / E;
-  constexpr int GG = CUB ? 1 : 4;  // points with their loads in flight together
-  static_assert(E % GG == 0, "gather groups");
+                                             cplx<T> (&z)[fft_E<N>()], T* pair, cplx<T>* half) {
+  constexpr int E = fft_E<N>(), NT = N / E, H = CUB ? E / 2 : E;
+  constexpr int GG = gather_points<N, CUB>(H);
   const T inv_s = SPOS ? T(1.0 / s) : T(0);
   const unsigned at = (unsigned)(y * N);
-  auto velocity = [&](int x, cplx<T> xi) -> cplx<T> {
+  // w and the wave's own component: -w_i - w . grad
+  const bool subx = (w == 1), suby = (w == 2);
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int x = t + NT * e;
+    cplx<T> v;
     if constexpr (SPOS) {
-      return {xi.x * inv_s, xi.y * inv_s};
+      const cplx<T> xi = XI.get(x);
+      v = {xi.x * inv_s, xi.y * inv_s};
     } else {
-      const P4<T> q = at32(F, at + x);
-      return {T(0.5) * q.u, T(0.5) * q.v};
+      const P4<T> q = at32(F + NT * e, at + t);
+      v = {T(0.5) * q.u, T(0.5) * q.v};
     }
-  };
+    const T own = subx ? v.x : (suby ? v.y : T(0));
+    z[e].x = -own - (v.x * z[e].x + v.y * z[e].y);
+    if (e % 4 == 3) sched_fence();
+  }
   if (w & 1) {
 #pragma unroll
-    for (int e0 = 0; e0 < E; e0 += GG) {
+    for (int e0 = 0; e0 < H; e0 += GG) {
 #pragma unroll
       for (int e = e0; e < e0 + GG; ++e) {
-        const int x = t + NT * e;
-        const cplx<T> xi = XI.get(x), v = velocity(x, xi);
-        const cplx<T> g = gather_pair<T, N, CUB>(F, w >> 1, x, y, xi.x, xi.y);
-        const T wx = (w == 1) ? v.x : T(0);
-        z[e] = {g.x - wx - (v.x * z[e].x + v.y * z[e].y), g.y};
+        const cplx<T> xi = XI.get(t + NT * e);
+        const cplx<T> g = gather_pair<T, N, CUB>(F, w >> 1, t + NT * e, y, xi.x, xi.y);
+        z[e] = {g.x + z[e].x, g.y};
       }
       sched_fence();
     }
+#pragma unroll
+    for (int e = H; e < E; ++e) z[e].y = T(0);
   } else {
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int x = t + NT * e;
-      const cplx<T> v = velocity(x, XI.get(x));
-      const T wy = (w == 2) ? v.y : T(0);
-      pair[x] = -wy - (v.x * z[e].x + v.y * z[e].y);
-      if (e % 4 == 3) sched_fence();
+    for (int e = 0; e < E; ++e) pair[t + NT * e] = z[e].x;
+    if constexpr (H == E) return;
+#pragma unroll
+    for (int e0 = H; e0 < E; e0 += GG) {
+#pragma unroll
+      for (int e = e0; e < e0 + GG; ++e) {
+        const cplx<T> xi = XI.get(t + NT * e);
+        half[t + NT * (e - H)] = gather_pair<T, N, CUB>(F, w == 0 ? 1 : 0, t + NT * e, y, xi.x, xi.y);
+      }
+      sched_fence();
     }
   }
 }
@@ -758,13 +796,22 @@ __device__ __forceinline__ void rows_rhs_body(const StepPtrs<T>& P, double s, in
     load_pair<T, N, true, false>(z, P.IC + IC_GBZ * rf, P.IC + (IC_GBZ + 1) * rf, row, t);
     inverse_row<T, N, SPLIT>(z, mine, t, P.tw);
   }
-  T* pair = buf(w == 0 ? 3 : 1);  // the transform buffer of the pair's other wave
-  if (s > 0.0) rhs_products<T, N, CUB, true>(P.uvhz, s, y, t, w, XI, z, pair);
-  else rhs_products<T, N, CUB, false>(P.uvhz, s, y, t, w, XI, z, pair);
+  // the even waves' component goes to their partner's transform buffer, their half
+  // of the gathered points (N / 2 pairs) to their own
+  T* pair = buf(w == 0 ? 3 : 1);
+  if (s > 0.0) rhs_products<T, N, CUB, true>(P.uvhz, s, y, t, w, XI, z, pair, reinterpret_cast<cplx<T>*>(mine));
+  else rhs_products<T, N, CUB, false>(P.uvhz, s, y, t, w, XI, z, pair, reinterpret_cast<cplx<T>*>(mine));
   __syncthreads();
   if (!(w & 1)) return;
+  const cplx<T>* half = reinterpret_cast<const cplx<T>*>(buf(w == 1 ? 2 : 0));
 #pragma unroll
-  for (int e = 0; e < E; ++e) z[e].y = z[e].y + mine[t + NT * e];
+  for (int e = 0; e < E; ++e) {
+    z[e].y = z[e].y + mine[t + NT * e];
+    if (CUB && e >= E / 2) {
+      const cplx<T> g = half[t + NT * (e - E / 2)];
+      z[e] = {z[e].x + g.x, z[e].y + g.y};
+    }
+  }
   xsync<NT>();
   cplx<T>* OA = P.RS + (w == 1 ? RS_XIX : RS_GBH) * rf;
   forward_row<T, N, SPLIT>(z, mine, t, P.tw, OA, OA + rf, row);
@@ -772,7 +819,7 @@ __device__ __forceinline__ void rows_rhs_body(const StepPtrs<T>& P, double s, in
 
 // CUB: cubic instead of bilinear strategy-2 gathers
 template <typename T, int N, bool CUB>
-__global__ void __launch_bounds__((RhsGeo<T, N>::THREADS), (RhsGeo<T, N>::MIN_WAVES))
+__global__ void __launch_bounds__((RhsGeo<T, N>::THREADS), (RhsGeo<T, N>::min_waves(CUB)))
     k_rows_rhs(StepPtrs<T> P, double s, int remap) {
   __shared__ __align__(16) T lds[RhsGeo<T, N>::LDS];
   int rowblock, unused, z;
@@ -782,92 +829,114 @@ __global__ void __launch_bounds__((RhsGeo<T, N>::THREADS), (RhsGeo<T, N>::MIN_WA
 
 // --------------------------------------------------------------------------
 // rows_mom: the strategy-2 mean of the momentum 1-form (appendix C, eq. (C.4)
-// in the g-bar form of eq. (4.5b)), launched after rows_rhs when requested.
-// Component i = x (task 0) or y (task 1):
+// in the g-bar form of eq. (4.5b)), launched after rows_rhs when requested:
 //   R_i = u_j(x + xi)(delta_ij + d_i xi_j) - w_j d_j g_i - g_j d_i xi_j / s
 // (w = xi / s, or u / 2 at s = 0, where g = 0 and the last term is not formed).
-// Order of work keeps at most three lane arrays live beside a transform.
 // --------------------------------------------------------------------------
+// Six waves: wave 0 inverse-transforms xi and wave 1 g (both shared), waves 2 and
+// 3 d_x (xi_x, xi_y) and d_y (xi_x, xi_y), waves 4 and 5 grad g_x and grad g_y.
+// Waves 2 and 3 gather u at x + xi and form
+//   u_i + sum_j (u_j - g_j / s) d_i xi_j,   waves 4 and 5  -w . grad g_i;
+// wave 2 adds the halves of both components and forward-transforms the pair.
+template <typename T, int N>
+struct MomGeo : CoopGeo<T, N> {
+  using G = CoopGeo<T, N>;
+  static constexpr int WAVES = 6, THREADS = 64 * WAVES;
+  static constexpr int BUFS = G::SPLIT ? 8 : 6;  // split: xi_y and g_y get buffers of their own
+  static constexpr int LDS = BUFS * G::WR * G::RB;
+  static constexpr int min_waves(bool cub) { return sizeof(T) == 4 ? (cub && N < 1024 ? 2 : 3) : (cub ? 1 : 2); }
+};
+
 template <typename T, int N, bool CUB>
-__device__ __forceinline__ void rows_mom_body(const StepPtrs<T>& P, double s, int rowblock,
-                                              int task, T* lds) {
-  using G = RowGeo<N>;
-  constexpr int E = G::E, NT = G::NT;
-  const int grp = row_group<NT>(), t = threadIdx.x % NT;
-  const int y = rowblock * G::RPB + grp;
-  T* buf = lds + grp * 2 * G::L;
+__device__ __forceinline__ void rows_mom_body(const StepPtrs<T>& P, double s, int rowblock, T* lds) {
+  using G = MomGeo<T, N>;
+  constexpr int E = G::E, NT = G::NT, WR = G::WR, RB = G::RB;
+  constexpr bool SPLIT = G::SPLIT;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);  // the wave's role
+  const int lane = threadIdx.x % 64;
+  const int g = lane / NT, t = lane % NT;
+  const int y = rowblock * WR + g;
+  auto buf = [&](int i) { return lds + (i * WR + g) * RB; };
+  const SharedPair<T, SPLIT> XI{buf(0), buf(SPLIT ? 6 : 0)}, GM{buf(1), buf(SPLIT ? 7 : 1)};
+  T* mine = buf(w);
   constexpr Dims d = dims_of<N>();
   constexpr size_t rf = d.rowfield_elems();
   const unsigned row = (unsigned)y * (unsigned)d.NKXP;
   const P4<T>* F = P.uvhz;
-  const bool ix = (task == 0);
-  cplx<T> a[E], b[E], c[E];
-  // d_i xi_x, d_i xi_y: i kx in the row pass for i = x, the column pass's i ky versions for i = y
-  if (ix) load_pair<T, N, true, true>(b, P.IC + IC_XIX * rf, P.IC + IC_XIY * rf, row, t);
-  else load_pair<T, N, false, false>(b, P.IC + IC_XIX_Y * rf, P.IC + IC_XIY_Y * rf, row, t);
-  inverse_row<T, N>(b, buf, t, P.tw);
-  // stretching: a.x = -(g_x d_i xi_x + g_y d_i xi_y) / s
-  if (s > 0.0) {
-    load_pair<T, N, false, false>(c, P.IC + IC_GMX * rf, P.IC + IC_GMY * rf, row, t);
-    inverse_row<T, N>(c, buf, t, P.tw);
-    const T inv_s = T(1.0 / s);
-#pragma unroll
-    for (int e = 0; e < E; ++e) a[e] = {-(c[e].x * b[e].x + c[e].y * b[e].y) * inv_s, T(0)};
+
+  cplx<T> z[E];
+  if (w == 2) {
+    load_pair<T, N, true, true>(z, P.IC + IC_XIX * rf, P.IC + IC_XIY * rf, row, t);
+  } else if (w >= 4) {
+    const cplx<T>* A = P.IC + (w == 4 ? IC_GMX : IC_GMY) * rf;
+    load_pair<T, N, true, false>(z, A, A + rf, row, t);
   } else {
-#pragma unroll
-    for (int e = 0; e < E; ++e) a[e] = {T(0), T(0)};
+    // xi, g, and the column pass's i ky versions of xi
+    const cplx<T>* A = P.IC + (w == 0 ? IC_XIX : w == 1 ? IC_GMX : IC_XIX_Y) * rf;
+    load_pair<T, N, false, false>(z, A, A + 2 * rf, row, t);
   }
-  // xi (kept until the gathers consume it)
-  load_pair<T, N, false, false>(c, P.IC + IC_XIX * rf, P.IC + IC_XIY * rf, row, t);
-  inverse_row<T, N>(c, buf, t, P.tw);
-  // advection: a.x -= w . grad g_i with w = xi / s (u / 2 at s = 0), formed on the fly
-  {
-    cplx<T> dg[E];
-    const int gi = ix ? IC_GMX : IC_GMY;
-    load_pair<T, N, true, false>(dg, P.IC + gi * rf, P.IC + (gi + 1) * rf, row, t);
-    inverse_row<T, N>(dg, buf, t, P.tw);
-    if (s > 0.0) {
-      const T inv_s = T(1.0 / s);
+  inverse_row<T, N, SPLIT>(z, mine, t, P.tw);
+  if (w < 2) {
+    const SharedPair<T, SPLIT> S{w == 0 ? XI.a : GM.a, w == 0 ? XI.b : GM.b};
 #pragma unroll
-      for (int e = 0; e < E; ++e) a[e].x = a[e].x - (c[e].x * inv_s * dg[e].x + c[e].y * inv_s * dg[e].y);
-    } else {
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const P4<T> q = at32(F, (unsigned)(y * N + t) + NT * e);
-        a[e].x = a[e].x - (T(0.5) * q.u * dg[e].x + T(0.5) * q.v * dg[e].y);
-      }
-    }
+    for (int e = 0; e < E; ++e) S.put(t + NT * e, z[e]);
   }
-  // the gathered (u, v) at x + xi and the pulled-back source (consumes xi)
-  const T dxi = ix ? T(1) : T(0), dyi = ix ? T(0) : T(1);
-  if constexpr (CUB) {
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const cplx<T> g = gather2_cubic<T, N>(F, 0, t + NT * e, y, c[e].x, c[e].y);
-      a[e].x = a[e].x + (g.x * (dxi + b[e].x) + g.y * (dyi + b[e].y));
-      sched_fence();
-    }
-  } else {
-    constexpr int GG = 4;
+  __syncthreads();
+  const bool spos = s > 0.0;
+  const T inv_s = spos ? T(1.0 / s) : T(0);
+  if (w == 2 || w == 3) {
+    constexpr int GG = gather_points<N, CUB>(E);
 #pragma unroll
     for (int e0 = 0; e0 < E; e0 += GG) {
 #pragma unroll
       for (int e = e0; e < e0 + GG; ++e) {
-        const cplx<T> g = gather2<T, N>(F, 0, t + NT * e, y, c[e].x, c[e].y);
-        a[e].x = a[e].x + (g.x * (dxi + b[e].x) + g.y * (dyi + b[e].y));
+        const int x = t + NT * e;
+        const cplx<T> xi = XI.get(x), gm = GM.get(x);
+        const cplx<T> u = gather_pair<T, N, CUB>(F, 0, x, y, xi.x, xi.y);
+        const T gx = spos ? gm.x * inv_s : T(0), gy = spos ? gm.y * inv_s : T(0);
+        const T ui = (w == 2) ? u.x : u.y;
+        z[e].x = ui + ((u.x - gx) * z[e].x + (u.y - gy) * z[e].y);
       }
       sched_fence();
     }
+  } else if (w >= 4) {
+    const unsigned at = (unsigned)(y * N);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int x = t + NT * e;
+      const cplx<T> xi = XI.get(x);
+      cplx<T> v = {xi.x * inv_s, xi.y * inv_s};
+      if (!spos) {
+        const P4<T> q = at32(F, at + x);
+        v = {T(0.5) * q.u, T(0.5) * q.v};
+      }
+      z[e].x = -(v.x * z[e].x + v.y * z[e].y);
+      if (e % 4 == 3) sched_fence();
+    }
   }
-  forward_row<T, N>(a, buf, t, P.tw, P.RS + (ix ? RS_GMX : RS_GMY) * rf, nullptr, row);
+  // every wave but 2 leaves its half as real values in its own buffer
+  if (w >= 3) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) mine[t + NT * e] = z[e].x;
+  }
+  __syncthreads();
+  if (w != 2) return;
+  const T *r3 = buf(3), *r4 = buf(4), *r5 = buf(5);
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int x = t + NT * e;
+    z[e] = {z[e].x + r4[x], r3[x] + r5[x]};
+  }
+  forward_row<T, N, SPLIT>(z, mine, t, P.tw, P.RS + RS_GMX * rf, P.RS + RS_GMY * rf, row);
 }
 
 template <typename T, int N, bool CUB>
-__global__ void __launch_bounds__(64 * ROW_WAVES) k_rows_mom(StepPtrs<T> P, double s, int remap) {
-  __shared__ __align__(16) T lds[RowGeo<N>::RPB * 2 * RowGeo<N>::L];
-  int rowblock, task, z;
-  xcd_split(gridDim.x, gridDim.y, rowblock, task, z, remap);  // grid = (row blocks, 2 components)
-  rows_mom_body<T, N, CUB>(P, s, rowblock, task, lds);
+__global__ void __launch_bounds__((MomGeo<T, N>::THREADS), (MomGeo<T, N>::min_waves(CUB)))
+    k_rows_mom(StepPtrs<T> P, double s, int remap) {
+  __shared__ __align__(16) T lds[MomGeo<T, N>::LDS];
+  int rowblock, unused, z;
+  xcd_split(gridDim.x, 1, rowblock, unused, z, remap);
+  rows_mom_body<T, N, CUB>(P, s, rowblock, lds);
 }
 
 // --------------------------------------------------------------------------
@@ -1487,7 +1556,7 @@ __device__ __forceinline__ double batch_s(const RunDesc<T>& R, int stage) {
 }
 
 template <typename T, int N, bool GEN>
-__global__ void __launch_bounds__((DynGeo<T, N>::THREADS), (DynGeo<T, N>::MIN_WAVES))
+__global__ void __launch_bounds__((DynGeo<T, N>::THREADS), (DynGeo<T, N>::min_waves(GEN)))
     k_rows_dyn_b(const RunDesc<T>* __restrict__ runs, int stage, int remap) {
   __shared__ __align__(16) T lds[DynGeo<T, N>::LDS];
   int rowblock, unused, z;
@@ -1497,7 +1566,7 @@ __global__ void __launch_bounds__((DynGeo<T, N>::THREADS), (DynGeo<T, N>::MIN_WA
 }
 
 template <typename T, int N, bool CUB>
-__global__ void __launch_bounds__((RhsGeo<T, N>::THREADS), (RhsGeo<T, N>::MIN_WAVES))
+__global__ void __launch_bounds__((RhsGeo<T, N>::THREADS), (RhsGeo<T, N>::min_waves(CUB)))
     k_rows_rhs_b(const RunDesc<T>* __restrict__ runs, int stage, int remap) {
   __shared__ __align__(16) T lds[RhsGeo<T, N>::LDS];
   int rowblock, unused, z;
@@ -1507,12 +1576,13 @@ __global__ void __launch_bounds__((RhsGeo<T, N>::THREADS), (RhsGeo<T, N>::MIN_WA
 }
 
 template <typename T, int N, bool CUB>
-__global__ void __launch_bounds__(64 * ROW_WAVES) k_rows_mom_b(const RunDesc<T>* __restrict__ runs, int stage, int remap) {
-  __shared__ __align__(16) T lds[RowGeo<N>::RPB * 2 * RowGeo<N>::L];
-  int rowblock, task, z;
-  xcd_split(gridDim.x, gridDim.y, rowblock, task, z, remap);
+__global__ void __launch_bounds__((MomGeo<T, N>::THREADS), (MomGeo<T, N>::min_waves(CUB)))
+    k_rows_mom_b(const RunDesc<T>* __restrict__ runs, int stage, int remap) {
+  __shared__ __align__(16) T lds[MomGeo<T, N>::LDS];
+  int rowblock, unused, z;
+  xcd_split(gridDim.x, 1, rowblock, unused, z, remap);
   const RunDesc<T>& R = runs[z];
-  rows_mom_body<T, N, CUB>(R.P, batch_s(R, stage), rowblock, task, lds);
+  rows_mom_body<T, N, CUB>(R.P, batch_s(R, stage), rowblock, lds);
 }
 
 // stage parity selects the stage-value buffers: between steps the current
