@@ -34,7 +34,6 @@ lm_status check_launch() {
   return LM_OK;
 }
 
-constexpr int NS = 11;  // spectral / physical fields of a stage
 constexpr int NOUT_E2D = 7;
 
 }  // namespace
@@ -44,9 +43,10 @@ struct lm_e2d {
   double dt, U0, V0;
   bool cubic;
   // byte offsets in v.slab
-  size_t Y, Y1, K1, R, S, IC, PH, NL, RSF, SLf[2], SLx[2], SLy[2], Zn[2], OUT, total;
+  size_t Y, K1, IC, PH, RSF, SLf[2], SLx[2], SLy[2], Zn[2], OUT, total;
   int cur;
   bool has_state, in_interval, has_out;
+  bool ic_current;  // the column-pass outputs are those of the current state
   int64_t n, n_tau;
   double T;
   template <typename X>
@@ -68,13 +68,9 @@ lm_status e2d_layout(lm_e2d* e) {
   e->v.L = lm::Layout{};
   e->v.L.tw64 = take(d.N * cD);
   e->Y = take(4 * sp * cD);
-  e->Y1 = take(4 * sp * cD);
   e->K1 = take(4 * sp * cD);
-  e->R = take(4 * sp * cD);
-  e->S = take(NS * sp * cD);
-  e->IC = take(NS * rf * cD);
-  e->PH = take(NS * nn * sizeof(double));
-  e->NL = take(4 * nn * sizeof(double));
+  e->IC = take(lm::E2D_NIC * rf * cD);
+  e->PH = take(3 * nn * sizeof(double));
   e->RSF = take(4 * rf * cD);
   for (int k = 0; k < 2; ++k) {
     e->SLf[k] = take(nn * sizeof(double));
@@ -87,70 +83,25 @@ lm_status e2d_layout(lm_e2d* e) {
   return LM_OK;
 }
 
-// spectral inputs -> physical fields: the first `count` of the 11 stage fields
-lm_status e2d_to_physical(lm_e2d* e, const cplx<double>* Yin, int count) {
-  lm::RunView& v = e->v;
-  const lm::Dims& d = v.d;
-  const size_t sp = d.spec_elems(), rf = d.rowfield_elems(), nn = (size_t)d.N * d.N;
-  cplx<double>* S = e->at<cplx<double>>(e->S);
-  cplx<double>* IC = e->at<cplx<double>>(e->IC);
-  double* PH = e->at<double>(e->PH);
-  lm::launch_e2d_spec(v.stream, d, Yin, S);
-  for (int q0 = 0; q0 < count; q0 += lm::IO_MAX) {
-    lm::IoColInv J{};
-    const int c = std::min(lm::IO_MAX, count - q0);
-    for (int q = 0; q < c; ++q) {
-      J.src[q] = S + (q0 + q) * sp;
-      J.src_f32[q] = 0;
-      J.dst[q] = IC + (q0 + q) * rf;
-    }
-    LM_DISPATCH_N(d.N, lm::launch_io_col_inverse, v, J, c);
-  }
-  lm::IoRowInv K{};
-  int p = 0;
-  for (int q = 0; q < count; q += 2, ++p) {
-    K.a[p] = IC + q * rf;
-    K.oa[p] = PH + q * nn;
-    K.sa[p] = 1.0;
-    K.ca[p] = (q == 0) ? e->U0 : 0.0;  // u carries the uniform flow
-    if (q + 1 < count) {
-      K.b[p] = IC + (q + 1) * rf;
-      K.ob[p] = PH + (q + 1) * nn;
-      K.sb[p] = 1.0;
-      K.cb[p] = (q == 0) ? e->V0 : 0.0;
-    }
-  }
-  LM_DISPATCH_N(d.N, lm::launch_io_row_inverse, v, K, p);
-  return check_launch();
+lm::E2DPtrs e2d_ptrs(lm_e2d* e) {
+  lm::E2DPtrs P;
+  P.Y = e->at<cplx<double>>(e->Y);
+  P.K1 = e->at<cplx<double>>(e->K1);
+  P.IC = e->at<cplx<double>>(e->IC);
+  P.RS = e->at<cplx<double>>(e->RSF);
+  P.PH = e->at<double>(e->PH);
+  P.tw = e->at<const cplx<double>>(e->v.L.tw64);
+  P.U0 = e->U0;
+  P.V0 = e->V0;
+  P.dt = e->dt;
+  return P;
 }
 
-// right-hand sides of the vorticity, g~, P_x, P_y at state Yin and time s since tau
-lm_status e2d_rhs(lm_e2d* e, const cplx<double>* Yin, double s) {
-  lm::RunView& v = e->v;
-  const lm::Dims& d = v.d;
-  const size_t sp = d.spec_elems(), rf = d.rowfield_elems(), nn = (size_t)d.N * d.N;
-  lm_status st;
-  if ((st = e2d_to_physical(e, Yin, NS)) != LM_OK) return st;
-  double* NL = e->at<double>(e->NL);
-  lm::launch_e2d_products(v.stream, (int)nn, e->at<double>(e->PH), NL, s);
-  cplx<double>* RSF = e->at<cplx<double>>(e->RSF);
-  lm::IoRowFwd F{};
-  for (int p = 0; p < 2; ++p) {
-    F.a[p] = NL + (2 * p) * nn;
-    F.b[p] = NL + (2 * p + 1) * nn;
-    F.oa[p] = RSF + (2 * p) * rf;
-    F.ob[p] = RSF + (2 * p + 1) * rf;
-  }
-  LM_DISPATCH_N(d.N, lm::launch_io_row_forward, v, F, 2);
-  lm::IoColFwd C{};
-  cplx<double>* R = e->at<cplx<double>>(e->R);
-  for (int q = 0; q < 4; ++q) {
-    C.src[q] = RSF + q * rf;
-    C.dst[q] = R + q * sp;
-    C.dst_f32[q] = 0;
-  }
-  LM_DISPATCH_N(d.N, lm::launch_io_col_forward, v, C, 4);
-  return check_launch();
+// the column-pass outputs of the current state
+void e2d_prologue(lm_e2d* e, const lm::E2DPtrs& P) {
+  if (e->ic_current) return;
+  LM_DISPATCH_N(e->v.d.N, lm::launch_e2d_columns, e->v.stream, P, -1, nullptr);
+  e->ic_current = true;
 }
 
 lm_status e2d_zero_means(lm_e2d* e) {
@@ -162,34 +113,55 @@ lm_status e2d_zero_means(lm_e2d* e) {
   return LM_OK;
 }
 
-// one Heun step of everything, then the semi-Lagrangian update; the events
-// ev0, ev1 (may be null) bracket the semi-Lagrangian kernel
-lm_status e2d_one_step(lm_e2d* e, hipEvent_t ev0, hipEvent_t ev1) {
-  lm::RunView& v = e->v;
-  const lm::Dims& d = v.d;
-  const size_t sp = d.spec_elems(), nn = (size_t)d.N * d.N;
-  const double m = double(e->n - e->n_tau);
-  const double s0 = m * e->dt;
-  cplx<double>* Y = e->at<cplx<double>>(e->Y);
-  cplx<double>* Y1 = e->at<cplx<double>>(e->Y1);
-  cplx<double>* K1 = e->at<cplx<double>>(e->K1);
-  const cplx<double>* R = e->at<cplx<double>>(e->R);
-  lm_status st;
-  if ((st = e2d_rhs(e, Y, s0)) != LM_OK) return st;
-  lm::launch_e2d_stage(v.stream, sp, Y, Y1, K1, R, e->dt, 0);
-  if ((st = e2d_rhs(e, Y1, s0 + e->dt)) != LM_OK) return st;
-  lm::launch_e2d_stage(v.stream, sp, Y, Y1, K1, R, e->dt, 1);
-  // u, v (with the uniform flow) and zeta at t_{n+1}: stage fields 0 .. 4
-  if ((st = e2d_to_physical(e, Y, 5)) != LM_OK) return st;
+// the semi-Lagrangian update after step m of the interval (u, v, zeta at its end
+// are in PH), between the two sets of fields; flips the current set
+lm::E2DSl e2d_sl_args(lm_e2d* e, double m) {
+  const size_t nn = (size_t)e->v.d.N * e->v.d.N;
   const double* PH = e->at<double>(e->PH);
   const int c = e->cur, o = c ^ 1;
-  if (ev0) HIP_TRY(hipEventRecord(ev0, v.stream));
-  lm::launch_e2d_sl(v.stream, d.N, PH, PH + nn, PH + 4 * nn, e->at<double>(e->Zn[c]), e->at<double>(e->SLf[c]),
-                    e->at<double>(e->SLx[c]), e->at<double>(e->SLy[c]), e->at<double>(e->SLf[o]),
-                    e->at<double>(e->SLx[o]), e->at<double>(e->SLy[o]), e->at<double>(e->Zn[o]), e->dt, m, e->cubic);
-  if (ev1) HIP_TRY(hipEventRecord(ev1, v.stream));
   e->cur = o;
-  e->n += 1;
+  return lm::E2DSl{PH, PH + nn, PH + 2 * nn, e->at<double>(e->Zn[c]), e->at<double>(e->SLf[c]),
+                   e->at<double>(e->SLx[c]), e->at<double>(e->SLy[c]), e->at<double>(e->SLf[o]),
+                   e->at<double>(e->SLx[o]), e->at<double>(e->SLy[o]), e->at<double>(e->Zn[o]), e->dt, m,
+                   e->cubic ? 1 : 0};
+}
+
+// nsteps Heun steps of everything with their semi-Lagrangian updates.  A step's
+// update needs u, v and zeta at its end: the next step's first rows pass stores
+// them, and its blocks ride in the column launch that follows; after the last
+// step a rows pass stores them and the update runs alone.  With events (a pair
+// per step) every update is a launch of its own between its pair.
+lm_status e2d_steps(lm_e2d* e, int nsteps, hipEvent_t* ev) {
+  if (nsteps <= 0) return LM_OK;
+  lm::RunView& v = e->v;
+  const int N = v.d.N;
+  const lm::E2DPtrs P = e2d_ptrs(e);
+  e2d_prologue(e, P);
+  auto sl_alone = [&](double m, hipEvent_t* pair) -> lm_status {
+    const lm::E2DSl a = e2d_sl_args(e, m);
+    if (pair) HIP_TRY(hipEventRecord(pair[0], v.stream));
+    LM_DISPATCH_N(N, lm::launch_e2d_sl, v.stream, a);
+    if (pair) HIP_TRY(hipEventRecord(pair[1], v.stream));
+    return LM_OK;
+  };
+  lm_status st;
+  for (int k = 0; k < nsteps; ++k) {
+    const double m = double(e->n - e->n_tau);
+    const double s0 = m * e->dt;
+    LM_DISPATCH_N(N, lm::launch_e2d_rows, v.stream, P, s0, k > 0 ? 1 : 0, 1);
+    if (k > 0 && !ev) {
+      const lm::E2DSl a = e2d_sl_args(e, m - 1.0);
+      LM_DISPATCH_N(N, lm::launch_e2d_columns, v.stream, P, 0, &a);
+    } else {
+      if (k > 0 && (st = sl_alone(m - 1.0, ev + 2 * (k - 1))) != LM_OK) return st;
+      LM_DISPATCH_N(N, lm::launch_e2d_columns, v.stream, P, 0, nullptr);
+    }
+    LM_DISPATCH_N(N, lm::launch_e2d_rows, v.stream, P, s0 + e->dt, 0, 1);
+    LM_DISPATCH_N(N, lm::launch_e2d_columns, v.stream, P, 1, nullptr);
+    e->n += 1;
+  }
+  LM_DISPATCH_N(N, lm::launch_e2d_rows, v.stream, P, 0.0, 1, 0);
+  if ((st = sl_alone(double(e->n - e->n_tau) - 1.0, ev ? ev + 2 * (nsteps - 1) : nullptr)) != LM_OK) return st;
   return check_launch();
 }
 
@@ -218,7 +190,7 @@ lm_status lm_e2d_create(const lm_e2d_config* cfg, void* hip_stream, lm_e2d** out
   e->V0 = cfg->V0;
   e->cubic = cfg->interp == LM_INTERP_CUBIC;
   e->cur = 0;
-  e->has_state = e->in_interval = e->has_out = false;
+  e->has_state = e->in_interval = e->has_out = e->ic_current = false;
   e->n = e->n_tau = 0;
   e->T = 0.0;
   e2d_layout(e);
@@ -243,7 +215,7 @@ lm_status lm_e2d_set_vorticity(lm_e2d* e, const double* zeta, int on_device) {
   if (!e || !zeta) return fail(LM_E_ARG, "null argument");
   lm::RunView& v = e->v;
   const lm::Dims& d = v.d;
-  const size_t sp = d.spec_elems(), rf = d.rowfield_elems(), nn = (size_t)d.N * d.N;
+  const size_t nn = (size_t)d.N * d.N;
   const lm::StreamDrain drain{v.stream};  // the caller's buffer is read before any return
   double* PH = e->at<double>(e->PH);
   HIP_TRY(hipMemcpyAsync(PH, zeta, nn * sizeof(double), on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
@@ -262,10 +234,13 @@ lm_status lm_e2d_set_vorticity(lm_e2d* e, const double* zeta, int on_device) {
   lm_status st;
   if ((st = e2d_zero_means(e)) != LM_OK) return st;
   // zeta_n on the grid for the first semi-Lagrangian step
-  if ((st = e2d_to_physical(e, e->at<cplx<double>>(e->Y), 5)) != LM_OK) return st;
-  HIP_TRY(hipMemcpyAsync(e->at<double>(e->Zn[e->cur]), PH + 4 * nn, nn * sizeof(double), hipMemcpyDeviceToDevice,
+  e->ic_current = false;
+  const lm::E2DPtrs P = e2d_ptrs(e);
+  e2d_prologue(e, P);
+  LM_DISPATCH_N(d.N, lm::launch_e2d_rows, v.stream, P, 0.0, 1, 0);
+  if ((st = check_launch()) != LM_OK) return st;
+  HIP_TRY(hipMemcpyAsync(e->at<double>(e->Zn[e->cur]), PH + 2 * nn, nn * sizeof(double), hipMemcpyDeviceToDevice,
                          v.stream));
-  (void)sp;
   HIP_TRY(hipStreamSynchronize(v.stream));
   e->n = e->n_tau = 0;
   e->has_state = true;
@@ -277,6 +252,7 @@ lm_status lm_e2d_begin_interval(lm_e2d* e) {
   if (!e) return fail(LM_E_ARG, "null handle");
   if (!e->has_state) return fail(LM_E_STATE, "no vorticity set");
   lm_status st;
+  e->ic_current = false;
   if ((st = e2d_zero_means(e)) != LM_OK) return st;
   e->n_tau = e->n;
   e->in_interval = true;
@@ -287,11 +263,7 @@ lm_status lm_e2d_step(lm_e2d* e, int32_t nsteps) {
   if (!e) return fail(LM_E_ARG, "null handle");
   if (nsteps < 0) return fail(LM_E_ARG, "nsteps < 0");
   if (!e->has_state) return fail(LM_E_STATE, "no vorticity set");
-  for (int k = 0; k < nsteps; ++k) {
-    lm_status st = e2d_one_step(e, nullptr, nullptr);
-    if (st != LM_OK) return st;
-  }
-  return LM_OK;
+  return e2d_steps(e, nsteps, nullptr);
 }
 
 lm_status lm_e2d_step_profiled(lm_e2d* e, int32_t nsteps, double* ms_step, double* ms_sl) {
@@ -303,7 +275,7 @@ lm_status lm_e2d_step_profiled(lm_e2d* e, int32_t nsteps, double* ms_step, doubl
   for (auto& x : ev)
     if (hipEventCreateWithFlags(&x, hipEventDisableSystemFence) != hipSuccess) st = fail(LM_E_HIP, "event creation");
   if (st == LM_OK && hipEventRecord(ev[2 * nsteps], e->v.stream) != hipSuccess) st = fail(LM_E_HIP, "event record");
-  for (int k = 0; k < nsteps && st == LM_OK; ++k) st = e2d_one_step(e, ev[2 * k], ev[2 * k + 1]);
+  if (st == LM_OK) st = e2d_steps(e, nsteps, ev.data());
   if (st == LM_OK && hipEventRecord(ev[2 * nsteps + 1], e->v.stream) != hipSuccess) st = fail(LM_E_HIP, "event record");
   if (st == LM_OK && hipEventSynchronize(ev[2 * nsteps + 1]) != hipSuccess) st = fail(LM_E_HIP, "event sync");
   if (st == LM_OK) {
@@ -332,6 +304,7 @@ lm_status lm_e2d_end_interval(lm_e2d* e, double* T_out) {
   const double T = double(e->n - e->n_tau) * e->dt;
   const lm::StreamDrain drain{v.stream};
   cplx<double>* IC = e->at<cplx<double>>(e->IC);
+  e->ic_current = false;  // its buffer takes the outputs' transforms
   double* OUT = e->at<double>(e->OUT);
   lm::IoColInv J{};
   for (int q = 0; q < 4; ++q) {

@@ -19,15 +19,29 @@ template <int N> void launch_io_col_forward(RunView& r, const IoColFwd& J, int c
 template <int N> void launch_io_col_inverse(RunView& r, const IoColInv& J, int count);
 template <int N> void launch_io_row_inverse(RunView& r, const IoRowInv& J, int count);
 void launch_nonfinite(RunView& r, const double* a, size_t n, int* flag);
-// two-dimensional incompressible flow (float64): spectral multipliers, products,
-// Heun stages and the semi-Lagrangian update (euler2d_kernels.hip)
-void launch_e2d_spec(hipStream_t st, const Dims& d, const cplx<double>* Y, cplx<double>* S);
-void launch_e2d_products(hipStream_t st, int nn, const double* PH, double* NL, double s);
-void launch_e2d_stage(hipStream_t st, size_t sp, cplx<double>* Y, cplx<double>* Y1, cplx<double>* K1,
-                      const cplx<double>* R, double dt, int stage);
-void launch_e2d_sl(hipStream_t st, int N, const double* u, const double* v, const double* znext, const double* znow,
-                   const double* f_old, const double* ex_old, const double* ey_old, double* f_new, double* ex_new,
-                   double* ey_new, double* z_new, double dt, double m, bool cubic);
+// two-dimensional incompressible flow (float64; euler2d_step.hpp, euler2d_sl.hpp)
+constexpr int E2D_NIC = 10;  // column-pass outputs
+struct E2DPtrs {
+  cplx<double>* Y;   // [4][NKX][NKY] zeta, g~, P_x, P_y
+  cplx<double>* K1;  // Heun's first slope, same shape
+  cplx<double>* IC;  // [E2D_NIC][N][NKXP]
+  cplx<double>* RS;  // [4][N][NKXP]
+  double* PH;        // [3][N][N] u, v, zeta
+  const cplx<double>* tw;
+  double U0, V0, dt;
+};
+struct E2DSl {  // one semi-Lagrangian update
+  const double *u, *v, *znext, *znow, *f_old, *ex_old, *ey_old;
+  double *f_new, *ex_new, *ey_new, *z_new;
+  double dt, m;
+  int cubic;
+};
+// store: u, v, zeta to PH; products: the right-hand sides' row spectra
+template <int N> void launch_e2d_rows(hipStream_t st, const E2DPtrs& P, double s, int store, int products);
+// stage 0, 1 of Heun's method, or -1: the current state's transforms; sl: a
+// semi-Lagrangian update carried along (or null)
+template <int N> void launch_e2d_columns(hipStream_t st, const E2DPtrs& P, int stage, const E2DSl* sl);
+template <int N> void launch_e2d_sl(hipStream_t st, const E2DSl& a);
 
 // strategy-1 remap of the interval outputs (float64, N x N planes)
 void launch_remap_s1(RunView& r, const double* fh, const double* fz, const double* ex, const double* ey,

@@ -4,6 +4,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "euler2d_step.hpp"
 #include "io_kernels.hpp"
 #include "launch.hpp"
 #include "step_kernels.hpp"
@@ -324,4 +325,7 @@ void launch_io_col_forward(RunView& r, const IoColFwd& J, int count) {
   template void launch_io_col_forward<N>(RunView&, const IoColFwd&, int);                             \
   template void launch_io_col_inverse<N>(RunView&, const IoColInv&, int);                             \
   template void launch_io_row_inverse<N>(RunView&, const IoRowInv&, int);                             \
+  template void launch_e2d_rows<N>(hipStream_t, const E2DPtrs&, double, int, int);                    \
+  template void launch_e2d_columns<N>(hipStream_t, const E2DPtrs&, int, const E2DSl*);                \
+  template void launch_e2d_sl<N>(hipStream_t, const E2DSl&);                                          \
   }
