@@ -104,13 +104,14 @@ void e2d_prologue(lm_e2d* e, const lm::E2DPtrs& P) {
   e->ic_current = true;
 }
 
-lm_status e2d_zero_means(lm_e2d* e) {
+void e2d_zero_means(lm_e2d* e) {
   const size_t sp = e->v.d.spec_elems(), nn = (size_t)e->v.d.N * e->v.d.N;
-  HIP_TRY(hipMemsetAsync(e->at<char>(e->Y) + sp * sizeof(cplx<double>), 0, 3 * sp * sizeof(cplx<double>), e->v.stream));
-  HIP_TRY(hipMemsetAsync(e->at<char>(e->SLf[e->cur]), 0, nn * sizeof(double), e->v.stream));
-  HIP_TRY(hipMemsetAsync(e->at<char>(e->SLx[e->cur]), 0, nn * sizeof(double), e->v.stream));
-  HIP_TRY(hipMemsetAsync(e->at<char>(e->SLy[e->cur]), 0, nn * sizeof(double), e->v.stream));
-  return LM_OK;
+  lm::SetRanges R;
+  R.add(e->at<char>(e->Y) + sp * sizeof(cplx<double>), 3 * sp * sizeof(cplx<double>));
+  R.add(e->at<char>(e->SLf[e->cur]), nn * sizeof(double));
+  R.add(e->at<char>(e->SLx[e->cur]), nn * sizeof(double));
+  R.add(e->at<char>(e->SLy[e->cur]), nn * sizeof(double));
+  lm::launch_set_ranges(e->v.stream, R);
 }
 
 // the semi-Lagrangian update after step m of the interval (u, v, zeta at its end
@@ -232,15 +233,16 @@ lm_status lm_e2d_set_vorticity(lm_e2d* e, const double* zeta, int on_device) {
   LM_DISPATCH_N(d.N, lm::launch_io_col_forward, v, C, 1);
   e->cur = 0;
   lm_status st;
-  if ((st = e2d_zero_means(e)) != LM_OK) return st;
+  e2d_zero_means(e);
   // zeta_n on the grid for the first semi-Lagrangian step
   e->ic_current = false;
   const lm::E2DPtrs P = e2d_ptrs(e);
   e2d_prologue(e, P);
   LM_DISPATCH_N(d.N, lm::launch_e2d_rows, v.stream, P, 0.0, 1, 0);
+  lm::SetRanges Z;
+  Z.add(e->at<double>(e->Zn[e->cur]), nn * sizeof(double), PH + 2 * nn);
+  lm::launch_set_ranges(v.stream, Z);
   if ((st = check_launch()) != LM_OK) return st;
-  HIP_TRY(hipMemcpyAsync(e->at<double>(e->Zn[e->cur]), PH + 2 * nn, nn * sizeof(double), hipMemcpyDeviceToDevice,
-                         v.stream));
   HIP_TRY(hipStreamSynchronize(v.stream));
   e->n = e->n_tau = 0;
   e->has_state = true;
@@ -253,7 +255,8 @@ lm_status lm_e2d_begin_interval(lm_e2d* e) {
   if (!e->has_state) return fail(LM_E_STATE, "no vorticity set");
   lm_status st;
   e->ic_current = false;
-  if ((st = e2d_zero_means(e)) != LM_OK) return st;
+  e2d_zero_means(e);
+  if ((st = check_launch()) != LM_OK) return st;
   e->n_tau = e->n;
   e->in_interval = true;
   return LM_OK;
@@ -324,9 +327,11 @@ lm_status lm_e2d_end_interval(lm_e2d* e, double* T_out) {
   }
   LM_DISPATCH_N(d.N, lm::launch_io_row_inverse, v, K, 2);
   const size_t plane = nn * sizeof(double);
-  HIP_TRY(hipMemcpyAsync(OUT + 4 * nn, e->at<double>(e->SLf[e->cur]), plane, hipMemcpyDeviceToDevice, v.stream));
-  HIP_TRY(hipMemcpyAsync(OUT + 5 * nn, e->at<double>(e->SLx[e->cur]), plane, hipMemcpyDeviceToDevice, v.stream));
-  HIP_TRY(hipMemcpyAsync(OUT + 6 * nn, e->at<double>(e->SLy[e->cur]), plane, hipMemcpyDeviceToDevice, v.stream));
+  lm::SetRanges R;
+  R.add(OUT + 4 * nn, plane, e->at<double>(e->SLf[e->cur]));
+  R.add(OUT + 5 * nn, plane, e->at<double>(e->SLx[e->cur]));
+  R.add(OUT + 6 * nn, plane, e->at<double>(e->SLy[e->cur]));
+  lm::launch_set_ranges(v.stream, R);
   lm_status st;
   if ((st = check_launch()) != LM_OK) return st;
   HIP_TRY(hipStreamSynchronize(v.stream));

@@ -40,12 +40,20 @@ __global__ void __launch_bounds__(64 * ROW_WAVES) k_io_row_inverse(IoRowInv J, D
   cplx<double> z[E];
   load_pair<double, N, false, false>(z, A, B, (unsigned)y * (unsigned)d.NKXP, t);
   inverse_row<double, N>(z, buf, t, tw);
+  bool bad = false;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const size_t i = (size_t)y * N + t + NT * e;
-    J.oa[q][i] = z[e].x * J.sa[q] + J.ca[q];
-    if (J.b[q]) J.ob[q][i] = z[e].y * J.sb[q] + J.cb[q];
+    const double a = z[e].x * J.sa[q] + J.ca[q];
+    J.oa[q][i] = a;
+    bad |= (a - a != 0.0);  // NaN or infinite
+    if (J.b[q]) {
+      const double b = z[e].y * J.sb[q] + J.cb[q];
+      J.ob[q][i] = b;
+      bad |= (b - b != 0.0);
+    }
   }
+  if (J.flag && __any(bad) && (threadIdx.x & 63) == 0) atomicOr(J.flag, 1);
 }
 
 template <int N>

@@ -5,7 +5,7 @@
 
 namespace lm {
 
-constexpr int IO_MAX = 8;
+constexpr int IO_MAX = 10;
 
 struct IoRowFwd {  // two physical fields -> two half-spectrum row fields
   const double* a[IO_MAX];
@@ -34,6 +34,7 @@ struct IoRowInv {  // two column-pass outputs -> two physical fields, scaled
   double sb[IO_MAX];
   double ca[IO_MAX];
   double cb[IO_MAX];
+  int* flag;  // set when an output is not finite (or null)
 };
 
 }  // namespace lm

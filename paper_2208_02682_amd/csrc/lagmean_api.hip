@@ -262,26 +262,26 @@ FieldRef state_field(lm_run* r, int which) {
   return {r->slab + r->L.Yd + dmap[which - LM_P_XI_X] * sp * sizeof(cplx<double>), nullptr, 0};
 }
 
-lm_status copy_in(lm_run* r, double* dst, const double* src, int on_device) {
-  const size_t bytes = (size_t)r->d.N * r->d.N * sizeof(double);
-  HIP_TRY(hipMemcpyAsync(dst, src, bytes, on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, r->stream));
-  return LM_OK;
-}
 lm_status copy_out(lm_run* r, double* dst, const double* src, int on_device) {
   const size_t bytes = (size_t)r->d.N * r->d.N * sizeof(double);
   HIP_TRY(hipMemcpyAsync(dst, src, bytes, on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, r->stream));
   return LM_OK;
 }
 
-lm_status zero_means(lm_run* r) {
-  const size_t sp = r->d.spec_elems();
+// the averaging state of a new interval: accumulators, xi and P zero, and with them
+// their column-pass outputs (the transforms of zero); the flag of non-finite
+// outputs cleared
+void zero_means(lm_run* r) {
+  const size_t sp = r->d.spec_elems(), rf = r->d.rowfield_elems();
   const size_t cT = r->fp32 ? sizeof(cplx<float>) : sizeof(cplx<double>);
-  const int nsf = r->mom ? lm::NSF_R : lm::SF_GMX;
-  HIP_TRY(hipMemsetAsync(r->slab + r->L.Yr + lm::SF_GBH * sp * cT, 0, (nsf - lm::SF_GBH) * sp * cT, r->stream));
-  if (r->fp32)
-    HIP_TRY(hipMemsetAsync(r->slab + r->L.Yl + lm::SF_GBH * sp * cT, 0, (nsf - lm::SF_GBH) * sp * cT, r->stream));
-  HIP_TRY(hipMemsetAsync(r->slab + r->L.Yd, 0, lm::NSF_D * sp * sizeof(cplx<double>), r->stream));
-  return LM_OK;
+  const int nsf = r->mom ? lm::NSF_R : lm::SF_GMX, nic = r->mom ? lm::NIC : lm::IC_GMX;
+  lm::SetRanges R;
+  R.add(r->slab + r->L.Yr + lm::SF_GBH * sp * cT, (nsf - lm::SF_GBH) * sp * cT);
+  if (r->fp32) R.add(r->slab + r->L.Yl + lm::SF_GBH * sp * cT, (nsf - lm::SF_GBH) * sp * cT);
+  R.add(r->slab + r->L.Yd, lm::NSF_D * sp * sizeof(cplx<double>));
+  R.add(r->slab + r->L.IC + lm::IC_XIX * rf * cT, (nic - lm::IC_XIX) * rf * cT);
+  R.flag = (int*)r->at(r->L.flag);
+  lm::launch_set_ranges(r->stream, R);
 }
 
 using lm::StreamDrain;
@@ -474,10 +474,10 @@ lm_status lm_set_state(lm_run* r, const double* u, const double* v, const double
   const StreamDrain drain{r->stream};  // the caller's buffers are read before any return
   const size_t nn = (size_t)r->d.N * r->d.N;
   double* phys = (double*)r->at(r->L.phys);
-  lm_status s;
-  if ((s = copy_in(r, phys, u, on_device)) != LM_OK) return s;
-  if ((s = copy_in(r, phys + nn, v, on_device)) != LM_OK) return s;
-  if ((s = copy_in(r, phys + 2 * nn, h, on_device)) != LM_OK) return s;
+  const double* in[3] = {u, v, h};
+  for (int q = 0; q < 3; ++q)
+    HIP_TRY(hipMemcpyAsync(phys + q * nn, in[q], nn * sizeof(double),
+                           on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, r->stream));
   const size_t rf = r->d.rowfield_elems();
   cplx<double>* ioC = (cplx<double>*)r->at(r->L.ioC);
   lm::IoRowFwd J{};
@@ -494,10 +494,11 @@ lm_status lm_set_state(lm_run* r, const double* u, const double* v, const double
     K.dst_f32[q] = r->fp32 ? 1 : 0;
   }
   LM_DISPATCH_N(r->d.N, lm::launch_io_col_forward, *r, K, 3);
-  if ((s = zero_means(r)) != LM_OK) return s;
+  zero_means(r);
   r->ys_cur = 0;
   use_sched(r);
-  LM_DISPATCH_N(r->d.N, lm::launch_prologue, *r);
+  LM_DISPATCH_N(r->d.N, lm::launch_prologue_dyn, *r);
+  lm_status s;
   if ((s = check_launch()) != LM_OK) return s;
   HIP_TRY(hipStreamSynchronize(r->stream));
   r->n = r->n_tau = 0;
@@ -539,10 +540,10 @@ lm_status lm_begin_interval(lm_run* r) {
   if (!r) return fail(LM_E_ARG, "null run");
   if (r->batch) return fail(LM_E_STATE, "the run belongs to a batch");
   if (!r->has_state) return fail(LM_E_STATE, "no state set");
+  // the dynamics' column-pass outputs are those of the current state already
+  // (lm_set_state, lm_restore and every step leave them so)
+  zero_means(r);
   lm_status s;
-  if ((s = zero_means(r)) != LM_OK) return s;
-  use_sched(r);
-  LM_DISPATCH_N(r->d.N, lm::launch_prologue, *r);
   if ((s = check_launch()) != LM_OK) return s;
   r->n_tau = r->n;
   r->in_interval = true;
@@ -607,6 +608,7 @@ lm_status lm_end_interval(lm_run* r, double* T_out) {
   if (!r->in_interval) return fail(LM_E_STATE, "no open interval");
   if (r->n == r->n_tau) return fail(LM_E_STATE, "interval holds no step");
   const double T = double(r->n - r->n_tau) * r->ph.dt;
+  int hflag = 0;  // outlives every copy into it
   const StreamDrain drain{r->stream};
   const size_t nn = (size_t)r->d.N * r->d.N, rf = r->d.rowfield_elems();
   cplx<double>* ioC = (cplx<double>*)r->at(r->L.ioC);
@@ -615,17 +617,17 @@ lm_status lm_end_interval(lm_run* r, double* T_out) {
   // accumulators in output order: (gbar_h, gbar_z), (xi_x, xi_y), (gtil_h, gtil_z), (P_x, P_y), (E_h, E_z)
   static const int order[10] = {LM_P_GBAR_H, LM_P_GBAR_ZETA, LM_P_XI_X, LM_P_XI_Y, LM_P_GTIL_H,
                                 LM_P_GTIL_ZETA, LM_P_P_X, LM_P_P_Y, LM_P_E_H, LM_P_E_ZETA};
-  for (int half = 0; half < 2; ++half) {
-    lm::IoColInv J{};
-    for (int q = 0; q < 5; ++q) {
-      const FieldRef f = state_field(r, order[half * 5 + q]);
-      J.src[q] = f.ptr;
-      J.src_lo[q] = f.lo;
-      J.src_f32[q] = f.f32;
-      J.dst[q] = ioC + (half * 5 + q) * rf;
-    }
-    LM_DISPATCH_N(r->d.N, lm::launch_io_col_inverse, *r, J, 5);
+  lm::IoColInv J{};
+  for (int q = 0; q < 10; ++q) {
+    const FieldRef f = state_field(r, order[q]);
+    J.src[q] = f.ptr;
+    J.src_lo[q] = f.lo;
+    J.src_f32[q] = f.f32;
+    J.dst[q] = ioC + q * rf;
   }
+  LM_DISPATCH_N(r->d.N, lm::launch_io_col_inverse, *r, J, 10);
+  // cleared when the interval was opened
+  int* flag = (int*)r->at(r->L.flag);
   lm::IoRowInv K{};
   for (int p = 0; p < 5; ++p) {
     K.a[p] = ioC + (2 * p) * rf;
@@ -639,6 +641,7 @@ lm_status lm_end_interval(lm_run* r, double* T_out) {
     K.ca[p] = ((p == 0 || p == 2 || p == 4) && r->ph.fs0 == lm::FS_ETA) ? r->ph.H : 0.0;
     K.cb[p] = 0.0;
   }
+  K.flag = flag;
   LM_DISPATCH_N(r->d.N, lm::launch_io_row_inverse, *r, K, 5);
   if (r->mom) {
     // the momentum 1-form mean g-bar_m / T (planes OUT_MOM, OUT_MOM + 1)
@@ -657,18 +660,13 @@ lm_status lm_end_interval(lm_run* r, double* T_out) {
     Km.oa[0] = out + lm::OUT_MOM * nn;
     Km.ob[0] = out + (lm::OUT_MOM + 1) * nn;
     Km.sa[0] = Km.sb[0] = 1.0 / T;
+    Km.flag = flag;
     LM_DISPATCH_N(r->d.N, lm::launch_io_row_inverse, *r, Km, 1);
   }
-  int* flag = (int*)r->at(r->L.flag);
-  HIP_TRY(hipMemsetAsync(flag, 0, sizeof(int), r->stream));
-  lm::launch_nonfinite(*r, out, 10 * nn, flag);
-  if (r->mom) lm::launch_nonfinite(*r, out + lm::OUT_MOM * nn, 2 * nn, flag);
   lm_status s;
   if ((s = check_launch()) != LM_OK) return s;
-  // the flag is read with a blocking copy once the stream has drained
-  int hflag = 0;
+  HIP_TRY(hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, r->stream));
   HIP_TRY(hipStreamSynchronize(r->stream));
-  HIP_TRY(hipMemcpy(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost));
   r->T = T;
   r->has_mean = true;
   r->in_interval = false;
@@ -864,6 +862,7 @@ lm_status lm_restore(lm_run* r, const void* buf, size_t size, int on_device) {
   if (h.bytes_l) HIP_TRY(hipMemcpyAsync(r->slab + r->L.Yl, in + off, h.bytes_l, x2d, r->stream));
   off += h.bytes_l;
   HIP_TRY(hipMemcpyAsync(r->slab + r->L.Yd, in + off, h.bytes_d, x2d, r->stream));
+  HIP_TRY(hipMemsetAsync(r->at(r->L.flag), 0, sizeof(int), r->stream));
   r->n = h.steps;
   r->n_tau = h.n_tau;
   r->ys_cur = 0;

@@ -10,6 +10,7 @@ namespace lm {
 template <int N> void launch_steps(RunView& r, int nsteps);   // nsteps RK4 steps
 template <int N> hipError_t launch_steps_profiled(RunView& r, int nsteps, double* ms);  // + kernel times
 template <int N> void launch_prologue(RunView& r);            // column pass of the current state
+template <int N> void launch_prologue_dyn(RunView& r);        // of u, v, h alone
 // one RK4 step for nruns runs of one (N, precision, gather, momentum, averaged fields) group; desc: device array of RunDesc<T>
 template <int N> void launch_batch_step(hipStream_t st, const void* desc, int nruns, bool fp32, bool cubic, bool mom,
                                         bool gen, const Sched& sc);
@@ -18,7 +19,20 @@ template <int N> void launch_io_row_forward(RunView& r, const IoRowFwd& J, int c
 template <int N> void launch_io_col_forward(RunView& r, const IoColFwd& J, int count);
 template <int N> void launch_io_col_inverse(RunView& r, const IoColInv& J, int count);
 template <int N> void launch_io_row_inverse(RunView& r, const IoRowInv& J, int count);
-void launch_nonfinite(RunView& r, const double* a, size_t n, int* flag);
+// device ranges of 64-bit words set in one launch: zeroed, or copied from src
+struct SetRanges {
+  int count = 0;
+  unsigned long long* dst[5] = {};
+  const unsigned long long* src[5] = {};
+  size_t words[5] = {};
+  int* flag = nullptr;  // zeroed as well, when given
+  void add(void* d, size_t bytes, const void* s = nullptr) {
+    dst[count] = (unsigned long long*)d;
+    src[count] = (const unsigned long long*)s;
+    words[count++] = bytes / 8;
+  }
+};
+void launch_set_ranges(hipStream_t st, const SetRanges& R);
 // two-dimensional incompressible flow (float64; euler2d_step.hpp, euler2d_sl.hpp)
 constexpr int E2D_NIC = 10;  // column-pass outputs
 struct E2DPtrs {

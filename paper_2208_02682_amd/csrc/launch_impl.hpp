@@ -271,6 +271,12 @@ void launch_prologue(RunView& r) {
 }
 
 template <int N>
+void launch_prologue_dyn(RunView& r) {
+  if (r.fp32) launch_columns_part<float, N>(r, -1, 0, 3, r.stream);
+  else launch_columns_part<double, N>(r, -1, 0, 3, r.stream);
+}
+
+template <int N>
 void launch_io_col_inverse(RunView& r, const IoColInv& J, int count) {
   hipLaunchKernelGGL((k_io_col_inverse<N>), col_grid<N>(r.d, count), col_block<N>(), 0, r.stream, J, r.d,
                      (const cplx<double>*)r.at(r.L.tw64));
@@ -302,6 +308,7 @@ void launch_io_col_forward(RunView& r, const IoColFwd& J, int count) {
   template void launch_steps_t<T, N>(RunView&, int);                                                     \
   template hipError_t launch_steps_profiled_t<T, N>(RunView&, int, double*);                             \
   template void launch_columns_t<T, N>(RunView&, int);                                                   \
+  template void launch_columns_part<T, N>(RunView&, int, int, int, hipStream_t);                         \
   template void launch_batch_step_t<T, N>(hipStream_t, const RunDesc<T>*, int, bool, bool, bool, const Sched&); \
   }
 
@@ -310,6 +317,7 @@ void launch_io_col_forward(RunView& r, const IoColFwd& J, int count) {
   extern template void launch_steps_t<T, N>(RunView&, int);                                                     \
   extern template hipError_t launch_steps_profiled_t<T, N>(RunView&, int, double*);                             \
   extern template void launch_columns_t<T, N>(RunView&, int);                                                   \
+  extern template void launch_columns_part<T, N>(RunView&, int, int, int, hipStream_t);                         \
   extern template void launch_batch_step_t<T, N>(hipStream_t, const RunDesc<T>*, int, bool, bool, bool, const Sched&); \
   }
 
@@ -321,6 +329,7 @@ void launch_io_col_forward(RunView& r, const IoColFwd& J, int count) {
   template void launch_batch_step<N>(hipStream_t, const void*, int, bool, bool, bool, bool, const Sched&); \
   template hipError_t launch_steps_profiled<N>(RunView&, int, double*);                               \
   template void launch_prologue<N>(RunView&);                                                         \
+  template void launch_prologue_dyn<N>(RunView&);                                                     \
   template void launch_io_row_forward<N>(RunView&, const IoRowFwd&, int);                             \
   template void launch_io_col_forward<N>(RunView&, const IoColFwd&, int);                             \
   template void launch_io_col_inverse<N>(RunView&, const IoColInv&, int);                             \
