@@ -43,8 +43,10 @@ struct lm_e2d {
   double dt, U0, V0;
   bool cubic;
   // byte offsets in v.slab
-  size_t Y, K1, IC, PH, RSF, SLf[2], SLx[2], SLy[2], Zn[2], OUT, total;
-  int cur;
+  size_t Yb[2], K1, IC, PH, RSF, SLf[2], SLx[2], SLy[2], Zn[2], OUT, total;
+  int cur;   // current semi-Lagrangian fields
+  int ycur;  // current spectral state
+  size_t Y() const { return Yb[ycur]; }
   bool has_state, in_interval, has_out;
   bool ic_current;  // the column-pass outputs are those of the current state
   int64_t n, n_tau;
@@ -67,7 +69,7 @@ lm_status e2d_layout(lm_e2d* e) {
   };
   e->v.L = lm::Layout{};
   e->v.L.tw64 = take(d.N * cD);
-  e->Y = take(4 * sp * cD);
+  for (int k = 0; k < 2; ++k) e->Yb[k] = take(4 * sp * cD);
   e->K1 = take(4 * sp * cD);
   e->IC = take(lm::E2D_NIC * rf * cD);
   e->PH = take(3 * nn * sizeof(double));
@@ -85,7 +87,8 @@ lm_status e2d_layout(lm_e2d* e) {
 
 lm::E2DPtrs e2d_ptrs(lm_e2d* e) {
   lm::E2DPtrs P;
-  P.Y = e->at<cplx<double>>(e->Y);
+  P.Y = e->at<cplx<double>>(e->Y());
+  P.Yn = e->at<cplx<double>>(e->Yb[e->ycur ^ 1]);
   P.K1 = e->at<cplx<double>>(e->K1);
   P.IC = e->at<cplx<double>>(e->IC);
   P.RS = e->at<cplx<double>>(e->RSF);
@@ -107,7 +110,7 @@ void e2d_prologue(lm_e2d* e, const lm::E2DPtrs& P) {
 void e2d_zero_means(lm_e2d* e) {
   const size_t sp = e->v.d.spec_elems(), nn = (size_t)e->v.d.N * e->v.d.N;
   lm::SetRanges R;
-  R.add(e->at<char>(e->Y) + sp * sizeof(cplx<double>), 3 * sp * sizeof(cplx<double>));
+  R.add(e->at<char>(e->Y()) + sp * sizeof(cplx<double>), 3 * sp * sizeof(cplx<double>));
   R.add(e->at<char>(e->SLf[e->cur]), nn * sizeof(double));
   R.add(e->at<char>(e->SLx[e->cur]), nn * sizeof(double));
   R.add(e->at<char>(e->SLy[e->cur]), nn * sizeof(double));
@@ -136,7 +139,7 @@ lm_status e2d_steps(lm_e2d* e, int nsteps, hipEvent_t* ev) {
   if (nsteps <= 0) return LM_OK;
   lm::RunView& v = e->v;
   const int N = v.d.N;
-  const lm::E2DPtrs P = e2d_ptrs(e);
+  lm::E2DPtrs P = e2d_ptrs(e);
   e2d_prologue(e, P);
   auto sl_alone = [&](double m, hipEvent_t* pair) -> lm_status {
     const lm::E2DSl a = e2d_sl_args(e, m);
@@ -159,6 +162,8 @@ lm_status e2d_steps(lm_e2d* e, int nsteps, hipEvent_t* ev) {
     }
     LM_DISPATCH_N(N, lm::launch_e2d_rows, v.stream, P, s0 + e->dt, 0, 1);
     LM_DISPATCH_N(N, lm::launch_e2d_columns, v.stream, P, 1, nullptr);
+    e->ycur ^= 1;
+    std::swap(P.Y, P.Yn);
     e->n += 1;
   }
   LM_DISPATCH_N(N, lm::launch_e2d_rows, v.stream, P, 0.0, 1, 0);
@@ -190,7 +195,7 @@ lm_status lm_e2d_create(const lm_e2d_config* cfg, void* hip_stream, lm_e2d** out
   e->U0 = cfg->U0;
   e->V0 = cfg->V0;
   e->cubic = cfg->interp == LM_INTERP_CUBIC;
-  e->cur = 0;
+  e->cur = e->ycur = 0;
   e->has_state = e->in_interval = e->has_out = e->ic_current = false;
   e->n = e->n_tau = 0;
   e->T = 0.0;
@@ -228,7 +233,7 @@ lm_status lm_e2d_set_vorticity(lm_e2d* e, const double* zeta, int on_device) {
   LM_DISPATCH_N(d.N, lm::launch_io_row_forward, v, F, 1);
   lm::IoColFwd C{};
   C.src[0] = RSF;
-  C.dst[0] = e->at<cplx<double>>(e->Y);
+  C.dst[0] = e->at<cplx<double>>(e->Y());
   C.dst_f32[0] = 0;
   LM_DISPATCH_N(d.N, lm::launch_io_col_forward, v, C, 1);
   e->cur = 0;
@@ -311,7 +316,7 @@ lm_status lm_e2d_end_interval(lm_e2d* e, double* T_out) {
   double* OUT = e->at<double>(e->OUT);
   lm::IoColInv J{};
   for (int q = 0; q < 4; ++q) {
-    J.src[q] = e->at<cplx<double>>(e->Y) + q * sp;
+    J.src[q] = e->at<cplx<double>>(e->Y()) + q * sp;
     J.src_f32[q] = 0;
     J.dst[q] = IC + q * rf;
   }

@@ -122,25 +122,33 @@ __global__ void __launch_bounds__((E2DRowGeo<N>::THREADS), 2) k_e2d_rows(E2DPtrs
 }
 
 // ---------------------------------------------------------------------------
-// columns: group q = zeta, g~, P_x, P_y.  stage 0: K1 = R, next input Y + dt K1;
-// stage 1: Y += dt/2 (K1 + R), next input Y; stage < 0: the current state's
-// transforms only.  Blocks past the column tiles carry the semi-Lagrangian update.
+// columns: groups 0..3 = zeta, g~, P_x, P_y, group 4 = psi (from zeta's update,
+// formed again: a second forward transform costs less than a block with twice the
+// inverse ones).  stage 0: K1 = R, next input Y + dt K1; stage 1: Yn = Y + dt/2
+// (K1 + R), the next input; stage < 0: the current state's transforms only.  The
+// new state goes to a buffer of its own, so that groups 0 and 4 read the same old
+// one.  Narrow tiles: five groups alone fill the chip poorly (512^2, 8 columns per
+// block 26 us, 4 columns and psi apart 17).  Blocks before the column tiles carry
+// the semi-Lagrangian update.
 // ---------------------------------------------------------------------------
+constexpr int E2D_W = -1;  // tile width
 template <int N>
-__global__ void __launch_bounds__((col_threads<N>()), 1)
+__global__ void __launch_bounds__((col_threads<N, E2D_W>()), 1)
     k_e2d_columns(E2DPtrs P, int stage, int sl_blocks, E2DSl sl) {
   using T = double;
-  constexpr int C = col_tile<N>();
+  constexpr int C = col_tile<N, E2D_W>();
   constexpr int E = fft_E<N>(), NT = N / E, LC = col_buf(N);
   constexpr int TILES = (dims_of<N>().NKX + C - 1) / C;
-  __shared__ cplx<T> lds[col_lds<T, N, 0>()];
+  __shared__ cplx<T> lds[col_lds<T, N, E2D_W>()];
   int b = blockIdx.x;
   if (b < sl_blocks) {
-    sl_update<N>(sl, b * col_threads<N>() + (int)threadIdx.x);
+    sl_update<N>(sl, b * col_threads<N, E2D_W>() + (int)threadIdx.x);
     return;
   }
   b -= sl_blocks;
-  const int q = b / TILES;
+  const int group = b / TILES;
+  const bool psi = group == 4;
+  const int q = psi ? 0 : group;  // the state field
   constexpr Dims d = dims_of<N>();
   constexpr size_t sp = d.spec_elems(), rf = d.rowfield_elems();
   ColCtx<T, N, C> cx;
@@ -152,7 +160,8 @@ __global__ void __launch_bounds__((col_threads<N>()), 1)
   cx.kx = cx.kx0 + cx.c;
   cx.valid = cx.kx <= kcut<N>();
   cx.ky0 = (unsigned)(min(cx.kx, kcut<N>()) * d.NKY + d.K);
-  cplx<T>* Y = P.Y + q * sp;
+  const cplx<T>* Y = P.Y + q * sp;
+  cplx<T>* Yn = P.Yn + q * sp;
   cplx<T>* K1 = P.K1 + q * sp;
 
   cplx<T> S[E], k1[E], R[E];
@@ -186,18 +195,16 @@ __global__ void __launch_bounds__((col_threads<N>()), 1)
       cplx<T> v = {sg * R[r].x, sg * R[r].y};
       if (cx.kx == 0 && ix.ky() == 0) v.y = 0.0;
       if (stage == 0) {
-        put32(K1 + ix.off(), j, v);
+        if (!psi) put32(K1 + ix.off(), j, v);
         S[r] = {S[r].x + P.dt * v.x, S[r].y + P.dt * v.y};
       } else {
         S[r] = {S[r].x + 0.5 * P.dt * (k1[r].x + v.x), S[r].y + 0.5 * P.dt * (k1[r].y + v.y)};
-        put32(Y + ix.off(), j, S[r]);
+        if (!psi) put32(Yn + ix.off(), j, S[r]);
       }
     }
     if (!keep) S[r] = {0.0, 0.0};
   }
-  cplx<T>* out = P.IC + (EI_Z + 2 * q) * rf;
-  column_inverse<T, N, C, T, true>(cx, S, out, out + rf, d, P.tw);
-  if (q == 0) {
+  if (psi) {
     // psi = -zeta / |k|^2, its k = 0 mode zero
 #pragma unroll
     for (int r = 0; r < E; ++r) {
@@ -207,9 +214,9 @@ __global__ void __launch_bounds__((col_threads<N>()), 1)
       const double inv = k2 > 0.0 ? 1.0 / k2 : 0.0;
       S[r] = {-S[r].x * inv, -S[r].y * inv};
     }
-    __syncthreads();  // the tiles above have been read
-    column_inverse<T, N, C, T, true>(cx, S, P.IC + EI_PSI * rf, P.IC + EI_PSI_Y * rf, d, P.tw);
   }
+  cplx<T>* out = P.IC + (psi ? EI_PSI : EI_Z + 2 * q) * rf;
+  column_inverse<T, N, C, T, true>(cx, S, out, out + rf, d, P.tw);
 }
 
 template <int N>
@@ -219,9 +226,9 @@ void launch_e2d_rows(hipStream_t st, const E2DPtrs& P, double s, int store, int 
 }
 template <int N>
 void launch_e2d_columns(hipStream_t st, const E2DPtrs& P, int stage, const E2DSl* sl) {
-  constexpr int TH = col_threads<N>(), TILES = (dims_of<N>().NKX + col_tile<N>() - 1) / col_tile<N>();
+  constexpr int C = col_tile<N, E2D_W>(), TH = col_threads<N, E2D_W>(), TILES = (dims_of<N>().NKX + C - 1) / C;
   const int nsl = sl ? (N * N + TH - 1) / TH : 0;
-  hipLaunchKernelGGL((k_e2d_columns<N>), dim3(4 * TILES + nsl), dim3(TH), 0, st, P, stage, nsl, sl ? *sl : E2DSl{});
+  hipLaunchKernelGGL((k_e2d_columns<N>), dim3(5 * TILES + nsl), dim3(TH), 0, st, P, stage, nsl, sl ? *sl : E2DSl{});
 }
 
 }  // namespace lm

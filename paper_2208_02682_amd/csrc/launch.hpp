@@ -37,6 +37,7 @@ void launch_set_ranges(hipStream_t st, const SetRanges& R);
 constexpr int E2D_NIC = 10;  // column-pass outputs
 struct E2DPtrs {
   cplx<double>* Y;   // [4][NKX][NKY] zeta, g~, P_x, P_y
+  cplx<double>* Yn;  // the state after the step
   cplx<double>* K1;  // Heun's first slope, same shape
   cplx<double>* IC;  // [E2D_NIC][N][NKXP]
   cplx<double>* RS;  // [4][N][NKXP]
