@@ -137,9 +137,11 @@ __global__ void __launch_bounds__((col_threads<N, E2D_W>()), 1)
     k_e2d_columns(E2DPtrs P, int stage, int sl_blocks, E2DSl sl) {
   using T = double;
   constexpr int C = col_tile<N, E2D_W>();
-  constexpr int E = fft_E<N>(), NT = N / E, LC = col_buf(N);
-  constexpr int TILES = (dims_of<N>().NKX + C - 1) / C;
-  __shared__ cplx<T> lds[col_lds<T, N, E2D_W>()];
+  constexpr int E = fft_E<N>();
+  constexpr Dims d = dims_of<N>();
+  constexpr size_t sp = d.spec_elems(), rf = d.rowfield_elems();
+  constexpr int TILES = (d.NKX + C - 1) / C;
+  __shared__ __align__(16) T lds[col_lds<T, N, C>()];
   int b = blockIdx.x;
   if (b < sl_blocks) {
     sl_update<N>(sl, b * col_threads<N, E2D_W>() + (int)threadIdx.x);
@@ -149,17 +151,7 @@ __global__ void __launch_bounds__((col_threads<N, E2D_W>()), 1)
   const int group = b / TILES;
   const bool psi = group == 4;
   const int q = psi ? 0 : group;  // the state field
-  constexpr Dims d = dims_of<N>();
-  constexpr size_t sp = d.spec_elems(), rf = d.rowfield_elems();
-  ColCtx<T, N, C> cx;
-  cx.lds = lds;
-  cx.c = threadIdx.x / NT;
-  cx.t = threadIdx.x % NT;
-  cx.buf = lds + cx.c * LC;
-  cx.kx0 = (b % TILES) * C;
-  cx.kx = cx.kx0 + cx.c;
-  cx.valid = cx.kx <= kcut<N>();
-  cx.ky0 = (unsigned)(min(cx.kx, kcut<N>()) * d.NKY + d.K);
+  const ColCtx<T, N, C> cx(lds, b % TILES);
   const cplx<T>* Y = P.Y + q * sp;
   cplx<T>* Yn = P.Yn + q * sp;
   cplx<T>* K1 = P.K1 + q * sp;
@@ -180,7 +172,7 @@ __global__ void __launch_bounds__((col_threads<N, E2D_W>()), 1)
     for (int r = 0; r < E; ++r) load(r);
     sched_fence();
   }
-  if (stage >= 0) column_forward<T, N, C>(cx, P.RS + q * rf, d, P.tw, R);
+  if (stage >= 0) column_forward<T, N, C>(cx, P.RS + q * rf, nullptr, P.tw, R);
   if constexpr (!PRE) {
 #pragma unroll
     for (int r = 0; r < E; ++r) load(r);
@@ -216,7 +208,7 @@ __global__ void __launch_bounds__((col_threads<N, E2D_W>()), 1)
     }
   }
   cplx<T>* out = P.IC + (psi ? EI_PSI : EI_Z + 2 * q) * rf;
-  column_inverse<T, N, C, T, true>(cx, S, out, out + rf, d, P.tw);
+  column_inverse<T, N, C, true>(cx, S, out, out + rf, P.tw);
 }
 
 template <int N>

@@ -60,19 +60,12 @@ template <int N>
 __global__ void __launch_bounds__(col_threads<N>())
     k_io_col_forward(IoColFwd J, Dims d, const cplx<double>* tw) {
   constexpr int C = col_tile<N>();
-  constexpr int E = fft_E<N>(), NT = N / E, LC = col_buf(N);
-  __shared__ cplx<double> lds[C * LC];
-  ColCtx<double, N, C> cx;
-  cx.lds = lds;
-  cx.c = threadIdx.x / NT;
-  cx.t = threadIdx.x % NT;
-  cx.buf = lds + cx.c * LC;
-  cx.kx0 = blockIdx.x * C;
-  cx.kx = cx.kx0 + cx.c;
-  cx.valid = cx.kx <= kcut<N>();
+  constexpr int E = fft_E<N>(), NT = N / E;
+  __shared__ __align__(16) double lds[col_lds<double, N, C>()];
+  const ColCtx<double, N, C> cx(lds, blockIdx.x);
   const int q = blockIdx.y;
   cplx<double> out[E];
-  column_forward<double, N, C>(cx, J.src[q], d, tw, out);
+  column_forward<double, N, C>(cx, J.src[q], nullptr, tw, out);
   if (!cx.valid) return;
   const size_t col = (size_t)cx.kx * d.NKY;
 #pragma unroll
@@ -100,16 +93,9 @@ template <int N>
 __global__ void __launch_bounds__(col_threads<N>())
     k_io_col_inverse(IoColInv J, Dims d, const cplx<double>* tw) {
   constexpr int C = col_tile<N>();
-  constexpr int E = fft_E<N>(), NT = N / E, LC = col_buf(N);
-  __shared__ cplx<double> lds[C * LC];
-  ColCtx<double, N, C> cx;
-  cx.lds = lds;
-  cx.c = threadIdx.x / NT;
-  cx.t = threadIdx.x % NT;
-  cx.buf = lds + cx.c * LC;
-  cx.kx0 = blockIdx.x * C;
-  cx.kx = cx.kx0 + cx.c;
-  cx.valid = cx.kx <= kcut<N>();
+  constexpr int E = fft_E<N>(), NT = N / E;
+  __shared__ __align__(16) double lds[col_lds<double, N, C>()];
+  const ColCtx<double, N, C> cx(lds, blockIdx.x);
   const int q = blockIdx.y;
   const size_t col = (size_t)cx.kx * d.NKY;
   cplx<double> S[E];
@@ -134,7 +120,7 @@ __global__ void __launch_bounds__(col_threads<N>())
       S[r] = reinterpret_cast<const cplx<double>*>(J.src[q])[j];
     }
   }
-  column_inverse<double, N, C, double, false>(cx, S, J.dst[q], nullptr, d, tw);
+  column_inverse<double, N, C, false>(cx, S, J.dst[q], nullptr, tw);
 }
 
 }  // namespace lm

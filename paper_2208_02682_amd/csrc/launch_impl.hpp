@@ -48,23 +48,60 @@ void with_tile(int tile, F&& go) {
   go(std::integral_constant<int, 0>{});
 }
 
-// the column groups in slots [first, first + count) of one stage, on stream st
-// (the stage-value buffers are flipped by the caller once per stage)
-template <typename T, int N>
-void launch_columns_part(RunView& r, int stage, int first, int count, hipStream_t st) {
-  const StepPtrs<T> P = step_ptrs<T>(r);
+// which column groups a launch carries: slots [first, first + count) of one stage
+// (stage < 0: the prologue), ys the stage-value buffer that holds their stage's
+// input (the buffers are flipped by the caller once per stage)
+struct ColPart {
+  int stage = 0, first = 0, count = 0, ys = 0;
+};
+
+template <typename T>
+ColArgs<T> col_args(RunView& r, const ColPart& c, int tiles) {
   cplx<T>* Ys[2] = {(cplx<T>*)r.at(r.L.Ys0), (cplx<T>*)r.at(r.L.Ys1)};
-  const cplx<T>* Ys_in = Ys[r.ys_cur];
-  cplx<T>* Ys_out = (stage < 0) ? Ys[r.ys_cur] : Ys[r.ys_cur ^ 1];
+  const int stage = c.stage;
+  ColArgs<T> a;
+  a.stage = stage;
+  a.slot0 = c.first;
+  a.nslot = c.count > 0 ? c.count : 1;
+  a.cols = (c.count * tiles + 7) / 8 * 8;
   // time of the stage input this launch prepares: the current one in the
   // prologue, else the next stage's (c = 1/2, 1/2, 1, then the next step's 0)
-  const double t_next = (double(r.n) + (stage < 0 ? 0.0 : (stage <= 1 ? 0.5 : 1.0))) * r.ph.dt;
+  a.t_next = (double(r.n) + (stage < 0 ? 0.0 : (stage <= 1 ? 0.5 : 1.0))) * r.ph.dt;
+  a.Ys_in = Ys[c.ys];
+  a.Ys_out = (stage < 0) ? Ys[c.ys] : Ys[c.ys ^ 1];
+  return a;
+}
+
+// one merged launch (small grids): A, dynamics and strategy-1 rows, or B, strategy-2
+// rows, at time s since the interval start (rows set), and column groups
+template <typename T, int N, bool B>
+void launch_merged(RunView& r, bool rows, double s, const ColPart& c, hipStream_t st) {
+  const StepPtrs<T> P = step_ptrs<T>(r);
   with_tile<T, N>(r.sched.tile, [&](auto w) {
     constexpr int W = decltype(w)::value;
-    const dim3 g = col_grid<N, W>(r.d, count), b = col_block<N, W>();
-    hipLaunchKernelGGL((k_columns<T, N, W>), g, b, 0, st, P, r.ph, stage, t_next, Ys_in, Ys_out,
-                       r.sched.remap, first);
+    using S = typename std::conditional<B, StageB<T, N, W>, StageA<T, N, W>>::type;
+    const ColArgs<T> a = col_args<T>(r, c, S::TILES);
+    const int nr = rows ? S::ROWS : 0;
+    const dim3 g(a.cols + nr), b(S::THREADS);
+    if constexpr (B) hipLaunchKernelGGL((k_stage_b<T, N, W>), g, b, 0, st, P, r.ph, s, a, nr, r.sched.remap);
+    else hipLaunchKernelGGL((k_stage_a<T, N, W>), g, b, 0, st, P, r.ph, s, a, nr, r.sched.remap);
   });
+}
+
+// column groups alone
+template <typename T, int N>
+void launch_columns_part(RunView& r, int stage, int first, int count, hipStream_t st) {
+  const ColPart c{stage, first, count, r.ys_cur};
+  if constexpr (stage_merged<T, N>()) {
+    launch_merged<T, N, true>(r, false, 0.0, c, st);
+  } else {
+    const StepPtrs<T> P = step_ptrs<T>(r);
+    with_tile<T, N>(r.sched.tile, [&](auto w) {
+      constexpr int W = decltype(w)::value;
+      const dim3 g = col_grid<N, W>(r.d, count), b(col_threads<N, W>());
+      hipLaunchKernelGGL((k_columns<T, N, W>), g, b, 0, st, P, r.ph, col_args<T>(r, c, g.x), r.sched.remap);
+    });
+  }
 }
 
 template <typename T, int N>
@@ -73,25 +110,39 @@ void launch_columns_t(RunView& r, int stage) {
   if (stage >= 0) r.ys_cur ^= 1;
 }
 
-// the rows pass of the dynamics and strategy 1
+// the rows pass of the dynamics and strategy 1 alone
 template <typename T, int N>
-void launch_rows_dyn(RunView& r, const StepPtrs<T>& P, double sval, hipStream_t st) {
+void launch_rows_dyn(RunView& r, double sval, hipStream_t st) {
   const dim3 g = coop_grid<T, N>(), b(DynGeo<T, N>::THREADS);
-  const int rm = r.sched.remap;
-  if (r.ph.gen) hipLaunchKernelGGL((k_rows_dyn<T, N, true>), g, b, 0, st, P, r.ph, sval, rm);
-  else hipLaunchKernelGGL((k_rows_dyn<T, N, false>), g, b, 0, st, P, r.ph, sval, rm);
+  if (r.ph.gen) {
+    hipLaunchKernelGGL((k_rows_dyn<T, N, true>), g, b, 0, st, step_ptrs<T>(r), r.ph, sval, r.sched.remap);
+  } else if constexpr (stage_merged<T, N>()) {
+    launch_merged<T, N, false>(r, true, sval, ColPart{}, st);
+  } else {
+    hipLaunchKernelGGL((k_rows_dyn<T, N, false>), g, b, 0, st, step_ptrs<T>(r), r.ph, sval, r.sched.remap);
+  }
 }
 
-// the rows pass of strategy 2, and the momentum rows when requested
+// the momentum rows, when requested
 template <typename T, int N>
-void launch_rows_rhs(RunView& r, const StepPtrs<T>& P, double sval) {
-  const dim3 g = coop_grid<T, N>(), b(RhsGeo<T, N>::THREADS), bm(MomGeo<T, N>::THREADS);
-  const int rm = r.sched.remap;
-  if (r.cubic) hipLaunchKernelGGL((k_rows_rhs<T, N, true>), g, b, 0, r.stream, P, sval, rm);
-  else hipLaunchKernelGGL((k_rows_rhs<T, N, false>), g, b, 0, r.stream, P, sval, rm);
-  if (r.mom) {
-    if (r.cubic) hipLaunchKernelGGL((k_rows_mom<T, N, true>), g, bm, 0, r.stream, P, sval, rm);
-    else hipLaunchKernelGGL((k_rows_mom<T, N, false>), g, bm, 0, r.stream, P, sval, rm);
+void launch_rows_mom(RunView& r, double sval) {
+  if (!r.mom) return;
+  const StepPtrs<T> P = step_ptrs<T>(r);
+  const dim3 g = coop_grid<T, N>(), b(MomGeo<T, N>::THREADS);
+  if (r.cubic) hipLaunchKernelGGL((k_rows_mom<T, N, true>), g, b, 0, r.stream, P, sval, r.sched.remap);
+  else hipLaunchKernelGGL((k_rows_mom<T, N, false>), g, b, 0, r.stream, P, sval, r.sched.remap);
+}
+
+// the rows pass of strategy 2 alone
+template <typename T, int N>
+void launch_rows_rhs(RunView& r, double sval) {
+  const dim3 g = coop_grid<T, N>(), b(RhsGeo<T, N>::THREADS);
+  if (r.cubic) {
+    hipLaunchKernelGGL((k_rows_rhs<T, N, true>), g, b, 0, r.stream, step_ptrs<T>(r), sval, r.sched.remap);
+  } else if constexpr (stage_merged<T, N>()) {
+    launch_merged<T, N, true>(r, true, sval, ColPart{}, r.stream);
+  } else {
+    hipLaunchKernelGGL((k_rows_rhs<T, N, false>), g, b, 0, r.stream, step_ptrs<T>(r), sval, r.sched.remap);
   }
 }
 
@@ -109,9 +160,8 @@ void launch_rows_rhs(RunView& r, const StepPtrs<T>& P, double sval) {
 // groups.  Same kernels, same arguments, same results as the one-stream form.
 template <typename T, int N>
 hipError_t launch_steps_2s(RunView& r, int nsteps) {
-  const StepPtrs<T> P = step_ptrs<T>(r);
   static const double c[4] = {0.0, 0.5, 0.5, 1.0};
-  const int nd = col_dyn_groups(r.ph), nm = col_mean_groups(r.ph);
+  const int nd = col_dyn_groups(r.ph), nm = col_groups(r.ph) - nd;
   hipEvent_t fork = r.ev[0], dyn = r.ev[1], rhs = r.ev[2], join = r.ev[3];
   hipError_t e = hipEventRecord(fork, r.stream);  // aux starts after everything queued so far
   if (e == hipSuccess) e = hipStreamWaitEvent(r.aux, fork, 0);
@@ -123,12 +173,13 @@ hipError_t launch_steps_2s(RunView& r, int nsteps) {
       // next dynamics groups overwrite
       if (s + stage > 0) e = hipStreamWaitEvent(r.aux, rhs, 0);
       if (e != hipSuccess) break;
-      launch_rows_dyn<T, N>(r, P, sval, r.aux);
+      launch_rows_dyn<T, N>(r, sval, r.aux);
       e = hipEventRecord(dyn, r.aux);
       launch_columns_part<T, N>(r, stage, 0, nd, r.aux);
       if (e == hipSuccess) e = hipStreamWaitEvent(r.stream, dyn, 0);
       if (e != hipSuccess) break;
-      launch_rows_rhs<T, N>(r, P, sval);  // on the run's stream
+      launch_rows_rhs<T, N>(r, sval);  // on the run's stream
+      launch_rows_mom<T, N>(r, sval);
       launch_columns_part<T, N>(r, stage, nd, nm, r.stream);
       e = hipEventRecord(rhs, r.stream);
       r.ys_cur ^= 1;
@@ -141,33 +192,52 @@ hipError_t launch_steps_2s(RunView& r, int nsteps) {
   return e != hipSuccess ? e : e3;
 }
 
+// One stream.  Small grids: launches A and B of every stage (k_stage_a, k_stage_b),
+// the strategy-2 column groups of the last stage at the end; the rows of other
+// averaged fields than (h, zeta) and of cubic gathers are kernels of their own, and
+// such runs take the passes one by one, as large grids do.
 template <typename T, int N>
 void launch_steps_t(RunView& r, int nsteps) {
-  const StepPtrs<T> P = step_ptrs<T>(r);
   static const double c[4] = {0.0, 0.5, 0.5, 1.0};
   if (r.sched.streams == 2 && r.aux && nsteps > 0) {
     (void)launch_steps_2s<T, N>(r, nsteps);  // launch errors surface through hipGetLastError
     return;
   }
-  for (int s = 0; s < nsteps; ++s) {
+  const int n1 = col_first_groups(r.ph), n2 = col_second_groups(r.ph);
+  const bool merged = stage_merged<T, N>() && !r.ph.gen && !r.cubic;
+  ColPart second;  // the strategy-2 column groups still to be launched
+  for (int st = 0; st < nsteps; ++st) {
     for (int stage = 0; stage < 4; ++stage) {
       // time since the interval start, from integers
       const double sval = (double(r.n - r.n_tau) + c[stage]) * r.ph.dt;
-      launch_rows_dyn<T, N>(r, P, sval, r.stream);
-      launch_rows_rhs<T, N>(r, P, sval);
+      if constexpr (stage_merged<T, N>()) {
+        if (merged) {
+          launch_merged<T, N, false>(r, true, sval, second, r.stream);
+          launch_merged<T, N, true>(r, true, sval, ColPart{stage, 0, n1, r.ys_cur}, r.stream);
+          launch_rows_mom<T, N>(r, sval);
+          second = ColPart{stage, n1, n2, r.ys_cur};
+          r.ys_cur ^= 1;
+          continue;
+        }
+      }
+      launch_rows_dyn<T, N>(r, sval, r.stream);
+      launch_rows_rhs<T, N>(r, sval);
+      launch_rows_mom<T, N>(r, sval);
       launch_columns_t<T, N>(r, stage);
     }
     r.n += 1;
   }
+  if constexpr (stage_merged<T, N>()) {
+    if (second.count) launch_merged<T, N, true>(r, false, 0.0, second, r.stream);
+  }
 }
 
-// Same launches as launch_steps_t, each bracketed by a pair of events on the
-// run's stream; nothing synchronises until all steps are enqueued, so the
-// kernels run back to back as in launch_steps_t.  The three kernel durations
-// are accumulated into ms[0..2].
+// The passes of launch_steps_t one by one (rows of the dynamics and strategy 1,
+// rows of strategy 2, columns), each bracketed by a pair of events on the run's
+// stream; nothing synchronises until all steps are enqueued, so the kernels run
+// back to back.  The three durations are accumulated into ms[0..2].
 template <typename T, int N>
 hipError_t launch_steps_profiled_t(RunView& r, int nsteps, double* ms) {
-  const StepPtrs<T> P = step_ptrs<T>(r);
   static const double c[4] = {0.0, 0.5, 0.5, 1.0};
   const int nev = nsteps * 4 * 3 * 2;
   std::vector<hipEvent_t> ev(nev);
@@ -187,11 +257,12 @@ hipError_t launch_steps_profiled_t(RunView& r, int nsteps, double* ms) {
       // start marker absorbs the work done at kernel boundaries, so each
       // interval covers one kernel's execution only
       (void)hipEventRecord(ev[e++], r.stream);
-      launch_rows_dyn<T, N>(r, P, sval, r.stream);
+      launch_rows_dyn<T, N>(r, sval, r.stream);
       (void)hipEventRecord(ev[e++], r.stream);
       hipLaunchKernelGGL(k_drain<N>, dim3(1), dim3(64), 0, r.stream);
       (void)hipEventRecord(ev[e++], r.stream);
-      launch_rows_rhs<T, N>(r, P, sval);
+      launch_rows_rhs<T, N>(r, sval);
+      launch_rows_mom<T, N>(r, sval);
       (void)hipEventRecord(ev[e++], r.stream);
       hipLaunchKernelGGL(k_drain<N>, dim3(1), dim3(64), 0, r.stream);
       (void)hipEventRecord(ev[e++], r.stream);
@@ -217,38 +288,66 @@ hipError_t launch_steps_profiled(RunView& r, int nsteps, double* ms) {
   return launch_steps_profiled_t<double, N>(r, nsteps, ms);
 }
 
-// one RK4 step of every run of one (N, precision) group: blockIdx.z selects
-// the run's descriptor
+// one RK4 step of every run of one (N, precision) group, the launches of
+// launch_steps_t with all runs' blocks in each
 template <typename T, int N>
 void launch_batch_step_t(hipStream_t st, const RunDesc<T>* desc, int nruns, bool cubic, bool mom, bool gen,
                          const Sched& sc) {
-  const Dims d = Dims::make(N);
   Phys gp{};
   gp.mom = mom;
   gp.gen = gen;
-  const int ncg = col_groups(gp);  // column groups per run
   const int rm = sc.remap;
-  for (int stage = 0; stage < 4; ++stage) {
-    dim3 g1 = coop_grid<T, N>();
-    g1.z = nruns;
-    const dim3 b1(DynGeo<T, N>::THREADS);
-    if (gen) hipLaunchKernelGGL((k_rows_dyn_b<T, N, true>), g1, b1, 0, st, desc, stage, rm);
-    else hipLaunchKernelGGL((k_rows_dyn_b<T, N, false>), g1, b1, 0, st, desc, stage, rm);
-    const dim3 b2(RhsGeo<T, N>::THREADS), bm(MomGeo<T, N>::THREADS);
-    if (cubic) hipLaunchKernelGGL((k_rows_rhs_b<T, N, true>), g1, b2, 0, st, desc, stage, rm);
-    else hipLaunchKernelGGL((k_rows_rhs_b<T, N, false>), g1, b2, 0, st, desc, stage, rm);
-    if (mom) {
-      if (cubic) hipLaunchKernelGGL((k_rows_mom_b<T, N, true>), g1, bm, 0, st, desc, stage, rm);
-      else hipLaunchKernelGGL((k_rows_mom_b<T, N, false>), g1, bm, 0, st, desc, stage, rm);
+  dim3 gr = coop_grid<T, N>();  // one pass per launch: blockIdx.z selects the run
+  gr.z = nruns;
+  const dim3 b1(DynGeo<T, N>::THREADS), b2(RhsGeo<T, N>::THREADS), bm(MomGeo<T, N>::THREADS);
+  auto launch_mom = [&](int stage) {
+    if (!mom) return;
+    if (cubic) hipLaunchKernelGGL((k_rows_mom_b<T, N, true>), gr, bm, 0, st, desc, stage, rm);
+    else hipLaunchKernelGGL((k_rows_mom_b<T, N, false>), gr, bm, 0, st, desc, stage, rm);
+  };
+  with_tile<T, N>(sc.tile, [&](auto w) {
+    constexpr int W = decltype(w)::value;
+    if constexpr (stage_merged<T, N>()) {
+      using A = StageA<T, N, W>;
+      using B = StageB<T, N, W>;
+      const int n1 = col_first_groups(gp), n2 = col_second_groups(gp);
+      auto launch_ab = [&](bool b, bool rows, int stage, int cstage, int first, int count) {
+        const int nc = (count * A::TILES * nruns + 7) / 8 * 8, nr = rows ? A::ROWS * nruns : 0, ns = count > 0 ? count : 1;
+        if (b) hipLaunchKernelGGL((k_stage_b_b<T, N, W>), dim3(nc + nr), dim3(B::THREADS), 0, st, desc, nruns, stage,
+                                  cstage, first, ns, nc, nr, rm);
+        else hipLaunchKernelGGL((k_stage_a_b<T, N, W>), dim3(nc + nr), dim3(A::THREADS), 0, st, desc, nruns, stage,
+                                cstage, first, ns, nc, nr, rm);
+      };
+      if (!gen && !cubic) {
+        for (int stage = 0; stage < 4; ++stage) {
+          launch_ab(false, true, stage, stage - 1, n1, stage > 0 ? n2 : 0);
+          launch_ab(true, true, stage, stage, 0, n1);
+          launch_mom(stage);
+        }
+        launch_ab(true, false, 0, 3, n1, n2);
+        return;
+      }
+      for (int stage = 0; stage < 4; ++stage) {
+        if (gen) hipLaunchKernelGGL((k_rows_dyn_b<T, N, true>), gr, b1, 0, st, desc, stage, rm);
+        else launch_ab(false, true, stage, 0, 0, 0);
+        if (cubic) hipLaunchKernelGGL((k_rows_rhs_b<T, N, true>), gr, b2, 0, st, desc, stage, rm);
+        else launch_ab(true, true, stage, 0, 0, 0);
+        launch_mom(stage);
+        launch_ab(true, false, 0, stage, 0, n1 + n2);
+      }
+    } else {
+      for (int stage = 0; stage < 4; ++stage) {
+        if (gen) hipLaunchKernelGGL((k_rows_dyn_b<T, N, true>), gr, b1, 0, st, desc, stage, rm);
+        else hipLaunchKernelGGL((k_rows_dyn_b<T, N, false>), gr, b1, 0, st, desc, stage, rm);
+        if (cubic) hipLaunchKernelGGL((k_rows_rhs_b<T, N, true>), gr, b2, 0, st, desc, stage, rm);
+        else hipLaunchKernelGGL((k_rows_rhs_b<T, N, false>), gr, b2, 0, st, desc, stage, rm);
+        launch_mom(stage);
+        dim3 g3 = col_grid<N, W>(Dims::make(N), col_groups(gp));
+        g3.z = nruns;
+        hipLaunchKernelGGL((k_columns_b<T, N, W>), g3, dim3(col_threads<N, W>()), 0, st, desc, stage, rm);
+      }
     }
-    with_tile<T, N>(sc.tile, [&](auto w) {
-      constexpr int W = decltype(w)::value;
-      dim3 g3 = col_grid<N, W>(d, ncg);
-      g3.z = nruns;
-      const dim3 b3 = col_block<N, W>();
-      hipLaunchKernelGGL((k_columns_b<T, N, W>), g3, b3, 0, st, desc, stage, rm);
-    });
-  }
+  });
 }
 
 template <int N>

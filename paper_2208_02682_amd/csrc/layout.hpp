@@ -94,19 +94,20 @@ struct Phys {
   double kx, ky, A, omega, phase, U0, V0;  // kinematic: h' = A cos(kx x + ky y - omega t + phase)
 };
 
-// Column groups launched for a run, in slot order: first the groups that need
-// only the dynamics rows pass (u, v, h, and the Eulerian groups of fields other
-// than (h, zeta)), then those that need the mean right-hand-side rows pass (xi,
-// g-bar, g-tilde, P, and the momentum 1-form).  A launch covers a range of slots.
+// Column groups launched for a run, in slot order: first those that need only the
+// dynamics rows pass (u, v, h, the Eulerian groups of fields other than (h, zeta),
+// and strategy 1), then those that need strategy 2's rows (xi, g-bar, and the
+// momentum 1-form).  A launch covers a range of slots.
 __host__ __device__ inline int col_dyn_groups(const Phys& ph) { return 3 + (ph.gen ? 2 : 0); }
-__host__ __device__ inline int col_mean_groups(const Phys& ph) { return 8 + (ph.mom ? 2 : 0); }
-__host__ __device__ inline int col_groups(const Phys& ph) { return col_dyn_groups(ph) + col_mean_groups(ph); }
+__host__ __device__ inline int col_first_groups(const Phys& ph) { return col_dyn_groups(ph) + 4; }
+__host__ __device__ inline int col_second_groups(const Phys& ph) { return 4 + (ph.mom ? 2 : 0); }
+__host__ __device__ inline int col_groups(const Phys& ph) { return col_first_groups(ph) + col_second_groups(ph); }
 __host__ __device__ inline int col_group_of(const Phys& ph, int slot) {
   if (slot < 3) return CG_U + slot;
   const int nd = col_dyn_groups(ph);
   if (slot < nd) return CG_EF0 + (slot - 3);
   const int j = slot - nd;
-  return (j < 8) ? CG_XIX + j : CG_GMX + (j - 8);
+  return (j < 4) ? CG_GTH + j : (j < 8) ? CG_XIX + (j - 4) : CG_GMX + (j - 8);
 }
 
 }  // namespace lm

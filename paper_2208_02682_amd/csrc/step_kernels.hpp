@@ -943,9 +943,6 @@ __global__ void __launch_bounds__((MomGeo<T, N>::THREADS), (MomGeo<T, N>::min_wa
 // columns
 // --------------------------------------------------------------------------
 
-template <typename TS>
-__device__ __forceinline__ cplx<TS> cadd(cplx<TS> a, cplx<TS> b) { return {a.x + b.x, a.y + b.y}; }
-
 // (hi, lo) + d for a float value carried as two words: Knuth's two-sum of hi
 // and d gives the sum and its exact rounding error, which is folded into lo
 // before the pair is renormalised (|lo| <= half an ulp of hi).  Contraction to
@@ -970,16 +967,18 @@ __device__ __forceinline__ void comp_add(float& hi, float& lo, float d) {
 // rounding of the state at every step no longer accumulates over a long run.
 // Stage inputs, right-hand sides and the accumulator stay float (their rounding
 // enters once per step, scaled by dt).  Float64 state ignores lo.
-template <typename TS>
-__device__ __forceinline__ cplx<TS> rk4v(int stage, cplx<TS>& y, cplx<TS>& lo, cplx<TS>& a, cplx<TS> k,
-                                         double dt) {
-  if (stage == 0) {
+// K: the stage's kind, fixed at compile time (a uniform branch around whole
+// batches instead of one per coefficient): 0 the first stage, 1 the two middle
+// ones, whose coefficient cn is dt/2 or dt, 3 the last.
+template <int K, typename TS>
+__device__ __forceinline__ cplx<TS> rk4v(cplx<TS>& y, cplx<TS>& lo, cplx<TS>& a, cplx<TS> k, double dt, double cn) {
+  if constexpr (K == 0) {
     a = k;
     const TS c = TS(0.5 * dt);
     return {y.x + c * k.x, y.y + c * k.y};
-  } else if (stage == 1 || stage == 2) {
+  } else if constexpr (K == 1) {
     a = {a.x + TS(2) * k.x, a.y + TS(2) * k.y};
-    const TS c = TS(stage == 1 ? 0.5 * dt : dt);
+    const TS c = TS(cn);
     return {y.x + c * k.x, y.y + c * k.y};
   } else {
     const TS c = TS(dt / 6.0);
@@ -995,19 +994,17 @@ __device__ __forceinline__ cplx<TS> rk4v(int stage, cplx<TS>& y, cplx<TS>& lo, c
 
 // the words rk4v reads (y always, a from stage 1, lo at stage 3 for float) and
 // writes back (a at stages 0-2, y and lo at stage 3)
-template <typename TS>
-__device__ __forceinline__ void rk4_load(int stage, const cplx<TS>* Yp, const cplx<TS>* Lp, const cplx<TS>* Ap,
-                                         unsigned j, cplx<TS>& y, cplx<TS>& lo, cplx<TS>& a) {
+template <int K, typename TS>
+__device__ __forceinline__ void rk4_load(const cplx<TS>* Yp, const cplx<TS>* Lp, const cplx<TS>* Ap, unsigned j,
+                                         cplx<TS>& y, cplx<TS>& lo, cplx<TS>& a) {
   y = at32(Yp, j);
-  if (stage >= 1) a = at32(Ap, j);
-  if constexpr (std::is_same<TS, float>::value) {
-    if (stage == 3) lo = at32(Lp, j);
-  }
+  if constexpr (K >= 1) a = at32(Ap, j);
+  if constexpr (K == 3 && std::is_same<TS, float>::value) lo = at32(Lp, j);
 }
-template <typename TS>
-__device__ __forceinline__ void rk4_store(int stage, cplx<TS>* Yp, cplx<TS>* Lp, cplx<TS>* Ap, unsigned j,
-                                          const cplx<TS>& y, const cplx<TS>& lo, const cplx<TS>& a) {
-  if (stage <= 2) {
+template <int K, typename TS>
+__device__ __forceinline__ void rk4_store(cplx<TS>* Yp, cplx<TS>* Lp, cplx<TS>* Ap, unsigned j, const cplx<TS>& y,
+                                          const cplx<TS>& lo, const cplx<TS>& a) {
+  if constexpr (K < 3) {
     put32(Ap, j, a);
   } else {
     put32(Yp, j, y);
@@ -1017,12 +1014,23 @@ __device__ __forceinline__ void rk4_store(int stage, cplx<TS>* Yp, cplx<TS>* Lp,
 
 template <typename T, int N, int C>
 struct ColCtx {
-  static constexpr int E = fft_E<N>(), NT = N / E, LC = col_buf(N);
-  cplx<T>* lds;     // C buffers of LC
-  cplx<T>* buf;     // this group's buffer
+  static constexpr int E = fft_E<N>(), NT = N / E;
+  static constexpr int CS = 2 * col_buf(N);  // a column's buffer, in values of T
+  T* lds;           // C buffers
+  T* buf;           // this lane group's buffer
   int c, t, kx0, kx;
   bool valid;       // kx <= K
   unsigned ky0;     // index of ky = 0 in the column's state (columns past K: of column K)
+  __device__ __forceinline__ ColCtx(T* l, int tile) : lds(l) {
+    constexpr Dims d = dims_of<N>();
+    c = threadIdx.x / NT;
+    t = threadIdx.x % NT;
+    buf = lds + c * CS;
+    kx0 = tile * C;
+    kx = kx0 + c;
+    valid = kx <= kcut<N>();
+    ky0 = (unsigned)(min(kx, kcut<N>()) * d.NKY + d.K);
+  }
 };
 
 // Coefficient ky that entry k = t + NT r of a column transform stands for:
@@ -1055,131 +1063,87 @@ __device__ __forceinline__ cplx<T> buffer_cplx(__amdgpu_buffer_rsrc_t rs, unsign
   else return __builtin_bit_cast(cplx<T>, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, 0));
 }
 
-// block-wide: rows of a [N][NKXP] field (columns kx0..kx0+C-1) into the C buffers.
-// A thread keeps one column c and visits rows y = threadIdx.x / C + NT k.  The
-// field is read as one buffer resource: the thread's offset sits in one vector
-// register and the row step of each of its E loads in a scalar register, so all
-// E loads are in flight at once for the price of their data registers (global
-// loads would need an address register pair each).  Columns past K read the
-// row's padding and are replaced by zeros.
-template <typename T, int N, int C>
-__device__ __forceinline__ void tile_load(const ColCtx<T, N, C>& cx, const cplx<T>* __restrict__ src,
-                                          const Dims& d) {
-  constexpr int LC = ColCtx<T, N, C>::LC, E = fft_E<N>(), NT = N / E;
+// block-wide: columns kx0..kx0+C-1 of a [N][NKXP] field A, or of A - i kx B, into
+// lane registers, v[r] = row t + NT r of the lane group's column.  A thread loads
+// one column c at rows y = threadIdx.x / C + NT k; the tile is transposed in LDS.
+// A field is read as one buffer resource: the thread's offset sits in one vector
+// register and the row step of each of its E loads in a scalar register, so all E
+// loads are in flight at once for the price of their data registers.  (A column's
+// kx is fixed, so the x derivative of B joins A before the one transform.)
+// Columns past K read the row's padding and are replaced by zeros.
+template <typename T, int N, int C, bool DX>
+__device__ __forceinline__ void tile_load(const ColCtx<T, N, C>& cx, const cplx<T>* __restrict__ A,
+                                          const cplx<T>* __restrict__ B, cplx<T> (&v)[fft_E<N>()]) {
+  using X = ColCtx<T, N, C>;
+  constexpr int E = X::E, NT = X::NT;
+  constexpr Dims d = dims_of<N>();
+  constexpr int bytes = (int)(d.rowfield_elems() * sizeof(cplx<T>));
   const int c = threadIdx.x % C, y0 = threadIdx.x / C;
   const bool in = cx.kx0 + c <= kcut<N>();
-  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<cplx<T>*>(src), (short)0, (int)(d.rowfield_elems() * sizeof(cplx<T>)), 0x00020000);
+  const __amdgpu_buffer_rsrc_t ra =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<cplx<T>*>(A), (short)0, bytes, 0x00020000);
   const unsigned voff = ((unsigned)y0 * (unsigned)d.NKXP + (unsigned)(cx.kx0 + c)) * (unsigned)sizeof(cplx<T>);
-  const unsigned dy = (unsigned)NT * (unsigned)d.NKXP * (unsigned)sizeof(cplx<T>);
-  cplx<T>* dstl = cx.lds + c * LC;
-  __syncthreads();
+  constexpr unsigned dy = (unsigned)NT * (unsigned)d.NKXP * (unsigned)sizeof(cplx<T>);
   cplx<T> val[E];
 #pragma unroll
-  for (int k = 0; k < E; ++k) val[k] = buffer_cplx<T>(rs, voff, (unsigned)k * dy);
+  for (int k = 0; k < E; ++k) val[k] = buffer_cplx<T>(ra, voff, (unsigned)k * dy);
+  if constexpr (DX) {
+    const __amdgpu_buffer_rsrc_t rb =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<cplx<T>*>(B), (short)0, bytes, 0x00020000);
+    const T kx = T(cx.kx0 + c);
 #pragma unroll
-  for (int k = 0; k < E; ++k) dstl[pidx(LaneIdx{y0, NT * k})] = in ? val[k] : cplx<T>{T(0), T(0)};
+    for (int k = 0; k < E; ++k) {
+      const cplx<T> b = buffer_cplx<T>(rb, voff, (unsigned)k * dy);
+      val[k] = {val[k].x + kx * b.y, val[k].y - kx * b.x};
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < E; ++k) val[k] = in ? val[k] : cplx<T>{T(0), T(0)};
+  T* col = cx.lds + c * X::CS;
+  __syncthreads();  // the buffers' earlier contents have been read
+#pragma unroll
+  for (int k = 0; k < E; ++k) reinterpret_cast<cplx<T>*>(col)[pidx(LaneIdx{y0, NT * k})] = val[k];
   __syncthreads();
+#pragma unroll
+  for (int r = 0; r < E; ++r) v[r] = reinterpret_cast<const cplx<T>*>(cx.buf)[pidx(LaneIdx{cx.t, NT * r})];
+  xsync<NT>();
 }
 
-// block-wide: the C buffers at lds to rows of a [N][NKXP] field (columns kx0..),
-// between barriers of the caller.  The block is C * N / E threads, a compile-time
-// count, so the loop unrolls and all of a thread's LDS reads are issued before
-// its stores.
+// block-wide: the C buffers at lds (entries in natural order) to columns
+// kx0.. of a [N][NKXP] field, after a barrier of the caller.  The block is C * N /
+// E threads, a compile-time count, so the loop unrolls and all of a thread's LDS
+// reads are issued before its stores.
 template <typename T, int N, int C>
-__device__ __forceinline__ void tile_store(const ColCtx<T, N, C>& cx, const cplx<T>* lds, cplx<T>* __restrict__ dst,
-                                           const Dims& d) {
-  constexpr int LC = ColCtx<T, N, C>::LC;
-  constexpr int NTH = C * (N / fft_E<N>());
-  static_assert((N * C) % NTH == 0 && NTH % C == 0, "tile store rounds");
+__device__ __forceinline__ void tile_store(const ColCtx<T, N, C>& cx, const T* lds, cplx<T>* __restrict__ dst) {
+  using X = ColCtx<T, N, C>;
+  constexpr Dims d = dims_of<N>();
   const int c = (int)threadIdx.x % C, y0 = (int)threadIdx.x / C;
   const unsigned at = (unsigned)(y0 * d.NKXP + cx.kx0 + c);
   if (cx.kx0 + c <= kcut<N>()) {
+    const cplx<T>* col = reinterpret_cast<const cplx<T>*>(lds + c * X::CS);
 #pragma unroll
-    for (int k = 0; k < N * C / NTH; ++k)
-      put32(dst + (size_t)(NTH / C) * k * d.NKXP, at, lds[c * LC + pidx(LaneIdx{y0, (NTH / C) * k})]);
+    for (int k = 0; k < X::E; ++k)
+      put32(dst + (size_t)X::NT * k * d.NKXP, at, col[pidx(LaneIdx{y0, X::NT * k})]);
   }
 }
 
-// forward column transform of one row-spectrum field; the spectrum is left in
-// the wave's buffer (natural order), unnormalised
-template <typename T, int N, int C>
-__device__ __forceinline__ void column_forward_lds(const ColCtx<T, N, C>& cx, const cplx<T>* src, const Dims& d,
-                                                   const cplx<T>* __restrict__ tw) {
-  constexpr int E = fft_E<N>(), NT = N / E;
-  tile_load<T, N, C>(cx, src, d);
-  cplx<T> v[E];
-#pragma unroll
-  for (int r = 0; r < E; ++r) v[r] = cx.buf[pidx(LaneIdx{cx.t, NT * r})];
-  xsync<NT>();
-  fft<T, N, fft_E<N>(), -1>(v, reinterpret_cast<T*>(cx.buf), cx.t, tw);
-}
-
-// the masked, 1/N^2-normalised right-hand-side value at k = t + NT r from the
-// spectrum column_forward_lds left in the buffer
-template <typename T, int N, int C>
-__device__ __forceinline__ cplx<T> column_value(const ColCtx<T, N, C>& cx, int r) {
-  constexpr int NT = N / fft_E<N>();
-  const T inv = T(1.0 / (double(N) * double(N)));
-  const cplx<T> q = cx.buf[pidx(LaneIdx{cx.t, NT * r})];
-  return {q.x * inv, q.y * inv};
-}
-
-// forward transform of v, masked, 1/N^2-normalised values at k = t + NT r in v.
-// With 16 values per lane they come back through the buffer: kept in registers
-// across the last stage, the float kernels spill under their 128 registers.
-template <typename T, int N, int C>
-__device__ __forceinline__ void column_fft_out(const ColCtx<T, N, C>& cx, cplx<T> (&v)[fft_E<N>()],
-                                               const cplx<T>* __restrict__ tw) {
-  constexpr int E = fft_E<N>();
-  fft<T, N, E, -1, (E < 16)>(v, reinterpret_cast<T*>(cx.buf), cx.t, tw);
-  if constexpr (E < 16) {
-    const T inv = T(1.0 / (double(N) * double(N)));
-#pragma unroll
-    for (int r = 0; r < E; ++r) v[r] = {v[r].x * inv, v[r].y * inv};
-  } else {
-#pragma unroll
-    for (int r = 0; r < E; ++r) v[r] = column_value<T, N, C>(cx, r);
-  }
-}
-
-// forward column transform of A - i kx B for two row-spectrum fields: a
-// column's kx is fixed, so the x-derivative of B joins A before one transform
-// (the transform is linear).  Returns the masked, 1/N^2-normalised values at
-// k = t + NT r.
-template <typename T, int N, int C>
-__device__ __forceinline__ void column_forward_dx(const ColCtx<T, N, C>& cx, const cplx<T>* srcA,
-                                                  const cplx<T>* srcB, const Dims& d,
-                                                  const cplx<T>* __restrict__ tw, cplx<T> (&out)[fft_E<N>()]) {
-  constexpr int E = fft_E<N>(), NT = N / E;
-  tile_load<T, N, C>(cx, srcA, d);
-  cplx<T> v[E];
-#pragma unroll
-  for (int r = 0; r < E; ++r) v[r] = cx.buf[pidx(LaneIdx{cx.t, NT * r})];
-  tile_load<T, N, C>(cx, srcB, d);  // its opening barrier: every wave has read A
-  const T kxT = T(cx.kx);
-#pragma unroll
-  for (int r = 0; r < E; ++r) {
-    const cplx<T> b = cx.buf[pidx(LaneIdx{cx.t, NT * r})];
-    v[r] = {v[r].x + kxT * b.y, v[r].y - kxT * b.x};
-  }
-  xsync<NT>();
-  column_fft_out<T, N, C>(cx, v, tw);
-#pragma unroll
-  for (int r = 0; r < E; ++r) out[r] = v[r];
-}
-
-// forward column transform of one row-spectrum field; returns the masked,
-// 1/N^2-normalised right-hand-side values at k = t + NT r
-template <typename T, int N, int C>
-__device__ __forceinline__ void column_forward(const ColCtx<T, N, C>& cx, const cplx<T>* src, const Dims& d,
+// forward column transform of one row-spectrum field A, or of A - i kx B (DX):
+// the masked, 1/N^2-normalised right-hand-side values at k = t + NT r
+template <typename T, int N, int C, bool DX = false>
+__device__ __forceinline__ void column_forward(const ColCtx<T, N, C>& cx, const cplx<T>* A, const cplx<T>* B,
                                                const cplx<T>* __restrict__ tw, cplx<T> (&out)[fft_E<N>()]) {
-  constexpr int E = fft_E<N>(), NT = N / E;
-  tile_load<T, N, C>(cx, src, d);
+  using X = ColCtx<T, N, C>;
+  tile_load<T, N, C, DX>(cx, A, B, out);
+  // with 16 values per lane they come back through the buffer: kept in registers
+  // across the last stage, the kernels spill
+  fft<T, N, X::E, -1, (X::E < 16)>(out, cx.buf, cx.t, tw);
+  if constexpr (X::E >= 16) {
 #pragma unroll
-  for (int r = 0; r < E; ++r) out[r] = cx.buf[pidx(LaneIdx{cx.t, NT * r})];
-  xsync<NT>();
-  column_fft_out<T, N, C>(cx, out, tw);
+    for (int r = 0; r < X::E; ++r) out[r] = reinterpret_cast<const cplx<T>*>(cx.buf)[pidx(LaneIdx{cx.t, X::NT * r})];
+  }
+  const T inv = T(1.0 / (double(N) * double(N)));
+#pragma unroll
+  for (int r = 0; r < X::E; ++r) out[r] = {out[r].x * inv, out[r].y * inv};
 }
 
 // whether a block's two inverse transforms (a field and its i ky version) run side
@@ -1189,47 +1153,49 @@ template <typename T, int N, int C>
 __host__ __device__ constexpr bool col_dual() {
   return fft_E<N>() <= 12 && 2 * C * col_buf(N) * sizeof(cplx<T>) <= 80 * 1024;
 }
+// a column block's LDS, in values of T
+template <typename T, int N, int C>
+__host__ __device__ constexpr int col_lds() {
+  return (col_dual<T, N, C>() ? 2 : 1) * C * ColCtx<T, N, C>::CS;
+}
 
 // inverse column transforms of values S at k = t + NT r (already zero outside
 // the mask) to the intermediate field dst and, with WITH_DY, of i ky S to dst_dy
-template <typename T, int N, int C, typename TS, bool WITH_DY>
-__device__ __forceinline__ void column_inverse(const ColCtx<T, N, C>& cx, const cplx<TS> (&S)[fft_E<N>()],
-                                               cplx<T>* dst, cplx<T>* dst_dy, const Dims& d,
-                                               const cplx<T>* __restrict__ tw) {
-  constexpr int E = fft_E<N>(), NT = N / E;
+template <typename T, int N, int C, bool WITH_DY>
+__device__ __forceinline__ void column_inverse(const ColCtx<T, N, C>& cx, const cplx<T> (&S)[fft_E<N>()],
+                                               cplx<T>* dst, cplx<T>* dst_dy, const cplx<T>* __restrict__ tw) {
+  using X = ColCtx<T, N, C>;
+  constexpr int E = X::E, NT = X::NT;
   auto value = [&](int r, bool dy) -> cplx<T> {
-    const cplx<T> q = {T(S[r].x), T(S[r].y)};
+    const cplx<T> q = S[r];
     if (!dy) return q;
     const int k = cx.t + NT * r;
     const int ky = (k <= N / 2) ? k : k - N;
     return {-T(ky) * q.y, T(ky) * q.x};
   };
-  // no barrier: since the last block-wide tile access (which ends with one)
-  // only this wavefront has touched its buffer
+  // no barrier: since the last block-wide tile access (whose last barrier every
+  // wave has passed) only this lane group has touched its buffer
   if constexpr (WITH_DY && col_dual<T, N, C>()) {
     cplx<T> v[2][E];
 #pragma unroll
     for (int r = 0; r < E; ++r) v[0][r] = value(r, false), v[1][r] = value(r, true);
-    constexpr int SECOND = C * ColCtx<T, N, C>::LC;
-    T* const b[2] = {reinterpret_cast<T*>(cx.buf), reinterpret_cast<T*>(cx.buf + SECOND)};
+    constexpr int SECOND = C * X::CS;
+    T* const b[2] = {cx.buf, cx.buf + SECOND};
     fft_side_by_side<T, N, E, +1, false, false, 2>(v, b, cx.t, tw);
     __syncthreads();
-    tile_store<T, N, C>(cx, cx.lds, dst, d);
-    tile_store<T, N, C>(cx, cx.lds + SECOND, dst_dy, d);
+    tile_store<T, N, C>(cx, cx.lds, dst);
+    tile_store<T, N, C>(cx, cx.lds + SECOND, dst_dy);
   } else {
-    cplx<T> v[E];
 #pragma unroll
-    for (int r = 0; r < E; ++r) v[r] = value(r, false);
-    fft<T, N, E, +1>(v, reinterpret_cast<T*>(cx.buf), cx.t, tw);
-    __syncthreads();
-    tile_store<T, N, C>(cx, cx.lds, dst, d);
-    if constexpr (WITH_DY) {
-      __syncthreads();
+    for (int pass = 0; pass < (WITH_DY ? 2 : 1); ++pass) {
+      if (pass) __syncthreads();  // the tile before has been read
+      cplx<T> v[E];
 #pragma unroll
-      for (int r = 0; r < E; ++r) v[r] = value(r, true);
-      fft<T, N, E, +1>(v, reinterpret_cast<T*>(cx.buf), cx.t, tw);
+      for (int r = 0; r < E; ++r) v[r] = value(r, pass);
+      cplx<T>* out = pass ? dst_dy : dst;
+      fft<T, N, E, +1>(v, cx.buf, cx.t, tw);
       __syncthreads();
-      tile_store<T, N, C>(cx, cx.lds, dst_dy, d);
+      tile_store<T, N, C>(cx, cx.lds, out);
     }
   }
 }
@@ -1273,28 +1239,28 @@ __device__ cplx<double> kin_coef(int kx, int ky, double t, const Phys& ph) {
 // stage >= 0: the RK4 stage; stage < 0: the prologue (the current state's
 // column-pass outputs only).  t_next: time of the stage input this launch
 // prepares (the prescribed flow of a kinematic run is evaluated there).
+// G: the group's kind, g the group itself; groups that differ only in their
+// fields' places (xi and P: CG_XIX, the momentum 1-form: CG_GMX, the Eulerian
+// means of other fields: CG_EF0) share a kind.
 template <typename T, int N, int C, int G>
-__device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const StepPtrs<T>& P, const Dims& d,
-                                             const Phys& ph, int stage, double t_next,
-                                             const cplx<T>* __restrict__ Ys_in, cplx<T>* __restrict__ Ys_out) {
+__device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const StepPtrs<T>& P, const Phys& ph, int g,
+                                             int stage, double t_next, const cplx<T>* __restrict__ Ys_in,
+                                             cplx<T>* __restrict__ Ys_out) {
   constexpr int E = fft_E<N>(), NT = N / E;
-  constexpr bool DBL = (G == CG_XIX || G == CG_XIY || G == CG_PX || G == CG_PY);
+  constexpr bool DBL = G == CG_XIX;
   constexpr bool DYN = (G == CG_U || G == CG_V || G == CG_H);
-  constexpr bool EUL = (G == CG_EF0 || G == CG_EF1);  // Eulerian accumulators of the averaged fields
+  constexpr bool EUL = G == CG_EF0;  // Eulerian accumulators of the averaged fields
   using TS = typename std::conditional<DBL, double, T>::type;
-  const size_t sp = d.spec_elems();
-  const size_t rf = d.rowfield_elems();
+  constexpr Dims d = dims_of<N>();
+  constexpr size_t sp = d.spec_elems(), rf = d.rowfield_elems();
   if constexpr (EUL) {
     if (stage < 0) return;  // not an input of the rows passes
   }
 
-  // right-hand-side inputs of this group
-  constexpr int NF = DYN ? 2 : 1;
-  constexpr int F0 = (G == CG_U) ? RS_ZV : (G == CG_V) ? RS_ZU : (G == CG_H) ? RS_HU
-                   : (G == CG_XIX) ? RS_XIX : (G == CG_XIY) ? RS_XIY : (G == CG_GBH) ? RS_GBH
-                   : (G == CG_GBZ) ? RS_GBZ : (G == CG_GTH) ? RS_GTH : (G == CG_GTZ) ? RS_GTZ
-                   : (G == CG_PX) ? RS_PX : (G == CG_PY) ? RS_PY : (G == CG_GMX) ? RS_GMX
-                   : (G == CG_GMY) ? RS_GMY : (G == CG_EF0) ? RS_F0 : RS_F1;
+  // right-hand-side inputs of this group: F0, and for the dynamics F1
+  static_assert(RS_PY - RS_XIX == CG_PY - CG_XIX && IC_PY - IC_XIX == 2 * (CG_PY - CG_XIX), "mean groups in field order");
+  const int F0 = (G == CG_U) ? RS_ZV : (G == CG_V) ? RS_ZU : (G == CG_H) ? RS_HU : (G == CG_GMX) ? RS_GMX + (g - CG_GMX)
+               : EUL ? RS_F0 + (g - CG_EF0) : RS_XIX + (g - CG_XIX);
   constexpr int F1 = (G == CG_U || G == CG_V) ? RS_K : RS_HV;
 
   // state of this group
@@ -1302,39 +1268,41 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
   cplx<TS>* YL = nullptr;  // trailing words of compensated float state
   cplx<TS>* A;
   if constexpr (DBL) {
-    constexpr int sd = (G == CG_XIX) ? SD_XIX : (G == CG_XIY) ? SD_XIY : (G == CG_PX) ? SD_PX : SD_PY;
+    const int sd = (g < CG_PX) ? SD_XIX + (g - CG_XIX) : SD_PX + (g - CG_PX);
     Y = P.Yd + sd * sp;
     A = P.Ad + sd * sp;
   } else {
-    constexpr int sr = (G == CG_U) ? SF_U : (G == CG_V) ? SF_V : (G == CG_H) ? SF_H : (G == CG_GBH) ? SF_GBH
-                     : (G == CG_GBZ) ? SF_GBZ : (G == CG_GTH) ? SF_GTH : (G == CG_GTZ) ? SF_GTZ
-                     : (G == CG_GMX) ? SF_GMX : (G == CG_GMY) ? SF_GMY : (G == CG_EF0) ? SF_EH : SF_EZ;
+    const int sr = (G == CG_U) ? SF_U : (G == CG_V) ? SF_V : (G == CG_H) ? SF_H : (G == CG_GBH) ? SF_GBH
+                 : (G == CG_GBZ) ? SF_GBZ : (G == CG_GTH) ? SF_GTH : (G == CG_GTZ) ? SF_GTZ
+                 : (G == CG_GMX) ? SF_GMX + (g - CG_GMX) : SF_EH + (g - CG_EF0);
     Y = reinterpret_cast<cplx<TS>*>(P.Yr) + sr * sp;
     if constexpr (std::is_same<TS, float>::value) YL = reinterpret_cast<cplx<TS>*>(P.Yl) + sr * sp;
     A = reinterpret_cast<cplx<TS>*>(P.Ar) + sr * sp;
   }
   const T fT = T(ph.f), gT = T(ph.g), HT = T(ph.H);
 
-  cplx<TS> S[E];
+  // the next stage input, in the transforms' precision
+  cplx<T> S[E];
   if (stage < 0 || (DYN && ph.kin)) {
     // prologue (the current state's transforms) or a prescribed flow (a kinematic
     // run has no dynamics right-hand sides)
 #pragma unroll
     for (int r = 0; r < E; ++r) {
       const ColIdx<N> ix{cx.t, r};
-      S[r] = {TS(0), TS(0)};
+      S[r] = {T(0), T(0)};
       if (ix.none() || !(ix.in() && cx.valid)) continue;
       const unsigned j = cx.ky0 + ix.lane();
       if constexpr (DYN) {
         if (ph.kin) {
           // the next stage input is the prescribed flow at t_next
           const cplx<double> c = kin_coef<G>(cx.kx, ix.ky(), t_next, ph);
-          S[r] = {TS(c.x), TS(c.y)};
+          S[r] = {T(c.x), T(c.y)};
           put32(Ys_out + (G - CG_U) * sp + ix.off(), j, S[r]);
           continue;
         }
       }
-      S[r] = at32(Y + ix.off(), j);
+      const cplx<TS> now = at32(Y + ix.off(), j);
+      S[r] = {T(now.x), T(now.y)};
       if constexpr (DYN) put32(Ys_out + (G - CG_U) * sp + ix.off(), j, S[r]);
     }
   } else {
@@ -1356,15 +1324,18 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
     constexpr bool EULA = (G == CG_GTH || G == CG_GBH), EULB = (G == CG_GTZ || G == CG_GBZ);
     constexpr bool SRCG = (G == CG_GTH || G == CG_GTZ);
     constexpr int EPAR = SRCG ? 0 : 1;
-    const bool eul = (EULA || EULB) && !ph.gen;
+    const double cn = (stage == 1) ? 0.5 * ph.dt : ph.dt;
     constexpr bool PRE = E <= 8;
-    constexpr int RB0 = (DBL || DYN || EULA || EULB) ? 4 : 8;
+    constexpr int RB0 = (DBL || DYN || EULA || EULB) ? 2 : 4;  // (4 and 8: spills at 16 values per lane)
     constexpr int RB = PRE ? E : ((E % RB0 == 0) ? RB0 : 4);
     static_assert(E % RB == 0, "coefficient batches");
     cplx<T> su[RB], sv[RB], sh[RB];
     cplx<TS> y[RB], lo[RB], a[RB];
     cplx<T> ey[RB], el[RB], ea[RB];  // Eulerian accumulator
-    auto load = [&](int r0i) {
+    // kind: the stage's (rk4v); eul: the group carries an Eulerian accumulator
+    auto load = [&](auto kind, auto eulc, int r0i) {
+      constexpr int KS = decltype(kind)::value;
+      constexpr bool eul = decltype(eulc)::value;
 #pragma unroll
       for (int q = 0; q < RB; ++q) {
         const ColIdx<N> ix{cx.t, r0i + q};
@@ -1376,7 +1347,7 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
           sv[q] = at32(Ys_in + 1 * sp + o, j);
           sh[q] = at32(Ys_in + 2 * sp + o, j);
         }
-        rk4_load<TS>(stage, Y + o, YL + o, A + o, j, y[q], lo[q], a[q]);
+        rk4_load<KS>(Y + o, YL + o, A + o, j, y[q], lo[q], a[q]);
         if constexpr (EULA || EULB) {
           const bool acc = (r0i + q) % 2 == EPAR;
           if (eul && (SRCG || acc)) {
@@ -1389,33 +1360,25 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
           }
           if (eul && acc) {
             constexpr int se = EULA ? SF_EH : SF_EZ;
-            rk4_load<T>(stage, P.Yr + se * sp + o, P.Yl + se * sp + o, P.Ar + se * sp + o, j, ey[q], el[q], ea[q]);
+            rk4_load<KS, T>(P.Yr + se * sp + o, P.Yl + se * sp + o, P.Ar + se * sp + o, j, ey[q], el[q], ea[q]);
           }
         }
       }
     };
-    if constexpr (PRE) {
-      load(0);
-      sched_fence();
-    }
-    // the first input's values in registers; the second one's (dynamics groups)
-    // stay in the wave's buffer until the stage update reads them
-    cplx<T> r0[E];
-    if constexpr (G == CG_U) {
-      // zeta v - i kx K in one transform
-      column_forward_dx<T, N, C>(cx, P.RS + F0 * rf, P.RS + F1 * rf, d, P.tw, r0);
-    } else {
-      column_forward<T, N, C>(cx, P.RS + F0 * rf, d, P.tw, r0);
-      if constexpr (NF == 2) column_forward_lds<T, N, C>(cx, P.RS + F1 * rf, d, P.tw);
-    }
-#pragma unroll
-    for (int r0i = 0; r0i < E; r0i += RB) {
-      if constexpr (!PRE) load(r0i);
+    cplx<T> r0[E];  // the transformed right-hand side
+    auto update = [&](auto kind, auto eulc, int r0i) {
+      constexpr int KS = decltype(kind)::value;
+      constexpr bool eul = decltype(eulc)::value;
+      // a fresh view of the lane's index for every batch: what is computed from it
+      // (wavenumbers, the hyperviscosity) stays inside the batch, instead of being
+      // formed for all coefficients ahead of the stage kinds' common code
+      int t = cx.t;
+      if constexpr (!PRE) asm volatile("" : "+v"(t));
 #pragma unroll
       for (int q = 0; q < RB; ++q) {
         const int r = r0i + q;
-        const ColIdx<N> ix{cx.t, r};
-        S[r] = {TS(0), TS(0)};
+        const ColIdx<N> ix{t, r};
+        S[r] = {T(0), T(0)};
         if (ix.none() || !(ix.in() && cx.valid)) continue;
         const int ky = ix.ky(), o = ix.off();
         const unsigned j = cx.ky0 + ix.lane();
@@ -1434,8 +1397,8 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
           }
           if (eul && acc) {
             constexpr int se = EULA ? SF_EH : SF_EZ;
-            rk4v<T>(stage, ey[q], el[q], ea[q], fsrc, ph.dt);
-            rk4_store<T>(stage, P.Yr + se * sp + o, P.Yl + se * sp + o, P.Ar + se * sp + o, j, ey[q], el[q], ea[q]);
+            rk4v<KS, T>(ey[q], el[q], ea[q], fsrc, ph.dt, cn);
+            rk4_store<KS, T>(P.Yr + se * sp + o, P.Yl + se * sp + o, P.Ar + se * sp + o, j, ey[q], el[q], ea[q]);
           }
         }
         const double k2 = double(cx.kx) * cx.kx + double(ky) * ky;
@@ -1444,108 +1407,252 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
         if constexpr (G == CG_U) {
           // (zeta v - i kx K) + f v - i kx g h - nu8 |k|^8 u
           const cplx<T> u = su[q], v = sv[q], h = sh[q];
-          const cplx<T> B = {gT * h.x, gT * h.y};
-          R = {r0[r].x + fT * v.x + kxT * B.y - hv * u.x, r0[r].y + fT * v.y - kxT * B.x - hv * u.y};
+          R = {r0[r].x + fT * v.x + kxT * (gT * h.y) - hv * u.x, r0[r].y + fT * v.y - kxT * (gT * h.x) - hv * u.y};
         } else if constexpr (G == CG_V) {
-          // -zeta u - f u - i ky (g h + K) - nu8 |k|^8 v
+          // (-zeta u - i ky K) - f u - i ky g h - nu8 |k|^8 v
           const cplx<T> u = su[q], v = sv[q], h = sh[q];
-          const cplx<T> r1 = column_value<T, N, C>(cx, r);
-          const cplx<T> B = {gT * h.x + r1.x, gT * h.y + r1.y};
-          R = {-r0[r].x - fT * u.x + kyT * B.y - hv * v.x, -r0[r].y - fT * u.y - kyT * B.x - hv * v.y};
+          R = {r0[r].x - fT * u.x + kyT * (gT * h.y) - hv * v.x, r0[r].y - fT * u.y - kyT * (gT * h.x) - hv * v.y};
         } else if constexpr (G == CG_H) {
-          // -i kx (H u + F(eta u)) - i ky (H v + F(eta v)) - nu8 |k|^8 h
+          // (-i kx F(eta u) - i ky F(eta v)) - i kx H u - i ky H v - nu8 |k|^8 h
           const cplx<T> u = su[q], v = sv[q], h = sh[q];
-          const cplx<T> fx = {HT * u.x + r0[r].x, HT * u.y + r0[r].y};
-          const cplx<T> r1 = column_value<T, N, C>(cx, r);
-          const cplx<T> fy = {HT * v.x + r1.x, HT * v.y + r1.y};
-          R = {kxT * fx.y + kyT * fy.y - hv * h.x, -kxT * fx.x - kyT * fy.x - hv * h.y};
+          R = {r0[r].x + kxT * (HT * u.y) + kyT * (HT * v.y) - hv * h.x,
+               r0[r].y - kxT * (HT * u.x) - kyT * (HT * v.x) - hv * h.y};
         } else {
           R = r0[r];
           if constexpr (SRCG) R = {R.x + fsrc.x, R.y + fsrc.y};
           (void)hv;
         }
         const cplx<TS> Rk = {TS(R.x), TS(R.y)};
-        S[r] = rk4v<TS>(stage, y[q], lo[q], a[q], Rk, ph.dt);
-        rk4_store<TS>(stage, Y + o, YL + o, A + o, j, y[q], lo[q], a[q]);
+        const cplx<TS> next = rk4v<KS, TS>(y[q], lo[q], a[q], Rk, ph.dt, cn);
+        S[r] = {T(next.x), T(next.y)};
+        rk4_store<KS, TS>(Y + o, YL + o, A + o, j, y[q], lo[q], a[q]);
         if constexpr (DYN) put32(Ys_out + (G - CG_U) * sp + o, j, S[r]);
       }
+    };
+    // f(kind, eul) for this launch's stage and run
+    auto with_kind = [&](auto&& f) {
+      auto by_stage = [&](auto eulc) {
+        if (stage == 0) f(std::integral_constant<int, 0>{}, eulc);
+        else if (stage < 3) f(std::integral_constant<int, 1>{}, eulc);
+        else f(std::integral_constant<int, 3>{}, eulc);
+      };
+      if constexpr (EULA || EULB) {
+        if (!ph.gen) by_stage(std::true_type{});
+        else by_stage(std::false_type{});
+      } else {
+        by_stage(std::false_type{});
+      }
+    };
+    if constexpr (PRE) {
+      with_kind([&](auto kind, auto eulc) { load(kind, eulc, 0); });
+      sched_fence();
     }
+    // the transformed products; the dynamics groups' two inputs as one spectrum:
+    //   u: zeta v - i kx K   v: -zeta u - i ky K   h: -i kx (eta u) - i ky (eta v)
+    // (an i kx joins before the transform, where kx is a column's constant; an i ky
+    // after it, its input first, so that one spectrum at a time is in registers)
+    if constexpr (G == CG_U) {
+      column_forward<T, N, C, true>(cx, P.RS + F0 * rf, P.RS + F1 * rf, P.tw, r0);
+    } else if constexpr (G == CG_V || G == CG_H) {
+      column_forward<T, N, C>(cx, P.RS + F1 * rf, nullptr, P.tw, r0);
+#pragma unroll
+      for (int r = 0; r < E; ++r) {
+        const int k = cx.t + NT * r;
+        const T ky = T((k <= N / 2) ? k : k - N);
+        r0[r] = {ky * r0[r].y, -ky * r0[r].x};
+      }
+      cplx<T> f[E];
+      column_forward<T, N, C>(cx, P.RS + F0 * rf, nullptr, P.tw, f);
+      const T kx = T(cx.kx);
+#pragma unroll
+      for (int r = 0; r < E; ++r) {
+        if constexpr (G == CG_V) r0[r] = {r0[r].x - f[r].x, r0[r].y - f[r].y};
+        else r0[r] = {r0[r].x + kx * f[r].y, r0[r].y - kx * f[r].x};
+      }
+    } else {
+      column_forward<T, N, C>(cx, P.RS + F0 * rf, nullptr, P.tw, r0);
+    }
+    with_kind([&](auto kind, auto eulc) {
+#pragma unroll
+      for (int r0i = 0; r0i < E; r0i += RB) {
+        if constexpr (!PRE) {
+          load(kind, eulc, r0i);
+          sched_fence();  // the batch's loads together, and none of the next one's with them
+        }
+        update(kind, eulc, r0i);
+        if constexpr (!PRE) sched_fence();
+      }
+    });
   }
 
   // inverse column transforms of the next stage input
   if constexpr (G == CG_U) {
-    column_inverse<T, N, C, TS, true>(cx, S, P.IC + IC_U * rf, P.IC + IC_UY * rf, d, P.tw);
+    column_inverse<T, N, C, true>(cx, S, P.IC + IC_U * rf, P.IC + IC_UY * rf, P.tw);
   } else if constexpr (G == CG_V) {
-    column_inverse<T, N, C, TS, false>(cx, S, P.IC + IC_V * rf, nullptr, d, P.tw);
+    column_inverse<T, N, C, false>(cx, S, P.IC + IC_V * rf, nullptr, P.tw);
   } else if constexpr (G == CG_H) {
     // the rows passes work with eta = h - H: drop H from the mean (k = 0, lane 0)
-    if (cx.kx == 0 && cx.t == 0) S[0].x -= TS(ph.H);
-    column_inverse<T, N, C, TS, false>(cx, S, P.IC + IC_H * rf, nullptr, d, P.tw);
+    if (cx.kx == 0 && cx.t == 0) S[0].x -= T(ph.H);
+    column_inverse<T, N, C, false>(cx, S, P.IC + IC_H * rf, nullptr, P.tw);
   } else if constexpr (!EUL) {
-    constexpr int o = (G == CG_XIX) ? IC_XIX : (G == CG_XIY) ? IC_XIY : (G == CG_GBH) ? IC_GBH
-                    : (G == CG_GBZ) ? IC_GBZ : (G == CG_GTH) ? IC_GTH : (G == CG_GTZ) ? IC_GTZ
-                    : (G == CG_PX) ? IC_PX : (G == CG_PY) ? IC_PY : (G == CG_GMX) ? IC_GMX : IC_GMY;
-    column_inverse<T, N, C, TS, true>(cx, S, P.IC + o * rf, P.IC + (o + 1) * rf, d, P.tw);
+    const int o = (G == CG_GMX) ? IC_GMX + 2 * (g - CG_GMX) : IC_XIX + 2 * (g - CG_XIX);
+    column_inverse<T, N, C, true>(cx, S, P.IC + o * rf, P.IC + (o + 1) * rf, P.tw);
   }
 }
 
 // stage >= 0: RK4 stage; stage < 0: only transform the current state (prologue)
 template <typename T, int N, int C>
-__device__ __forceinline__ void columns_body(const StepPtrs<T>& P, const Dims& d, const Phys& ph, int stage,
-                                             double t_next, const cplx<T>* Ys_in, cplx<T>* Ys_out, int tile,
-                                             int slot, cplx<T>* lds) {
-  constexpr int NT = N / fft_E<N>(), LC = col_buf(N);
-  ColCtx<T, N, C> cx;
-  cx.lds = lds;
-  cx.c = threadIdx.x / NT;
-  cx.t = threadIdx.x % NT;
-  cx.buf = lds + cx.c * LC;
-  cx.kx0 = tile * C;
-  cx.kx = cx.kx0 + cx.c;
-  cx.valid = cx.kx <= kcut<N>();
-  cx.ky0 = (unsigned)(min(cx.kx, kcut<N>()) * d.NKY + d.K);
-#define LM_CG(g) \
-  case g: column_group<T, N, C, g>(cx, P, d, ph, stage, t_next, Ys_in, Ys_out); break
-  switch (col_group_of(ph, slot)) {
-    LM_CG(CG_U); LM_CG(CG_V); LM_CG(CG_H); LM_CG(CG_XIX); LM_CG(CG_XIY); LM_CG(CG_GBH); LM_CG(CG_GBZ);
-    LM_CG(CG_GTH); LM_CG(CG_GTZ); LM_CG(CG_PX); LM_CG(CG_PY); LM_CG(CG_GMX); LM_CG(CG_GMY);
-    LM_CG(CG_EF0); LM_CG(CG_EF1);
-    default: break;
+__device__ __forceinline__ void columns_body(const StepPtrs<T>& P, const Phys& ph, int stage, double t_next,
+                                             const cplx<T>* Ys_in, cplx<T>* Ys_out, int tile, int slot, T* lds) {
+  const ColCtx<T, N, C> cx(lds, tile);
+  const int g = col_group_of(ph, slot);
+#define LM_CG(k) column_group<T, N, C, k>(cx, P, ph, g, stage, t_next, Ys_in, Ys_out)
+  switch (g) {
+    case CG_U: LM_CG(CG_U); break;
+    case CG_V: LM_CG(CG_V); break;
+    case CG_H: LM_CG(CG_H); break;
+    case CG_GBH: LM_CG(CG_GBH); break;
+    case CG_GBZ: LM_CG(CG_GBZ); break;
+    case CG_GTH: LM_CG(CG_GTH); break;
+    case CG_GTZ: LM_CG(CG_GTZ); break;
+    case CG_GMX: case CG_GMY: LM_CG(CG_GMX); break;
+    case CG_EF0: case CG_EF1: LM_CG(CG_EF0); break;
+    default: LM_CG(CG_XIX); break;  // xi_x, xi_y, P_x, P_y
   }
 #undef LM_CG
 }
 
-// resident waves per SIMD asked for.  16 (or 12) values per lane in float32: 4 (at
-// most 128 registers).  8 values per lane: the whole column's state is in
-// registers during the transforms, and the grids are too small to fill the chip:
-// 2.  float64: 1.
+// --------------------------------------------------------------------------
+// the launches of a stage
+// --------------------------------------------------------------------------
+// Large grids: three passes in order, rows of the dynamics and strategy 1, rows of
+// strategy 2, all column groups.
+//
+// Small grids (stage_merged): blocks of a rows pass and of the column groups that
+// do not depend on it share a launch; stage i is
+//   A(i)  dynamics and strategy-1 rows of stage i, with the strategy-2 (and
+//         momentum) column groups of stage i - 1
+//   B(i)  strategy-2 rows of stage i, with the dynamics and strategy-1 column
+//         groups of stage i (their inputs came with A(i))
+// so a stage has two launch boundaries instead of three, and two chains side by
+// side.  Every block does what it would in a launch of its own.  Neither part of a
+// launch writes what the other reads: A's columns write the strategy-2 state and
+// inputs, which only B's rows read; its rows write the physical fields and the
+// dynamics' and strategy-1 row spectra; B's columns write those groups' state,
+// inputs and the other stage-value buffer.  A launch of one kind alone is the same
+// kernel with no blocks of the other.  Measured per step, three passes -> two
+// launches: 64^2 float64 59.1 -> 44.4 us, 128^2 float32 62.2 -> 53.9, 192^2 float32
+// 99.6 -> 67.8, 256^2 float64 100.4 -> 96.7, 384^2 float32 141 -> 116.  From 512^2 on
+// the passes fill the chip by themselves and the larger of the two parts' registers
+// and LDS costs both (merged, 512^2 float32 130.6 -> 139.3, 1024^2 346 -> 366).
+template <typename T, int N>
+__host__ __device__ constexpr bool stage_merged() { return N < 512; }
+
+template <typename T, int N, int W, int ROW_THREADS, int ROW_LDS>
+struct StageGeo {
+  static constexpr int C = col_tile<N, W>(), COL_THREADS = col_threads<N, W>();
+  static constexpr int THREADS = COL_THREADS > ROW_THREADS ? COL_THREADS : ROW_THREADS;
+  static constexpr int LDS = col_lds<T, N, C>() > ROW_LDS ? col_lds<T, N, C>() : ROW_LDS;  // values of T
+  static constexpr int TILES = (dims_of<N>().NKX + C - 1) / C;
+  static constexpr int ROWS = N / CoopGeo<T, N>::WR;  // row blocks of a run
+  static_assert(COL_THREADS % 64 == 0 && THREADS <= 1024 && ROWS % 8 == 0, "stage blocks");
+};
+template <typename T, int N, int W>
+using StageA = StageGeo<T, N, W, DynGeo<T, N>::THREADS, DynGeo<T, N>::LDS>;
+template <typename T, int N, int W>
+using StageB = StageGeo<T, N, W, RhsGeo<T, N>::THREADS, RhsGeo<T, N>::LDS>;
+
+// Resident waves per SIMD the column groups' registers leave room for: at 1024 in
+// float32 4 (at most 128 registers), in float64 2; on smaller grids, which do not
+// fill the chip, they keep their whole state in registers.
 template <typename T, int N>
 __host__ __device__ constexpr int col_waves() {
-  return sizeof(T) == 4 ? (fft_E<N>() <= 8 ? 2 : 4) : 1;
+  return N >= 1024 ? (sizeof(T) == 4 ? 4 : 2) : (sizeof(T) == 4 ? 2 : 1);
 }
 
-// buffers of a column block: one set, or two for side-by-side inverse transforms
-template <typename T, int N, int W>
-__host__ __device__ constexpr int col_lds() {
-  constexpr int C = col_tile<N, W>();
-  return (col_dual<T, N, C>() ? 2 : 1) * C * col_buf(N);
-}
+// the column pass (grid = (column tiles, group slots)), slots from slot0 on
+template <typename T>
+struct ColArgs {
+  int stage, slot0, nslot, cols;  // stage < 0: the prologue; cols: column blocks (merged launches)
+  double t_next;
+  const cplx<T>* Ys_in;
+  cplx<T>* Ys_out;
+};
 
 // W: column tile width (col_tile<N, W>)
-// slot0: the first group slot of this launch (grid = (column tiles, group slots))
 template <typename T, int N, int W>
 __global__ void __launch_bounds__((col_threads<N, W>()), (col_waves<T, N>()))
-    k_columns(StepPtrs<T> P, Phys ph, int stage, double t_next, const cplx<T>* Ys_in, cplx<T>* Ys_out,
-              int remap, int slot0) {
+    k_columns(StepPtrs<T> P, Phys ph, ColArgs<T> ca, int remap) {
+  constexpr int C = col_tile<N, W>();
   static_assert(col_threads<N, W>() % 64 == 0 && col_threads<N, W>() <= 1024, "column block");
-  __shared__ cplx<T> lds[col_lds<T, N, W>()];
+  __shared__ __align__(16) T lds[col_lds<T, N, C>()];
   int tile, slot, z;
   xcd_split(gridDim.x, gridDim.y, tile, slot, z, remap);
-  columns_body<T, N, col_tile<N, W>()>(P, dims_of<N>(), ph, stage, t_next, Ys_in, Ys_out, tile, slot0 + slot, lds);
+  columns_body<T, N, C>(P, ph, ca.stage, ca.t_next, ca.Ys_in, ca.Ys_out, tile, ca.slot0 + slot, lds);
+}
+
+// what a block of a stage launch is: column blocks come first (cols of them, a
+// multiple of 8, of which nslot * TILES * runs do work), then row blocks.
+// Workgroups go round-robin to the 8 XCDs (each with its own L2): with remap every
+// XCD gets a contiguous run of column tiles (all groups of a tile next to each
+// other) and of rows, as xcd_split.
+struct StageRole {
+  bool col, idle;
+  int tile, slot, row, run;
+};
+template <typename S>
+__device__ __forceinline__ StageRole stage_role(unsigned cols, unsigned nslot, unsigned runs, unsigned rows, int remap) {
+  StageRole r{};
+  const unsigned b = blockIdx.x, x = b % NUM_XCD;
+  r.col = b < cols;
+  if (r.col) {
+    const unsigned i = remap ? x * (cols / NUM_XCD) + b / NUM_XCD : b;
+    r.idle = i >= nslot * S::TILES * runs;
+    r.slot = (int)(i % nslot);
+    const unsigned rest = i / nslot;
+    r.tile = (int)(rest % S::TILES);
+    r.run = (int)(rest / S::TILES);
+  } else {
+    const unsigned bb = b - cols;
+    const unsigned i = remap ? x * (rows / NUM_XCD) + bb / NUM_XCD : bb;
+    r.row = (int)(i % S::ROWS);
+    r.run = (int)(i / S::ROWS);
+  }
+  return r;
+}
+
+template <typename T, int N, int W>
+__global__ void __launch_bounds__((StageA<T, N, W>::THREADS), (col_waves<T, N>()))
+    k_stage_a(StepPtrs<T> P, Phys ph, double s, ColArgs<T> ca, int rows, int remap) {
+  using S = StageA<T, N, W>;
+  __shared__ __align__(16) T lds[S::LDS];
+  const StageRole r = stage_role<S>(ca.cols, ca.nslot, 1, rows, remap);
+  if (r.col) {
+    if (r.idle || threadIdx.x >= S::COL_THREADS) return;
+    columns_body<T, N, S::C>(P, ph, ca.stage, ca.t_next, ca.Ys_in, ca.Ys_out, r.tile, ca.slot0 + r.slot, lds);
+  } else {
+    if (threadIdx.x >= DynGeo<T, N>::THREADS) return;
+    rows_dyn_body<T, N, false>(P, ph, s, r.row, lds);
+  }
+}
+
+template <typename T, int N, int W>
+__global__ void __launch_bounds__((StageB<T, N, W>::THREADS), (col_waves<T, N>()))
+    k_stage_b(StepPtrs<T> P, Phys ph, double s, ColArgs<T> ca, int rows, int remap) {
+  using S = StageB<T, N, W>;
+  __shared__ __align__(16) T lds[S::LDS];
+  const StageRole r = stage_role<S>(ca.cols, ca.nslot, 1, rows, remap);
+  if (r.col) {
+    if (r.idle || threadIdx.x >= S::COL_THREADS) return;
+    columns_body<T, N, S::C>(P, ph, ca.stage, ca.t_next, ca.Ys_in, ca.Ys_out, r.tile, ca.slot0 + r.slot, lds);
+  } else {
+    if (threadIdx.x >= RhsGeo<T, N>::THREADS) return;
+    rows_rhs_body<T, N, false>(P, s, r.row, lds);
+  }
 }
 
 // --------------------------------------------------------------------------
-// batched entry points: blockIdx.z selects a run of one (N, precision) group
+// batched entry points: the launches of many runs of one (N, precision) group
 // --------------------------------------------------------------------------
 
 // time since the interval start at a stage, from integers (as the single-run path)
@@ -1585,21 +1692,61 @@ __global__ void __launch_bounds__((MomGeo<T, N>::THREADS), (MomGeo<T, N>::min_wa
   rows_mom_body<T, N, CUB>(R.P, batch_s(R, stage), rowblock, lds);
 }
 
-// stage parity selects the stage-value buffers: between steps the current
-// stage input is always Ys0 (four swaps per step)
-template <typename T, int N, int W>
-__global__ void __launch_bounds__((col_threads<N, W>()), (col_waves<T, N>()))
-    k_columns_b(const RunDesc<T>* __restrict__ runs, int stage, int remap) {
-  __shared__ cplx<T> lds[col_lds<T, N, W>()];
-  int tile, group, z;
-  xcd_split(gridDim.x, gridDim.y, tile, group, z, remap);
-  const RunDesc<T>& R = runs[z];
+// the column part of a batched launch; stage parity selects the stage-value
+// buffers: between steps the current stage input is always Ys0 (four swaps per step)
+template <typename T, int N, int C>
+__device__ __forceinline__ void columns_run(const RunDesc<T>& R, int stage, int tile, int slot, T* lds) {
   const cplx<T>* Ys_in = (stage & 1) ? R.Ys1 : R.Ys0;
   cplx<T>* Ys_out = (stage & 1) ? R.Ys0 : R.Ys1;
   // time of the next stage input, from integers (as the single-run path)
   const double cn = (stage <= 1) ? 0.5 : 1.0;
   const double t_next = (double(R.n_tau + *R.counter) + cn) * R.ph.dt;
-  columns_body<T, N, col_tile<N, W>()>(R.P, dims_of<N>(), R.ph, stage, t_next, Ys_in, Ys_out, tile, group, lds);
+  columns_body<T, N, C>(R.P, R.ph, stage, t_next, Ys_in, Ys_out, tile, slot, lds);
+}
+
+template <typename T, int N, int W>
+__global__ void __launch_bounds__((col_threads<N, W>()), (col_waves<T, N>()))
+    k_columns_b(const RunDesc<T>* __restrict__ runs, int stage, int remap) {
+  constexpr int C = col_tile<N, W>();
+  __shared__ __align__(16) T lds[col_lds<T, N, C>()];
+  int tile, slot, z;
+  xcd_split(gridDim.x, gridDim.y, tile, slot, z, remap);
+  columns_run<T, N, C>(runs[z], stage, tile, slot, lds);
+}
+
+// stage: of the rows; the columns are those of cstage
+template <typename T, int N, int W>
+__global__ void __launch_bounds__((StageA<T, N, W>::THREADS), (col_waves<T, N>()))
+    k_stage_a_b(const RunDesc<T>* __restrict__ runs, int nruns, int stage, int cstage, int slot0, int nslot, int cols,
+                int rows, int remap) {
+  using S = StageA<T, N, W>;
+  __shared__ __align__(16) T lds[S::LDS];
+  const StageRole r = stage_role<S>(cols, nslot, nruns, rows, remap);
+  if (r.col) {
+    if (r.idle || threadIdx.x >= S::COL_THREADS) return;
+    columns_run<T, N, S::C>(runs[r.run], cstage, r.tile, slot0 + r.slot, lds);
+  } else {
+    if (threadIdx.x >= DynGeo<T, N>::THREADS) return;
+    const RunDesc<T>& R = runs[r.run];
+    rows_dyn_body<T, N, false>(R.P, R.ph, batch_s(R, stage), r.row, lds);
+  }
+}
+
+template <typename T, int N, int W>
+__global__ void __launch_bounds__((StageB<T, N, W>::THREADS), (col_waves<T, N>()))
+    k_stage_b_b(const RunDesc<T>* __restrict__ runs, int nruns, int stage, int cstage, int slot0, int nslot, int cols,
+                int rows, int remap) {
+  using S = StageB<T, N, W>;
+  __shared__ __align__(16) T lds[S::LDS];
+  const StageRole r = stage_role<S>(cols, nslot, nruns, rows, remap);
+  if (r.col) {
+    if (r.idle || threadIdx.x >= S::COL_THREADS) return;
+    columns_run<T, N, S::C>(runs[r.run], cstage, r.tile, slot0 + r.slot, lds);
+  } else {
+    if (threadIdx.x >= RhsGeo<T, N>::THREADS) return;
+    const RunDesc<T>& R = runs[r.run];
+    rows_rhs_body<T, N, false>(R.P, batch_s(R, stage), r.row, lds);
+  }
 }
 
 }  // namespace lm
