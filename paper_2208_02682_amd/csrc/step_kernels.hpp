@@ -992,15 +992,8 @@ __device__ __forceinline__ cplx<TS> rk4v(cplx<TS>& y, cplx<TS>& lo, cplx<TS>& a,
   }
 }
 
-// the words rk4v reads (y always, a from stage 1, lo at stage 3 for float) and
-// writes back (a at stages 0-2, y and lo at stage 3)
-template <int K, typename TS>
-__device__ __forceinline__ void rk4_load(const cplx<TS>* Yp, const cplx<TS>* Lp, const cplx<TS>* Ap, unsigned j,
-                                         cplx<TS>& y, cplx<TS>& lo, cplx<TS>& a) {
-  y = at32(Yp, j);
-  if constexpr (K >= 1) a = at32(Ap, j);
-  if constexpr (K == 3 && std::is_same<TS, float>::value) lo = at32(Lp, j);
-}
+// the words rk4v writes back: a at stages 0-2, y and lo at stage 3 (it reads y
+// always, a from stage 1, lo at stage 3 for float)
 template <int K, typename TS>
 __device__ __forceinline__ void rk4_store(cplx<TS>* Yp, cplx<TS>* Lp, cplx<TS>* Ap, unsigned j, const cplx<TS>& y,
                                           const cplx<TS>& lo, const cplx<TS>& a) {
@@ -1332,40 +1325,53 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
     cplx<T> su[RB], sv[RB], sh[RB];
     cplx<TS> y[RB], lo[RB], a[RB];
     cplx<T> ey[RB], el[RB], ea[RB];  // Eulerian accumulator
-    // kind: the stage's (rk4v); eul: the group carries an Eulerian accumulator
-    auto load = [&](auto kind, auto eulc, int r0i) {
-      constexpr int KS = decltype(kind)::value;
-      constexpr bool eul = decltype(eulc)::value;
+    // acc1, acc3: the accumulator and the trailing words are wanted (stages 1 to 3,
+    // and 3); eul: the group carries an Eulerian accumulator.  One line of code for
+    // all stages: written once per stage kind, the arrays end up in scratch memory
+    // (64^2 float64 44.4 us per step, so 41.2)
+    auto load = [&](bool eul, bool acc1, bool acc3, int r0i) {
+      auto each = [&](auto f) {
 #pragma unroll
-      for (int q = 0; q < RB; ++q) {
-        const ColIdx<N> ix{cx.t, r0i + q};
-        if (ix.none()) continue;
-        const unsigned j = cx.ky0 + ix.lane();
-        const int o = ix.off();
+        for (int q = 0; q < RB; ++q) {
+          const ColIdx<N> ix{cx.t, r0i + q};
+          if (!ix.none()) f(q, ix.off(), cx.ky0 + ix.lane(), (r0i + q) % 2 == EPAR);
+        }
+      };
+      constexpr int se = EULA ? SF_EH : SF_EZ;
+      each([&](int q, int o, unsigned j, bool) {
         if constexpr (DYN) {
           su[q] = at32(Ys_in + 0 * sp + o, j);
           sv[q] = at32(Ys_in + 1 * sp + o, j);
           sh[q] = at32(Ys_in + 2 * sp + o, j);
         }
-        rk4_load<KS>(Y + o, YL + o, A + o, j, y[q], lo[q], a[q]);
-        if constexpr (EULA || EULB) {
-          const bool acc = (r0i + q) % 2 == EPAR;
-          if (eul && (SRCG || acc)) {
-            if constexpr (EULA) {
-              sh[q] = at32(Ys_in + 2 * sp + o, j);
-            } else {
-              su[q] = at32(Ys_in + 0 * sp + o, j);
-              sv[q] = at32(Ys_in + 1 * sp + o, j);
+        y[q] = at32(Y + o, j);
+      });
+      if (acc1) each([&](int q, int o, unsigned j, bool) { a[q] = at32(A + o, j); });
+      if constexpr (std::is_same<TS, float>::value) {
+        if (acc3) each([&](int q, int o, unsigned j, bool) { lo[q] = at32(YL + o, j); });
+      }
+      if constexpr (EULA || EULB) {
+        if (eul) {
+          each([&](int q, int o, unsigned j, bool acc) {
+            if (SRCG || acc) {
+              if constexpr (EULA) {
+                sh[q] = at32(Ys_in + 2 * sp + o, j);
+              } else {
+                su[q] = at32(Ys_in + 0 * sp + o, j);
+                sv[q] = at32(Ys_in + 1 * sp + o, j);
+              }
             }
-          }
-          if (eul && acc) {
-            constexpr int se = EULA ? SF_EH : SF_EZ;
-            rk4_load<KS, T>(P.Yr + se * sp + o, P.Yl + se * sp + o, P.Ar + se * sp + o, j, ey[q], el[q], ea[q]);
+            if (acc) ey[q] = at32(P.Yr + se * sp + o, j);
+          });
+          if (acc1) each([&](int q, int o, unsigned j, bool acc) { if (acc) ea[q] = at32(P.Ar + se * sp + o, j); });
+          if constexpr (std::is_same<T, float>::value) {
+            if (acc3) each([&](int q, int o, unsigned j, bool acc) { if (acc) el[q] = at32(P.Yl + se * sp + o, j); });
           }
         }
       }
     };
     cplx<T> r0[E];  // the transformed right-hand side
+    // kind: the stage's (rk4v)
     auto update = [&](auto kind, auto eulc, int r0i) {
       constexpr int KS = decltype(kind)::value;
       constexpr bool eul = decltype(eulc)::value;
@@ -1444,7 +1450,7 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
       }
     };
     if constexpr (PRE) {
-      with_kind([&](auto kind, auto eulc) { load(kind, eulc, 0); });
+      load(!ph.gen, stage >= 1, stage == 3, 0);
       sched_fence();
     }
     // the transformed products; the dynamics groups' two inputs as one spectrum:
@@ -1476,7 +1482,8 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
 #pragma unroll
       for (int r0i = 0; r0i < E; r0i += RB) {
         if constexpr (!PRE) {
-          load(kind, eulc, r0i);
+          constexpr int KS = decltype(kind)::value;
+          load(decltype(eulc)::value, KS >= 1, KS == 3, r0i);
           sched_fence();  // the batch's loads together, and none of the next one's with them
         }
         update(kind, eulc, r0i);
@@ -1542,9 +1549,11 @@ __device__ __forceinline__ void columns_body(const StepPtrs<T>& P, const Phys& p
 // inputs and the other stage-value buffer.  A launch of one kind alone is the same
 // kernel with no blocks of the other.  Measured per step, three passes -> two
 // launches: 64^2 float64 59.1 -> 44.4 us, 128^2 float32 62.2 -> 53.9, 192^2 float32
-// 99.6 -> 67.8, 256^2 float64 100.4 -> 96.7, 384^2 float32 141 -> 116.  From 512^2 on
-// the passes fill the chip by themselves and the larger of the two parts' registers
-// and LDS costs both (merged, 512^2 float32 130.6 -> 139.3, 1024^2 346 -> 366).
+// 99.6 -> 67.8, 256^2 float64 100.4 -> 96.7, 384^2 float32 141 -> 116 (41.2, 49.4,
+// 68.7, 87.8 and 105 with the state's loads in one straight line and the tiles
+// tuned).  From 512^2 on the passes fill the chip by themselves and the larger of
+// the two parts' registers and LDS costs both (merged, 512^2 float32 130.6 -> 139.3,
+// 127.7 with narrow tiles; 1024^2 346 -> 366).
 template <typename T, int N>
 __host__ __device__ constexpr bool stage_merged() { return N < 512; }
 
@@ -1567,7 +1576,7 @@ using StageB = StageGeo<T, N, W, RhsGeo<T, N>::THREADS, RhsGeo<T, N>::LDS>;
 // fill the chip, they keep their whole state in registers.
 template <typename T, int N>
 __host__ __device__ constexpr int col_waves() {
-  return N >= 1024 ? (sizeof(T) == 4 ? 4 : 2) : (sizeof(T) == 4 ? 2 : 1);
+  return N >= 1024 ? (sizeof(T) == 4 ? 4 : 2) : (sizeof(T) == 4 || N == 512 ? 2 : 1);
 }
 
 // the column pass (grid = (column tiles, group slots)), slots from slot0 on
