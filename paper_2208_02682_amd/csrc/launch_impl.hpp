@@ -136,7 +136,7 @@ void launch_rows_mom(RunView& r, double sval) {
 // the rows pass of strategy 2 alone
 template <typename T, int N>
 void launch_rows_rhs(RunView& r, double sval) {
-  const dim3 g = coop_grid<T, N>(), b(RhsGeo<T, N>::THREADS);
+  const dim3 g = coop_grid<T, N>(), b(r.cubic ? RhsGeo<T, N>::CUB_THREADS : RhsGeo<T, N>::THREADS);
   if (r.cubic) {
     hipLaunchKernelGGL((k_rows_rhs<T, N, true>), g, b, 0, r.stream, step_ptrs<T>(r), sval, r.sched.remap);
   } else if constexpr (stage_merged<T, N>()) {
@@ -299,7 +299,7 @@ void launch_batch_step_t(hipStream_t st, const RunDesc<T>* desc, int nruns, bool
   const int rm = sc.remap;
   dim3 gr = coop_grid<T, N>();  // one pass per launch: blockIdx.z selects the run
   gr.z = nruns;
-  const dim3 b1(DynGeo<T, N>::THREADS), b2(RhsGeo<T, N>::THREADS), bm(MomGeo<T, N>::THREADS);
+  const dim3 b1(DynGeo<T, N>::THREADS), b2(cubic ? RhsGeo<T, N>::CUB_THREADS : RhsGeo<T, N>::THREADS), bm(MomGeo<T, N>::THREADS);
   auto launch_mom = [&](int stage) {
     if (!mom) return;
     if (cubic) hipLaunchKernelGGL((k_rows_mom_b<T, N, true>), gr, bm, 0, st, desc, stage, rm);

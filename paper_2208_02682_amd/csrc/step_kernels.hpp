@@ -693,14 +693,20 @@ __global__ void __launch_bounds__((DynGeo<T, N>::THREADS), (DynGeo<T, N>::min_wa
 //   u(x+xi) - w - (w . grad) xi   (both components, eq. (4.5a)),
 //   f(x+xi) - w . grad g-bar      (eq. (4.5b))
 // each wave forms its own component's gradient terms; waves 1 and 3 gather their
-// pair, and with the sixteen corners of the cubic gathers waves 2 and 0 take half of
-// the points (bilinear ones: 128^2 float32 62.6 us per step whole, 64.4 in halves);
-// waves 2 and 0 hand theirs to waves 1 and 3, which forward-transform the pair.
+// pair; waves 2 and 0 hand theirs to waves 1 and 3, which forward-transform the pair.
+// The sixteen corners of the cubic gathers have waves of their own (GATHER_WAVES),
+// half of the points of a pair each, beside the second transform and the products;
+// rows exchanged in parts have no LDS to spare for that, there waves 2 and 0 take
+// half of their pair's points.  With the momentum rows' shared gathers, both passes
+// per stage: 384^2 float32 40.7 -> 22.3 us, 192^2 float64 40.8 -> 25.3, 64^2 float64
+// 12.4 -> 11.7 (bilinear gathers stay whole: 128^2 float32 62.6 us per
+// step whole, 64.4 in halves).
 // w = xi / (t - tau) is the partial-mean velocity (u / 2 at t = tau).
 template <typename T, int N>
 struct RhsGeo : CoopGeo<T, N> {
   using G = CoopGeo<T, N>;
-  static constexpr int WAVES = 4, THREADS = 64 * WAVES;
+  static constexpr int GATHER_WAVES = G::SPLIT ? 0 : 4;  // of cubic gathers
+  static constexpr int WAVES = 4, THREADS = 64 * WAVES, CUB_THREADS = 64 * (WAVES + GATHER_WAVES);
   static constexpr int BUFS = G::SPLIT ? 6 : 5;  // four transform buffers, then xi
   static constexpr int LDS = BUFS * G::WR * G::RB;
   // registers for this many resident waves per SIMD
@@ -713,7 +719,8 @@ template <typename T, int N, bool CUB, bool SPOS>
 __device__ __forceinline__ void rhs_products(const P4<T>* __restrict__ F, double s, int y, int t, int w,
                                              const SharedPair<T, CoopGeo<T, N>::SPLIT>& XI,
                                              cplx<T> (&z)[fft_E<N>()], T* pair, cplx<T>* half) {
-  constexpr int E = fft_E<N>(), NT = N / E, H = CUB ? E / 2 : E;
+  // points that waves 1 and 3 gather
+  constexpr int E = fft_E<N>(), NT = N / E, H = !CUB ? E : (RhsGeo<T, N>::GATHER_WAVES ? 0 : E / 2);
   constexpr int GG = gather_points<N, CUB>(H);
   const T inv_s = SPOS ? T(1.0 / s) : T(0);
   const unsigned at = (unsigned)(y * N);
@@ -750,7 +757,7 @@ __device__ __forceinline__ void rhs_products(const P4<T>* __restrict__ F, double
   } else {
 #pragma unroll
     for (int e = 0; e < E; ++e) pair[t + NT * e] = z[e].x;
-    if constexpr (H == E) return;
+    if constexpr (H == E || H == 0) return;
 #pragma unroll
     for (int e0 = H; e0 < E; e0 += GG) {
 #pragma unroll
@@ -778,6 +785,32 @@ __device__ __forceinline__ void rows_rhs_body(const StepPtrs<T>& P, double s, in
   constexpr Dims d = dims_of<N>();
   constexpr size_t rf = d.rowfield_elems();
   const unsigned row = (unsigned)y * (unsigned)d.NKXP;
+
+  // The gather waves leave a pair for wave q = 1 or 3: first components behind the N
+  // values that waves 2 and 0 hand over in q's buffer, second ones in wave 2's (which
+  // transforms nothing more, so neither q overwrites what the other still reads).
+  constexpr bool GW = CUB && G::GATHER_WAVES > 0;
+  auto gathered = [&](int q) { return SharedPair<T, true>{buf(q) + N, buf(2) + (q == 3 ? N : 0)}; };
+  if constexpr (GW) {
+    if (w >= G::WAVES) {
+      __syncthreads();  // xi is there, and waves 1 to 3 are done with their buffers
+      constexpr int H = E / 2, GG = gather_points<N, CUB>(H);
+      const int pair = (w >> 1) & 1, e1 = (w & 1) * H;
+      const SharedPair<T, true> to = gathered(2 * pair + 1);
+#pragma unroll
+      for (int e0 = 0; e0 < H; e0 += GG) {
+#pragma unroll
+        for (int e = e0; e < e0 + GG; ++e) {
+          const int x = t + NT * (e1 + e);
+          const cplx<T> xi = XI.get(x);
+          to.put(x, gather_pair<T, N, CUB>(P.uvhz, pair, x, y, xi.x, xi.y));
+        }
+        sched_fence();
+      }
+      __syncthreads();
+      return;
+    }
+  }
 
   cplx<T> z[E];
   if (w == 0) {
@@ -807,7 +840,10 @@ __device__ __forceinline__ void rows_rhs_body(const StepPtrs<T>& P, double s, in
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     z[e].y = z[e].y + mine[t + NT * e];
-    if (CUB && e >= E / 2) {
+    if constexpr (GW) {
+      const cplx<T> g = gathered(w).get(t + NT * e);
+      z[e] = {z[e].x + g.x, z[e].y + g.y};
+    } else if (CUB && e >= E / 2) {
       const cplx<T> g = half[t + NT * (e - E / 2)];
       z[e] = {z[e].x + g.x, z[e].y + g.y};
     }
@@ -819,7 +855,7 @@ __device__ __forceinline__ void rows_rhs_body(const StepPtrs<T>& P, double s, in
 
 // CUB: cubic instead of bilinear strategy-2 gathers
 template <typename T, int N, bool CUB>
-__global__ void __launch_bounds__((RhsGeo<T, N>::THREADS), (RhsGeo<T, N>::min_waves(CUB)))
+__global__ void __launch_bounds__((CUB ? RhsGeo<T, N>::CUB_THREADS : RhsGeo<T, N>::THREADS), (RhsGeo<T, N>::min_waves(CUB)))
     k_rows_rhs(StepPtrs<T> P, double s, int remap) {
   __shared__ __align__(16) T lds[RhsGeo<T, N>::LDS];
   int rowblock, unused, z;
@@ -835,9 +871,10 @@ __global__ void __launch_bounds__((RhsGeo<T, N>::THREADS), (RhsGeo<T, N>::min_wa
 // --------------------------------------------------------------------------
 // Six waves: wave 0 inverse-transforms xi and wave 1 g (both shared), waves 2 and
 // 3 d_x (xi_x, xi_y) and d_y (xi_x, xi_y), waves 4 and 5 grad g_x and grad g_y.
-// Waves 2 and 3 gather u at x + xi and form
-//   u_i + sum_j (u_j - g_j / s) d_i xi_j,   waves 4 and 5  -w . grad g_i;
-// wave 2 adds the halves of both components and forward-transforms the pair.
+// Waves 0 to 3 gather u at a quarter of the points x + xi each and share it, while
+// waves 4 and 5 form -w . grad g_i; then waves 2 and 3 form
+//   u_i + sum_j (u_j - g_j / s) d_i xi_j,
+// and wave 2 adds the halves of both components and forward-transforms the pair.
 template <typename T, int N>
 struct MomGeo : CoopGeo<T, N> {
   using G = CoopGeo<T, N>;
@@ -858,6 +895,7 @@ __device__ __forceinline__ void rows_mom_body(const StepPtrs<T>& P, double s, in
   const int y = rowblock * WR + g;
   auto buf = [&](int i) { return lds + (i * WR + g) * RB; };
   const SharedPair<T, SPLIT> XI{buf(0), buf(SPLIT ? 6 : 0)}, GM{buf(1), buf(SPLIT ? 7 : 1)};
+  const SharedPair<T, SPLIT> U{buf(2), buf(SPLIT ? 3 : 2)};  // their own transforms are done by then
   T* mine = buf(w);
   constexpr Dims d = dims_of<N>();
   constexpr size_t rf = d.rowfield_elems();
@@ -884,22 +922,20 @@ __device__ __forceinline__ void rows_mom_body(const StepPtrs<T>& P, double s, in
   __syncthreads();
   const bool spos = s > 0.0;
   const T inv_s = spos ? T(1.0 / s) : T(0);
-  if (w == 2 || w == 3) {
-    constexpr int GG = gather_points<N, CUB>(E);
+  if (w < 4) {
+    constexpr int Q = E / 4, GG = gather_points<N, CUB>(Q);
+    static_assert(E % 4 == 0, "four waves gather");
 #pragma unroll
-    for (int e0 = 0; e0 < E; e0 += GG) {
+    for (int e0 = 0; e0 < Q; e0 += GG) {
 #pragma unroll
       for (int e = e0; e < e0 + GG; ++e) {
-        const int x = t + NT * e;
-        const cplx<T> xi = XI.get(x), gm = GM.get(x);
-        const cplx<T> u = gather_pair<T, N, CUB>(F, 0, x, y, xi.x, xi.y);
-        const T gx = spos ? gm.x * inv_s : T(0), gy = spos ? gm.y * inv_s : T(0);
-        const T ui = (w == 2) ? u.x : u.y;
-        z[e].x = ui + ((u.x - gx) * z[e].x + (u.y - gy) * z[e].y);
+        const int x = t + NT * (w * Q + e);
+        const cplx<T> xi = XI.get(x);
+        U.put(x, gather_pair<T, N, CUB>(F, 0, x, y, xi.x, xi.y));
       }
       sched_fence();
     }
-  } else if (w >= 4) {
+  } else {
     const unsigned at = (unsigned)(y * N);
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -910,18 +946,27 @@ __device__ __forceinline__ void rows_mom_body(const StepPtrs<T>& P, double s, in
         const P4<T> q = at32(F, at + x);
         v = {T(0.5) * q.u, T(0.5) * q.v};
       }
-      z[e].x = -(v.x * z[e].x + v.y * z[e].y);
+      mine[x] = -(v.x * z[e].x + v.y * z[e].y);
       if (e % 4 == 3) sched_fence();
     }
   }
-  // every wave but 2 leaves its half as real values in its own buffer
-  if (w >= 3) {
+  __syncthreads();
+  T* r3 = buf(0);  // wave 3's half: xi has been read
+  if (w == 2 || w == 3) {
 #pragma unroll
-    for (int e = 0; e < E; ++e) mine[t + NT * e] = z[e].x;
+    for (int e = 0; e < E; ++e) {
+      const int x = t + NT * e;
+      const cplx<T> u = U.get(x), gm = GM.get(x);
+      const T gx = spos ? gm.x * inv_s : T(0), gy = spos ? gm.y * inv_s : T(0);
+      const T ui = (w == 2) ? u.x : u.y;
+      z[e].x = ui + ((u.x - gx) * z[e].x + (u.y - gy) * z[e].y);
+      if (w == 3) r3[x] = z[e].x;
+      if (e % 4 == 3) sched_fence();
+    }
   }
   __syncthreads();
   if (w != 2) return;
-  const T *r3 = buf(3), *r4 = buf(4), *r5 = buf(5);
+  const T *r4 = buf(4), *r5 = buf(5);
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const int x = t + NT * e;
@@ -1682,7 +1727,7 @@ __global__ void __launch_bounds__((DynGeo<T, N>::THREADS), (DynGeo<T, N>::min_wa
 }
 
 template <typename T, int N, bool CUB>
-__global__ void __launch_bounds__((RhsGeo<T, N>::THREADS), (RhsGeo<T, N>::min_waves(CUB)))
+__global__ void __launch_bounds__((CUB ? RhsGeo<T, N>::CUB_THREADS : RhsGeo<T, N>::THREADS), (RhsGeo<T, N>::min_waves(CUB)))
     k_rows_rhs_b(const RunDesc<T>* __restrict__ runs, int stage, int remap) {
   __shared__ __align__(16) T lds[RhsGeo<T, N>::LDS];
   int rowblock, unused, z;
