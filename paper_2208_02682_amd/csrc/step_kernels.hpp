@@ -695,7 +695,7 @@ __global__ void __launch_bounds__((DynGeo<T, N>::THREADS), (DynGeo<T, N>::min_wa
 // each wave forms its own component's gradient terms; waves 1 and 3 gather their
 // pair; waves 2 and 0 hand theirs to waves 1 and 3, which forward-transform the pair.
 // The sixteen corners of the cubic gathers have waves of their own (GATHER_WAVES),
-// half of the points of a pair each, beside the second transform and the products;
+// an even share of a pair's points each, beside the second transform and the products;
 // rows exchanged in parts have no LDS to spare for that, there waves 2 and 0 take
 // half of their pair's points.  With the momentum rows' shared gathers, both passes
 // per stage: 384^2 float32 40.7 -> 22.3 us, 192^2 float64 40.8 -> 25.3, 64^2 float64
@@ -705,7 +705,11 @@ __global__ void __launch_bounds__((DynGeo<T, N>::THREADS), (DynGeo<T, N>::min_wa
 template <typename T, int N>
 struct RhsGeo : CoopGeo<T, N> {
   using G = CoopGeo<T, N>;
-  static constexpr int GATHER_WAVES = G::SPLIT ? 0 : 4;  // of cubic gathers
+  // of cubic gathers; with twelve values per lane eight (4 -> 8 waves, a step with
+  // momentum: 384^2 float32 186.6 -> 183.3 us, 192^2 float32 143.3 -> 139.0; bilinear
+  // gathers on four waves of their own: 192^2 float32 68.8 -> 65.4, but 384^2 float64
+  // 145.6 -> 155.7)
+  static constexpr int GATHER_WAVES = G::SPLIT ? 0 : (G::E == 12 ? 8 : 4);
   static constexpr int WAVES = 4, THREADS = 64 * WAVES, CUB_THREADS = 64 * (WAVES + GATHER_WAVES);
   static constexpr int BUFS = G::SPLIT ? 6 : 5;  // four transform buffers, then xi
   static constexpr int LDS = BUFS * G::WR * G::RB;
@@ -794,8 +798,8 @@ __device__ __forceinline__ void rows_rhs_body(const StepPtrs<T>& P, double s, in
   if constexpr (GW) {
     if (w >= G::WAVES) {
       __syncthreads();  // xi is there, and waves 1 to 3 are done with their buffers
-      constexpr int H = E / 2, GG = gather_points<N, CUB>(H);
-      const int pair = (w >> 1) & 1, e1 = (w & 1) * H;
+      constexpr int PARTS = G::GATHER_WAVES / 2, H = E / PARTS, GG = gather_points<N, CUB>(H);
+      const int i = w - G::WAVES, pair = i % 2, e1 = i / 2 * H;
       const SharedPair<T, true> to = gathered(2 * pair + 1);
 #pragma unroll
       for (int e0 = 0; e0 < H; e0 += GG) {
