@@ -337,7 +337,7 @@ lm_status lm_batch_destroy(lm_batch* b);
  *   xcd_order  1: blocks renumbered so that each of the 8 XCDs (own L2)
  *              receives a contiguous range of row blocks / column tiles with
  *              all tasks of each (the default); 0: hardware dispatch order;
- *   streams    1: the three passes of an RK4 stage run in order on the run's
+ *   streams    1: the launches of an RK4 stage run in order on the run's
  *              stream (the default); 2: the stage's dependency graph runs on
  *              two streams (the run's and one of its own): the dynamics rows
  *              pass and the column groups of u, v, h on one, the mean

@@ -1,6 +1,7 @@
 // Hot-path kernels of one RK4 stage (templated on the transform precision T and N).
 //
-// One stage of the coupled system is three launches:
+// One stage of the coupled system is three passes (two launches on small grids,
+// see stage_merged):
 //
 //  rows_dyn   per grid row: inverse row transforms of the column-pass outputs to
 //             physical u, v, eta = h - H, zeta (zeta = dv/dx - du/dy); stores
@@ -879,6 +880,8 @@ __global__ void __launch_bounds__((CUB ? RhsGeo<T, N>::CUB_THREADS : RhsGeo<T, N
 // waves 4 and 5 form -w . grad g_i; then waves 2 and 3 form
 //   u_i + sum_j (u_j - g_j / s) d_i xi_j,
 // and wave 2 adds the halves of both components and forward-transforms the pair.
+// (Gathered on waves 2 and 3, every point twice: both strategy-2 passes of a cubic
+// run, us per stage, 1024^2 float32 79 -> 67, float64 259 -> 202.)
 template <typename T, int N>
 struct MomGeo : CoopGeo<T, N> {
   using G = CoopGeo<T, N>;
