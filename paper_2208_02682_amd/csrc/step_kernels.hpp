@@ -1193,10 +1193,13 @@ __device__ __forceinline__ void column_forward(const ColCtx<T, N, C>& cx, const 
 
 // whether a block's two inverse transforms (a field and its i ky version) run side
 // by side in two sets of buffers: on the grids whose columns are bound by latency,
-// where a second set leaves room for two blocks per CU
+// where a second set leaves room for two blocks per CU.  (Not at 512^2, whose blocks
+// fill the chip: one set and four waves per SIMD instead of two sets and three, with
+// the state's loads after the transforms, float32 130.7 -> 127.9 us per step, float64
+// 182.6 -> 173.0.)
 template <typename T, int N, int C>
 __host__ __device__ constexpr bool col_dual() {
-  return fft_E<N>() <= 12 && 2 * C * col_buf(N) * sizeof(cplx<T>) <= 80 * 1024;
+  return (fft_E<N>() == 4 || fft_E<N>() == 12) && 2 * C * col_buf(N) * sizeof(cplx<T>) <= 80 * 1024;
 }
 // a column block's LDS, in values of T
 template <typename T, int N, int C>
@@ -1355,7 +1358,7 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
     // batch (stage values, state, accumulator) is issued before its first
     // store, so the batch's loads are in flight together (stores to the state
     // could alias later loads as far as the compiler knows, which would
-    // otherwise serialise the coefficients).  On the smaller grids one batch takes
+    // otherwise serialise the coefficients).  Up to 256^2 one batch takes
     // all of a lane's coefficients, and its loads are issued before the forward
     // transforms (PRE): they wait for memory once, not twice.
     // For the default averaged fields (eta, zeta) the g-tilde groups take their
@@ -1370,7 +1373,7 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
     constexpr bool SRCG = (G == CG_GTH || G == CG_GTZ);
     constexpr int EPAR = SRCG ? 0 : 1;
     const double cn = (stage == 1) ? 0.5 * ph.dt : ph.dt;
-    constexpr bool PRE = E <= 8;
+    constexpr bool PRE = E == 4;
     constexpr int RB0 = (DBL || DYN || EULA || EULB) ? 2 : 4;  // (4 and 8: spills at 16 values per lane)
     constexpr int RB = PRE ? E : ((E % RB0 == 0) ? RB0 : 4);
     static_assert(E % RB == 0, "coefficient batches");
@@ -1623,12 +1626,12 @@ using StageA = StageGeo<T, N, W, DynGeo<T, N>::THREADS, DynGeo<T, N>::LDS>;
 template <typename T, int N, int W>
 using StageB = StageGeo<T, N, W, RhsGeo<T, N>::THREADS, RhsGeo<T, N>::LDS>;
 
-// Resident waves per SIMD the column groups' registers leave room for: at 1024 in
-// float32 4 (at most 128 registers), in float64 2; on smaller grids, which do not
+// Resident waves per SIMD the column groups' registers leave room for: from 512
+// on in float32 4 (at most 128 registers), in float64 2; on smaller grids, which do not
 // fill the chip, they keep their whole state in registers.
 template <typename T, int N>
 __host__ __device__ constexpr int col_waves() {
-  return N >= 1024 ? (sizeof(T) == 4 ? 4 : 2) : (sizeof(T) == 4 || N == 512 ? 2 : 1);
+  return N >= 512 ? (sizeof(T) == 4 ? 4 : 2) : (sizeof(T) == 4 ? 2 : 1);
 }
 
 // the column pass (grid = (column tiles, group slots)), slots from slot0 on
