@@ -132,6 +132,13 @@ __global__ void __launch_bounds__((E2DRowGeo<N>::THREADS), 2) k_e2d_rows(E2DPtrs
 // the semi-Lagrangian update.
 // ---------------------------------------------------------------------------
 constexpr int E2D_W = -1;  // tile width
+// both inverse transforms side by side up to 512^2, one more size than the columns of
+// a run: with this few blocks latency bounds them (512^2, one after the other, an
+// interval of 15 steps 1061 -> 1204 us)
+template <typename T, int N, int C>
+__host__ __device__ constexpr bool e2d_dual() {
+  return fft_E<N>() <= 12 && 2 * C * col_buf(N) * sizeof(cplx<T>) <= 80 * 1024;
+}
 template <int N>
 __global__ void __launch_bounds__((col_threads<N, E2D_W>()), 1)
     k_e2d_columns(E2DPtrs P, int stage, int sl_blocks, E2DSl sl) {
@@ -141,7 +148,7 @@ __global__ void __launch_bounds__((col_threads<N, E2D_W>()), 1)
   constexpr Dims d = dims_of<N>();
   constexpr size_t sp = d.spec_elems(), rf = d.rowfield_elems();
   constexpr int TILES = (d.NKX + C - 1) / C;
-  __shared__ __align__(16) T lds[col_lds<T, N, C>()];
+  __shared__ __align__(16) T lds[col_lds<T, N, C, e2d_dual<T, N, C>()>()];
   int b = blockIdx.x;
   if (b < sl_blocks) {
     sl_update<N>(sl, b * col_threads<N, E2D_W>() + (int)threadIdx.x);
@@ -208,7 +215,7 @@ __global__ void __launch_bounds__((col_threads<N, E2D_W>()), 1)
     }
   }
   cplx<T>* out = P.IC + (psi ? EI_PSI : EI_Z + 2 * q) * rf;
-  column_inverse<T, N, C, true>(cx, S, out, out + rf, P.tw);
+  column_inverse<T, N, C, true, e2d_dual<T, N, C>()>(cx, S, out, out + rf, P.tw);
 }
 
 template <int N>

@@ -1202,14 +1202,14 @@ __host__ __device__ constexpr bool col_dual() {
   return (fft_E<N>() == 4 || fft_E<N>() == 12) && 2 * C * col_buf(N) * sizeof(cplx<T>) <= 80 * 1024;
 }
 // a column block's LDS, in values of T
-template <typename T, int N, int C>
+template <typename T, int N, int C, bool DUAL = col_dual<T, N, C>()>
 __host__ __device__ constexpr int col_lds() {
-  return (col_dual<T, N, C>() ? 2 : 1) * C * ColCtx<T, N, C>::CS;
+  return (DUAL ? 2 : 1) * C * ColCtx<T, N, C>::CS;
 }
 
 // inverse column transforms of values S at k = t + NT r (already zero outside
 // the mask) to the intermediate field dst and, with WITH_DY, of i ky S to dst_dy
-template <typename T, int N, int C, bool WITH_DY>
+template <typename T, int N, int C, bool WITH_DY, bool DUAL = col_dual<T, N, C>()>
 __device__ __forceinline__ void column_inverse(const ColCtx<T, N, C>& cx, const cplx<T> (&S)[fft_E<N>()],
                                                cplx<T>* dst, cplx<T>* dst_dy, const cplx<T>* __restrict__ tw) {
   using X = ColCtx<T, N, C>;
@@ -1223,7 +1223,7 @@ __device__ __forceinline__ void column_inverse(const ColCtx<T, N, C>& cx, const 
   };
   // no barrier: since the last block-wide tile access (whose last barrier every
   // wave has passed) only this lane group has touched its buffer
-  if constexpr (WITH_DY && col_dual<T, N, C>()) {
+  if constexpr (WITH_DY && DUAL) {
     cplx<T> v[2][E];
 #pragma unroll
     for (int r = 0; r < E; ++r) v[0][r] = value(r, false), v[1][r] = value(r, true);
