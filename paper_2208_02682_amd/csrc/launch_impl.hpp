@@ -288,8 +288,9 @@ hipError_t launch_steps_profiled(RunView& r, int nsteps, double* ms) {
   return launch_steps_profiled_t<double, N>(r, nsteps, ms);
 }
 
-// one RK4 step of every run of one (N, precision) group, the launches of
-// launch_steps_t with all runs' blocks in each
+// one RK4 step of every run of one (N, precision) group, all runs' blocks in each
+// launch: up to batch_merged_runs() runs the launches of launch_steps_t, beyond them
+// the passes one by one, each a kernel of its own
 template <typename T, int N>
 void launch_batch_step_t(hipStream_t st, const RunDesc<T>* desc, int nruns, bool cubic, bool mom, bool gen,
                          const Sched& sc) {
@@ -308,44 +309,46 @@ void launch_batch_step_t(hipStream_t st, const RunDesc<T>* desc, int nruns, bool
   with_tile<T, N>(sc.tile, [&](auto w) {
     constexpr int W = decltype(w)::value;
     if constexpr (stage_merged<T, N>()) {
-      using A = StageA<T, N, W>;
-      using B = StageB<T, N, W>;
-      const int n1 = col_first_groups(gp), n2 = col_second_groups(gp);
-      auto launch_ab = [&](bool b, bool rows, int stage, int cstage, int first, int count) {
-        const int nc = (count * A::TILES * nruns + 7) / 8 * 8, nr = rows ? A::ROWS * nruns : 0, ns = count > 0 ? count : 1;
-        if (b) hipLaunchKernelGGL((k_stage_b_b<T, N, W>), dim3(nc + nr), dim3(B::THREADS), 0, st, desc, nruns, stage,
+      if (nruns <= batch_merged_runs<T, N>()) {
+        using A = StageA<T, N, W>;
+        using B = StageB<T, N, W>;
+        const int n1 = col_first_groups(gp), n2 = col_second_groups(gp);
+        auto launch_ab = [&](bool b, bool rows, int stage, int cstage, int first, int count) {
+          const int nc = (count * A::TILES * nruns + 7) / 8 * 8, nr = rows ? A::ROWS * nruns : 0, ns = count > 0 ? count : 1;
+          if (b) hipLaunchKernelGGL((k_stage_b_b<T, N, W>), dim3(nc + nr), dim3(B::THREADS), 0, st, desc, nruns, stage,
+                                    cstage, first, ns, nc, nr, rm);
+          else hipLaunchKernelGGL((k_stage_a_b<T, N, W>), dim3(nc + nr), dim3(A::THREADS), 0, st, desc, nruns, stage,
                                   cstage, first, ns, nc, nr, rm);
-        else hipLaunchKernelGGL((k_stage_a_b<T, N, W>), dim3(nc + nr), dim3(A::THREADS), 0, st, desc, nruns, stage,
-                                cstage, first, ns, nc, nr, rm);
-      };
-      if (!gen && !cubic) {
-        for (int stage = 0; stage < 4; ++stage) {
-          launch_ab(false, true, stage, stage - 1, n1, stage > 0 ? n2 : 0);
-          launch_ab(true, true, stage, stage, 0, n1);
-          launch_mom(stage);
+        };
+        if (!gen && !cubic) {
+          for (int stage = 0; stage < 4; ++stage) {
+            launch_ab(false, true, stage, stage - 1, n1, stage > 0 ? n2 : 0);
+            launch_ab(true, true, stage, stage, 0, n1);
+            launch_mom(stage);
+          }
+          launch_ab(true, false, 0, 3, n1, n2);
+          return;
         }
-        launch_ab(true, false, 0, 3, n1, n2);
+        for (int stage = 0; stage < 4; ++stage) {
+          if (gen) hipLaunchKernelGGL((k_rows_dyn_b<T, N, true>), gr, b1, 0, st, desc, stage, rm);
+          else launch_ab(false, true, stage, 0, 0, 0);
+          if (cubic) hipLaunchKernelGGL((k_rows_rhs_b<T, N, true>), gr, b2, 0, st, desc, stage, rm);
+          else launch_ab(true, true, stage, 0, 0, 0);
+          launch_mom(stage);
+          launch_ab(true, false, 0, stage, 0, n1 + n2);
+        }
         return;
       }
-      for (int stage = 0; stage < 4; ++stage) {
-        if (gen) hipLaunchKernelGGL((k_rows_dyn_b<T, N, true>), gr, b1, 0, st, desc, stage, rm);
-        else launch_ab(false, true, stage, 0, 0, 0);
-        if (cubic) hipLaunchKernelGGL((k_rows_rhs_b<T, N, true>), gr, b2, 0, st, desc, stage, rm);
-        else launch_ab(true, true, stage, 0, 0, 0);
-        launch_mom(stage);
-        launch_ab(true, false, 0, stage, 0, n1 + n2);
-      }
-    } else {
-      for (int stage = 0; stage < 4; ++stage) {
-        if (gen) hipLaunchKernelGGL((k_rows_dyn_b<T, N, true>), gr, b1, 0, st, desc, stage, rm);
-        else hipLaunchKernelGGL((k_rows_dyn_b<T, N, false>), gr, b1, 0, st, desc, stage, rm);
-        if (cubic) hipLaunchKernelGGL((k_rows_rhs_b<T, N, true>), gr, b2, 0, st, desc, stage, rm);
-        else hipLaunchKernelGGL((k_rows_rhs_b<T, N, false>), gr, b2, 0, st, desc, stage, rm);
-        launch_mom(stage);
-        dim3 g3 = col_grid<N, W>(Dims::make(N), col_groups(gp));
-        g3.z = nruns;
-        hipLaunchKernelGGL((k_columns_b<T, N, W>), g3, dim3(col_threads<N, W>()), 0, st, desc, stage, rm);
-      }
+    }
+    for (int stage = 0; stage < 4; ++stage) {
+      if (gen) hipLaunchKernelGGL((k_rows_dyn_b<T, N, true>), gr, b1, 0, st, desc, stage, rm);
+      else hipLaunchKernelGGL((k_rows_dyn_b<T, N, false>), gr, b1, 0, st, desc, stage, rm);
+      if (cubic) hipLaunchKernelGGL((k_rows_rhs_b<T, N, true>), gr, b2, 0, st, desc, stage, rm);
+      else hipLaunchKernelGGL((k_rows_rhs_b<T, N, false>), gr, b2, 0, st, desc, stage, rm);
+      launch_mom(stage);
+      dim3 g3 = col_grid<N, W>(Dims::make(N), col_groups(gp));
+      g3.z = nruns;
+      hipLaunchKernelGGL((k_columns_b<T, N, W>), g3, dim3(col_threads<N, W>()), 0, st, desc, stage, rm);
     }
   });
 }

@@ -1612,6 +1612,26 @@ __device__ __forceinline__ void columns_body(const StepPtrs<T>& P, const Phys& p
 template <typename T, int N>
 __host__ __device__ constexpr bool stage_merged() { return N < 512; }
 
+// Runs of a batched group up to which its launches are merged.  Merging pays while a
+// pass leaves the chip idle; once the row blocks fill it, they only lose by the column
+// groups' registers (rows of 64^2 to 256^2 take about 50 VGPRs in float32 and 75 in
+// float64 in kernels of their own, 118 and 175 here).  Those registers leave 4096
+// (float32) or 2048 (float64) waves resident, 640 or 320 blocks of launch A's six row
+// waves, and there both sides measure the same.  With twelve values per lane the
+// passes apart are less efficient: 8 and 14 runs.  A step, merged / apart, us: 64^2
+// float64 12 runs 73 / 80, 64 runs 237 / 190; 128^2 float32 8 runs 90 / 94, 12 runs
+// 127 / 123, 64 runs 470 / 419; 128^2 float64 5 runs 112 / 120, 64 runs 921 / 742;
+// 192^2 float64 12 runs 311 / 336, 64 runs 1630 / 1481; 256^2 float32 2 runs 103 / 105,
+// 12 runs 352 / 306, 64 runs 2190 / 1870; 256^2 float64 1 run 111 / 113, 16 runs
+// 991 / 726, 64 runs 3945 / 2865; 384^2 float32 7 runs 382 / 399, 16 runs 1063 / 980.
+template <typename T, int N>
+__host__ __device__ constexpr int batch_merged_runs() {
+  constexpr bool f32 = sizeof(T) == 4;
+  if (!stage_merged<T, N>()) return 0;
+  if (fft_E<N>() == 12) return f32 ? 8 : 14;
+  return (f32 ? 640 : 320) / (N / CoopGeo<T, N>::WR);
+}
+
 template <typename T, int N, int W, int ROW_THREADS, int ROW_LDS>
 struct StageGeo {
   static constexpr int C = col_tile<N, W>(), COL_THREADS = col_threads<N, W>();
