@@ -118,12 +118,11 @@ void e2d_zero_means(lm_e2d* e) {
 }
 
 // the semi-Lagrangian update after step m of the interval (u, v, zeta at its end
-// are in PH), between the two sets of fields; flips the current set
+// are in PH), from the current set of fields to the other
 lm::E2DSl e2d_sl_args(lm_e2d* e, double m) {
   const size_t nn = (size_t)e->v.d.N * e->v.d.N;
   const double* PH = e->at<double>(e->PH);
   const int c = e->cur, o = c ^ 1;
-  e->cur = o;
   return lm::E2DSl{PH, PH + nn, PH + 2 * nn, e->at<double>(e->Zn[c]), e->at<double>(e->SLf[c]),
                    e->at<double>(e->SLx[c]), e->at<double>(e->SLy[c]), e->at<double>(e->SLf[o]),
                    e->at<double>(e->SLx[o]), e->at<double>(e->SLy[o]), e->at<double>(e->Zn[o]), e->dt, m,
@@ -135,40 +134,61 @@ lm::E2DSl e2d_sl_args(lm_e2d* e, double m) {
 // them, and its blocks ride in the column launch that follows; after the last
 // step a rows pass stores them and the update runs alone.  With events (a pair
 // per step) every update is a launch of its own between its pair.
+// A step counts once its update is launched too.  Until then the state it began
+// from is whole (the next step writes over it after the update only), so when a
+// launch fails the handle stays at the last step that counts.
 lm_status e2d_steps(lm_e2d* e, int nsteps, hipEvent_t* ev) {
   if (nsteps <= 0) return LM_OK;
   lm::RunView& v = e->v;
   const int N = v.d.N;
   lm::E2DPtrs P = e2d_ptrs(e);
-  e2d_prologue(e, P);
+  bool pending = false;  // the spectral state is a step ahead of the update
+  auto counts = [&] {
+    e->cur ^= 1;
+    e->n += 1;
+    pending = false;
+  };
   auto sl_alone = [&](double m, hipEvent_t* pair) -> lm_status {
     const lm::E2DSl a = e2d_sl_args(e, m);
     if (pair) HIP_TRY(hipEventRecord(pair[0], v.stream));
     LM_DISPATCH_N(N, lm::launch_e2d_sl, v.stream, a);
     if (pair) HIP_TRY(hipEventRecord(pair[1], v.stream));
-    return LM_OK;
+    const lm_status st = check_launch();
+    if (st == LM_OK) counts();
+    return st;
   };
-  lm_status st;
-  for (int k = 0; k < nsteps; ++k) {
-    const double m = double(e->n - e->n_tau);
-    const double s0 = m * e->dt;
-    LM_DISPATCH_N(N, lm::launch_e2d_rows, v.stream, P, s0, k > 0 ? 1 : 0, 1);
-    if (k > 0 && !ev) {
-      const lm::E2DSl a = e2d_sl_args(e, m - 1.0);
-      LM_DISPATCH_N(N, lm::launch_e2d_columns, v.stream, P, 0, &a);
-    } else {
-      if (k > 0 && (st = sl_alone(m - 1.0, ev + 2 * (k - 1))) != LM_OK) return st;
-      LM_DISPATCH_N(N, lm::launch_e2d_columns, v.stream, P, 0, nullptr);
+  auto steps = [&]() -> lm_status {
+    lm_status st;
+    e2d_prologue(e, P);
+    for (int k = 0; k < nsteps; ++k) {
+      const double m = double(e->n - e->n_tau) + (pending ? 1.0 : 0.0);
+      const double s0 = m * e->dt;
+      LM_DISPATCH_N(N, lm::launch_e2d_rows, v.stream, P, s0, pending ? 1 : 0, 1);
+      if (pending && !ev) {
+        const lm::E2DSl a = e2d_sl_args(e, m - 1.0);
+        LM_DISPATCH_N(N, lm::launch_e2d_columns, v.stream, P, 0, &a);
+        if ((st = check_launch()) != LM_OK) return st;
+        counts();
+      } else {
+        if (pending && (st = sl_alone(m - 1.0, ev + 2 * (k - 1))) != LM_OK) return st;
+        LM_DISPATCH_N(N, lm::launch_e2d_columns, v.stream, P, 0, nullptr);
+      }
+      LM_DISPATCH_N(N, lm::launch_e2d_rows, v.stream, P, s0 + e->dt, 0, 1);
+      LM_DISPATCH_N(N, lm::launch_e2d_columns, v.stream, P, 1, nullptr);
+      if ((st = check_launch()) != LM_OK) return st;
+      e->ycur ^= 1;
+      std::swap(P.Y, P.Yn);
+      pending = true;
     }
-    LM_DISPATCH_N(N, lm::launch_e2d_rows, v.stream, P, s0 + e->dt, 0, 1);
-    LM_DISPATCH_N(N, lm::launch_e2d_columns, v.stream, P, 1, nullptr);
-    e->ycur ^= 1;
-    std::swap(P.Y, P.Yn);
-    e->n += 1;
+    LM_DISPATCH_N(N, lm::launch_e2d_rows, v.stream, P, 0.0, 1, 0);
+    return sl_alone(double(e->n - e->n_tau), ev ? ev + 2 * (nsteps - 1) : nullptr);
+  };
+  const lm_status st = steps();
+  if (st != LM_OK) {
+    if (pending) e->ycur ^= 1;
+    e->ic_current = false;
   }
-  LM_DISPATCH_N(N, lm::launch_e2d_rows, v.stream, P, 0.0, 1, 0);
-  if ((st = sl_alone(double(e->n - e->n_tau) - 1.0, ev ? ev + 2 * (nsteps - 1) : nullptr)) != LM_OK) return st;
-  return check_launch();
+  return st;
 }
 
 }  // namespace
@@ -247,7 +267,10 @@ lm_status lm_e2d_set_vorticity(lm_e2d* e, const double* zeta, int on_device) {
   lm::SetRanges Z;
   Z.add(e->at<double>(e->Zn[e->cur]), nn * sizeof(double), PH + 2 * nn);
   lm::launch_set_ranges(v.stream, Z);
-  if ((st = check_launch()) != LM_OK) return st;
+  if ((st = check_launch()) != LM_OK) {
+    e->ic_current = false;
+    return st;
+  }
   HIP_TRY(hipStreamSynchronize(v.stream));
   e->n = e->n_tau = 0;
   e->has_state = true;
