@@ -158,11 +158,16 @@ lm_status lm_begin_interval(lm_run* run);
    LM_E_STATE before lm_set_state. */
 lm_status lm_step(lm_run* run, int32_t nsteps);
 
-/* As lm_step, but every kernel launch is bracketed by a pair of HIP events on
-   the run's stream (all enqueued back to back; one synchronisation at the end).
-   ms_avg[0..2] receive the average duration in milliseconds of the three
-   hot-path kernels: [0] rows pass of the dynamics and strategy 1, [1] rows pass
-   of strategy 2, [2] column pass (spectral assembly + RK4).
+/* The launches lm_step makes on one stream, bracketed by pairs of HIP events (all
+   enqueued back to back; one synchronisation at the end).  ms_avg[0..2] receive
+   milliseconds per RK4 stage:
+     n >= 512, cubic gathers, or other averaged fields than (h, zeta): the three
+       passes of a stage, [0] rows of the dynamics and strategy 1, [1] rows of
+       strategy 2 (and the momentum 1-form), [2] columns (spectral assembly + RK4);
+     else a stage is two launches, [0] the rows of the dynamics and strategy 1
+       with strategy 2's columns of the stage before, [1] the rows of strategy 2
+       (and the momentum 1-form) with the other columns; [2] is the launch that
+       closes the call, the last stage's strategy-2 columns, over all its stages.
    1 <= nsteps <= 4096.  Synchronous.  For measurement. */
 lm_status lm_step_profiled(lm_run* run, int32_t nsteps, double* ms_avg);
 

@@ -195,14 +195,12 @@ hipError_t launch_steps_2s(RunView& r, int nsteps) {
 // One stream.  Small grids: launches A and B of every stage (k_stage_a, k_stage_b),
 // the strategy-2 column groups of the last stage at the end; the rows of other
 // averaged fields than (h, zeta) and of cubic gathers are kernels of their own, and
-// such runs take the passes one by one, as large grids do.
-template <typename T, int N>
-void launch_steps_t(RunView& r, int nsteps) {
+// such runs take the passes one by one, as large grids do.  Every launch goes out
+// through timed(i, f): i = 0 the dynamics' and strategy 1's rows (launch A), 1 the
+// rows of strategy 2 (launch B, and the momentum rows), 2 columns alone.
+template <typename T, int N, typename F>
+void launch_steps_through(RunView& r, int nsteps, F&& timed) {
   static const double c[4] = {0.0, 0.5, 0.5, 1.0};
-  if (r.sched.streams == 2 && r.aux && nsteps > 0) {
-    (void)launch_steps_2s<T, N>(r, nsteps);  // launch errors surface through hipGetLastError
-    return;
-  }
   const int n1 = col_first_groups(r.ph), n2 = col_second_groups(r.ph);
   const bool merged = stage_merged<T, N>() && !r.ph.gen && !r.cubic;
   ColPart second;  // the strategy-2 column groups still to be launched
@@ -212,35 +210,48 @@ void launch_steps_t(RunView& r, int nsteps) {
       const double sval = (double(r.n - r.n_tau) + c[stage]) * r.ph.dt;
       if constexpr (stage_merged<T, N>()) {
         if (merged) {
-          launch_merged<T, N, false>(r, true, sval, second, r.stream);
-          launch_merged<T, N, true>(r, true, sval, ColPart{stage, 0, n1, r.ys_cur}, r.stream);
-          launch_rows_mom<T, N>(r, sval);
+          timed(0, [&] { launch_merged<T, N, false>(r, true, sval, second, r.stream); });
+          timed(1, [&] {
+            launch_merged<T, N, true>(r, true, sval, ColPart{stage, 0, n1, r.ys_cur}, r.stream);
+            launch_rows_mom<T, N>(r, sval);
+          });
           second = ColPart{stage, n1, n2, r.ys_cur};
           r.ys_cur ^= 1;
           continue;
         }
       }
-      launch_rows_dyn<T, N>(r, sval, r.stream);
-      launch_rows_rhs<T, N>(r, sval);
-      launch_rows_mom<T, N>(r, sval);
-      launch_columns_t<T, N>(r, stage);
+      timed(0, [&] { launch_rows_dyn<T, N>(r, sval, r.stream); });
+      timed(1, [&] {
+        launch_rows_rhs<T, N>(r, sval);
+        launch_rows_mom<T, N>(r, sval);
+      });
+      timed(2, [&] { launch_columns_t<T, N>(r, stage); });
     }
     r.n += 1;
   }
   if constexpr (stage_merged<T, N>()) {
-    if (second.count) launch_merged<T, N, true>(r, false, 0.0, second, r.stream);
+    if (second.count) timed(2, [&] { launch_merged<T, N, true>(r, false, 0.0, second, r.stream); });
   }
 }
 
-// The passes of launch_steps_t one by one (rows of the dynamics and strategy 1,
-// rows of strategy 2, columns), each bracketed by a pair of events on the run's
-// stream; nothing synchronises until all steps are enqueued, so the kernels run
-// back to back.  The three durations are accumulated into ms[0..2].
+template <typename T, int N>
+void launch_steps_t(RunView& r, int nsteps) {
+  if (r.sched.streams == 2 && r.aux && nsteps > 0) {
+    (void)launch_steps_2s<T, N>(r, nsteps);  // launch errors surface through hipGetLastError
+    return;
+  }
+  launch_steps_through<T, N>(r, nsteps, [](int, auto&& f) { f(); });
+}
+
+// The one-stream launches of launch_steps_t, each bracketed by a pair of events on
+// the run's stream; nothing synchronises until all steps are enqueued, so the
+// kernels run back to back.  The durations are accumulated into ms[0..2].
 template <typename T, int N>
 hipError_t launch_steps_profiled_t(RunView& r, int nsteps, double* ms) {
-  static const double c[4] = {0.0, 0.5, 0.5, 1.0};
-  const int nev = nsteps * 4 * 3 * 2;
+  const int nev = (nsteps * 4 * 3 + 1) * 2;
   std::vector<hipEvent_t> ev(nev);
+  std::vector<int> kind;  // of each pair
+  kind.reserve(nev / 2);
   hipError_t err = hipSuccess;
   int made = 0;
   // device-scope markers: no system-scope cache release around every launch
@@ -249,34 +260,22 @@ hipError_t launch_steps_profiled_t(RunView& r, int nsteps, double* ms) {
     for (int i = 0; i < made - 1; ++i) (void)hipEventDestroy(ev[i]);
     return err;
   }
-  int e = 0;
-  for (int s = 0; s < nsteps; ++s) {
-    for (int stage = 0; stage < 4; ++stage) {
-      const double sval = (double(r.n - r.n_tau) + c[stage]) * r.ph.dt;
-      // an empty kernel between one kernel's end marker and the next one's
-      // start marker absorbs the work done at kernel boundaries, so each
-      // interval covers one kernel's execution only
-      (void)hipEventRecord(ev[e++], r.stream);
-      launch_rows_dyn<T, N>(r, sval, r.stream);
-      (void)hipEventRecord(ev[e++], r.stream);
-      hipLaunchKernelGGL(k_drain<N>, dim3(1), dim3(64), 0, r.stream);
-      (void)hipEventRecord(ev[e++], r.stream);
-      launch_rows_rhs<T, N>(r, sval);
-      launch_rows_mom<T, N>(r, sval);
-      (void)hipEventRecord(ev[e++], r.stream);
-      hipLaunchKernelGGL(k_drain<N>, dim3(1), dim3(64), 0, r.stream);
-      (void)hipEventRecord(ev[e++], r.stream);
-      launch_columns_t<T, N>(r, stage);
-      (void)hipEventRecord(ev[e++], r.stream);
-      hipLaunchKernelGGL(k_drain<N>, dim3(1), dim3(64), 0, r.stream);
-    }
-    r.n += 1;
-  }
-  err = hipEventSynchronize(ev[nev - 1]);
-  for (int i = 0; i < nev && err == hipSuccess; i += 2) {
+  launch_steps_through<T, N>(r, nsteps, [&](int i, auto&& f) {
+    // an empty kernel between one kernel's end marker and the next one's start
+    // marker absorbs the work done at kernel boundaries, so each interval covers
+    // one kernel's execution only
+    const int e = 2 * (int)kind.size();
+    kind.push_back(i);
+    (void)hipEventRecord(ev[e], r.stream);
+    f();
+    (void)hipEventRecord(ev[e + 1], r.stream);
+    hipLaunchKernelGGL(k_drain<N>, dim3(1), dim3(64), 0, r.stream);
+  });
+  if (!kind.empty()) err = hipEventSynchronize(ev[2 * kind.size() - 1]);
+  for (size_t i = 0; i < kind.size() && err == hipSuccess; ++i) {
     float t = 0.f;
-    err = hipEventElapsedTime(&t, ev[i], ev[i + 1]);
-    ms[(i / 2) % 3] += t;
+    err = hipEventElapsedTime(&t, ev[2 * i], ev[2 * i + 1]);
+    ms[kind[i]] += t;
   }
   for (auto& x : ev) (void)hipEventDestroy(x);
   return err;

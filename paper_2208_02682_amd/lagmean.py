@@ -422,7 +422,8 @@ class Run:
         return ms.value
 
     def step_profiled(self, nsteps: int):
-        """Average milliseconds of (rows_dyn, rows_rhs, columns) over nsteps steps."""
+        """Milliseconds per RK4 stage of the launches of nsteps steps: (rows_dyn, rows_rhs, columns),
+        or on small grids (launch A, launch B, the call's closing columns) (lm_step_profiled)."""
         ms = (ctypes.c_double * 3)()
         _check(self.lib.lm_step_profiled(self.h, int(nsteps), ms))
         return list(ms)
