@@ -7,14 +7,11 @@
 
 namespace lm {
 
-// column tile width: 8 columns (64-byte row segments in float32), or more when a
-// transform needs fewer than 8 lanes, so that a block is at least one wavefront.
-// W = -1 / +1: half / twice that width (the alternative launch schedules; the
-// arithmetic of every column is the same whatever the width)
-__host__ __device__ constexpr int col_tile_of(int n, int w) {
-  const int base = (n / fft_E_of(n) >= 8) ? 8 : 64 / (n / fft_E_of(n));
-  return w < 0 ? base / 2 : (w > 0 ? base * 2 : base);
-}
+// column tile width: 8 columns (64-byte row segments in float32).  W = -1 / +1: half /
+// twice that width (the alternative launch schedules; the arithmetic of every column
+// is the same whatever the width).  A transform has at least 16 lanes, so that a
+// block of half the width still is whole wavefronts.
+__host__ __device__ constexpr int col_tile_of(int w) { return w < 0 ? 4 : (w > 0 ? 16 : 8); }
 __host__ __device__ constexpr int col_buf(int N) { return padded_len(N) | 1; }
 // The widths offered as schedules: those whose block would be whole wavefronts
 // (at most 1024 threads) with 16 values per lane (12 for N = 3 * 2^k), and whose

@@ -6,9 +6,8 @@
 // later stages (radices R dividing E, each lane doing E/R butterflies) exchange
 // data through the group's private LDS buffer.  On exit the spectrum is in the
 // lanes' registers (lane t: entries t + NT e) or, if asked for, in the LDS
-// buffer in natural order (padded indexing).  When a group fits in one
-// wavefront (NT <= 64) the exchanges only need wavefront-scope ordering;
-// otherwise they use workgroup barriers.
+// buffer in natural order (padded indexing).  A group lies in one wavefront
+// (NT <= 64), so the exchanges only need wavefront-scope ordering.
 //
 // Stockham autosort formulation (decimation in time): at a stage with radix R
 // applied after sub-transforms of length Ns, butterfly j (0 <= j < N/R) reads
@@ -33,8 +32,6 @@ struct cplx {
 };
 
 template <typename T>
-__device__ __forceinline__ cplx<T> mk(T a, T b) { return cplx<T>{a, b}; }
-template <typename T>
 __device__ __forceinline__ cplx<T> operator+(cplx<T> a, cplx<T> b) { return {a.x + b.x, a.y + b.y}; }
 template <typename T>
 __device__ __forceinline__ cplx<T> operator-(cplx<T> a, cplx<T> b) { return {a.x - b.x, a.y - b.y}; }
@@ -47,8 +44,6 @@ template <typename T>
 __device__ __forceinline__ cplx<T> cmulc(cplx<T> a, cplx<T> b) {
   return {a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y};
 }
-template <typename T>
-__device__ __forceinline__ cplx<T> scale(cplx<T> a, T s) { return {a.x * s, a.y * s}; }
 // multiply by -i (DIR = -1, forward) or +i (DIR = +1, inverse)
 template <int DIR, typename T>
 __device__ __forceinline__ cplx<T> rot90(cplx<T> a) {
@@ -242,24 +237,9 @@ struct Radices {
 };
 __host__ __device__ constexpr Radices plan_of(int n, int e) {
   if (e == 16) {
-    switch (n) {
-      case 16: return {1, 1, 1};
-      case 32: return {2, 1, 1};
-      case 64: return {4, 1, 1};
-      case 128: return {8, 1, 1};
-      case 256: return {16, 1, 1};
-      case 512: return {16, 2, 1};
-      case 1024: return {16, 4, 1};
-      default: break;
-    }
+    if (n == 1024) return {16, 4, 1};
   } else if (e == 8) {
-    switch (n) {
-      case 64: return {8, 1, 1};
-      case 128: return {8, 2, 1};
-      case 256: return {8, 4, 1};
-      case 512: return {8, 8, 1};
-      default: break;
-    }
+    if (n == 512) return {8, 8, 1};
   } else if (e == 4) {
     switch (n) {
       case 64: return {4, 4, 1};
@@ -308,12 +288,11 @@ __host__ __device__ constexpr int fft_E_of(int n) {
 template <int N>
 __host__ __device__ constexpr int fft_E() { return fft_E_of(N); }
 
-// exchanges of a transform owned by NT lanes: wavefront-scope ordering when the
-// transform lives in one wavefront, a workgroup barrier otherwise
+// exchanges of a transform owned by NT lanes: wavefront-scope ordering
 template <int NT>
 __device__ __forceinline__ void xsync() {
-  if constexpr (NT > 64) __syncthreads();
-  else wave_sync();
+  static_assert(NT <= 64, "a transform lives in one wavefront");
+  wave_sync();
 }
 
 // the twiddle table lives in global memory: loads through this pointer type
@@ -419,7 +398,7 @@ __device__ __forceinline__ void lane_swap(V& a, V& b) {
   __builtin_memcpy(&b, wb, sizeof(V));
 }
 
-// The last two stages of N = 256 G (G = 2 or 4; 16 values per lane, NT = 16 G
+// The last two stages of N = 1024 = 256 G, G = 4 (16 values per lane, NT = 16 G
 // lanes, radix 16 then radix G) with the exchange between them done across
 // lanes instead of through LDS.  After the radix-16 stage, lane t = c + 16 q
 // (c < 16) holds entry 256 q + c + 16 r in x[r]; with r = G a + s that entry is
@@ -431,7 +410,7 @@ __device__ __forceinline__ void lane_swap(V& a, V& b) {
 template <typename T, int N, int E, int DIR, int M>
 __device__ __forceinline__ void stages_16_then_G(cplx<T> (&v)[M][E], int t, gptr<T> tw) {
   constexpr int NT = N / E, G = N / 256, A = 16 / G;
-  static_assert(E == 16 && (G == 2 || G == 4) && NT == 16 * G, "plan 16 x 16 x G");
+  static_assert(E == 16 && G == 4 && NT == 16 * G, "plan 16 x 16 x 4");
   stockham_stage<T, N, E, DIR, 16, 16, M>(v, t, tw);
   // G x G transpose across the lanes c + 16 q
 #pragma unroll
@@ -439,14 +418,10 @@ __device__ __forceinline__ void stages_16_then_G(cplx<T> (&v)[M][E], int t, gptr
     cplx<T>(&x)[E] = v[m];
 #pragma unroll
     for (int a = 0; a < A; ++a) {
-      if constexpr (G == 4) {
-        lane_swap<32>(x[4 * a + 0], x[4 * a + 2]);
-        lane_swap<32>(x[4 * a + 1], x[4 * a + 3]);
-        lane_swap<16>(x[4 * a + 0], x[4 * a + 1]);
-        lane_swap<16>(x[4 * a + 2], x[4 * a + 3]);
-      } else {
-        lane_swap<16>(x[2 * a + 0], x[2 * a + 1]);
-      }
+      lane_swap<32>(x[4 * a + 0], x[4 * a + 2]);
+      lane_swap<32>(x[4 * a + 1], x[4 * a + 3]);
+      lane_swap<16>(x[4 * a + 0], x[4 * a + 1]);
+      lane_swap<16>(x[4 * a + 2], x[4 * a + 3]);
     }
   }
   stockham_stage<T, N, E, DIR, 256, G, M>(v, t, tw + 15 * 16);
@@ -475,7 +450,7 @@ __device__ __forceinline__ void fft_side_by_side(cplx<T> (&v)[M][E], T* const (&
   for (int m = 0; m < M; ++m) dft<E, DIR>(v[m]);
   exchange<T, E, NT, SPLIT, M>(v, buf, [&](int i) { return LaneIdx{t * E + i, 0}; },
                                [&](int i) { return stage_in<N, E, R2>(i, t); });
-  if constexpr (E == 16 && R2 == 16 && (R3 == 2 || R3 == 4) && R4 == 1) {
+  if constexpr (E == 16) {
     stages_16_then_G<T, N, E, DIR, M>(v, t, ptw);
   } else {
     stockham_stage<T, N, E, DIR, E, R2, M>(v, t, ptw + tw_offset(N, E, 0));

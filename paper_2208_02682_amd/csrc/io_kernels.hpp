@@ -61,7 +61,7 @@ __global__ void __launch_bounds__(col_threads<N>())
     k_io_col_forward(IoColFwd J, Dims d, const cplx<double>* tw) {
   constexpr int C = col_tile<N>();
   constexpr int E = fft_E<N>(), NT = N / E;
-  __shared__ __align__(16) double lds[col_lds<double, N, C>()];
+  __shared__ __align__(16) double lds[col_lds<double, N, C, false>()];
   const ColCtx<double, N, C> cx(lds, blockIdx.x);
   const int q = blockIdx.y;
   cplx<double> out[E];
@@ -94,7 +94,7 @@ __global__ void __launch_bounds__(col_threads<N>())
     k_io_col_inverse(IoColInv J, Dims d, const cplx<double>* tw) {
   constexpr int C = col_tile<N>();
   constexpr int E = fft_E<N>(), NT = N / E;
-  __shared__ __align__(16) double lds[col_lds<double, N, C>()];
+  __shared__ __align__(16) double lds[col_lds<double, N, C, false>()];
   const ColCtx<double, N, C> cx(lds, blockIdx.x);
   const int q = blockIdx.y;
   const size_t col = (size_t)cx.kx * d.NKY;

@@ -52,14 +52,14 @@ enum RowSpec : int {
   NRS = 17
 };
 
-// column-kernel work groups (one prognostic field each; E_h, E_zeta ride with h)
+// column-kernel work groups (one prognostic field each; E_h, E_zeta ride with the
+// g-tilde and g-bar groups)
 // (the momentum groups come next and are launched only when requested, then the
 // Eulerian-mean groups of averaged fields other than (h, zeta))
 enum ColGroup : int {
   CG_U = 0, CG_V, CG_H, CG_XIX, CG_XIY, CG_GBH, CG_GBZ, CG_GTH, CG_GTZ, CG_PX, CG_PY,
-  NCG = 11,
-  CG_GMX = 11, CG_GMY, NCG_MOM = 13,
-  CG_EF0 = 13, CG_EF1
+  CG_GMX, CG_GMY,
+  CG_EF0, CG_EF1
 };
 
 // the fields the two averaging slots can hold (f_0, f_1; the default is (eta, zeta))

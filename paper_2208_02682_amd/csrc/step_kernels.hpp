@@ -64,7 +64,7 @@ template <int N>
 __host__ __device__ constexpr Dims dims_of() { return Dims::make(N); }
 
 template <int N, int W = 0>
-__host__ __device__ constexpr int col_tile() { return col_tile_of(N, W); }
+__host__ __device__ constexpr int col_tile() { return col_tile_of(W); }
 template <int N, int W = 0>
 __host__ __device__ constexpr int col_threads() { return col_tile<N, W>() * (N / fft_E<N>()); }
 
@@ -447,8 +447,9 @@ struct DynGeo : CoopGeo<T, N> {
   static constexpr bool SIX = N < 1024;
   static constexpr int WAVES = SIX ? 6 : 4, THREADS = 64 * WAVES;
   // six: shared pairs overlay their waves' buffers (split: second components apart);
-  // four: shared pairs apart from the transform buffers
-  static constexpr int BUFS = SIX ? (G::SPLIT ? 8 : 6) : (G::SPLIT ? 8 : 6);
+  // four: shared pairs apart from the transform buffers (split always)
+  static constexpr int BUFS = G::SPLIT ? 8 : 6;
+  static_assert(SIX || G::SPLIT, "four waves: split exchanges");
   static constexpr int LDS = BUFS * G::WR * G::RB;
   // registers for this many resident waves per SIMD; the averaged fields' formulas
   // (gen) take more of them
@@ -463,13 +464,13 @@ __device__ __forceinline__ void rows_dyn_four(const StepPtrs<T>& P, const Phys& 
                                               int rowblock, T* lds) {
   using G = DynGeo<T, N>;
   constexpr int E = G::E, NT = G::NT, WR = G::WR, RB = G::RB;
-  constexpr bool SPLIT = G::SPLIT;
+  constexpr bool SPLIT = true;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);  // the wave's role
   const int lane = threadIdx.x % 64;
   const int g = lane / NT, t = lane % NT;
   const int y = rowblock * WR + g;
   auto buf = [&](int i) { return lds + (i * WR + g) * RB; };
-  const SharedPair<T, SPLIT> UV{buf(4), buf(SPLIT ? 5 : 4)}, HZ{buf(SPLIT ? 6 : 5), buf(SPLIT ? 7 : 5)};
+  const SharedPair<T, SPLIT> UV{buf(4), buf(5)}, HZ{buf(6), buf(7)};
   T* mine = buf(w);
   constexpr Dims d = dims_of<N>();
   constexpr size_t rf = d.rowfield_elems();
@@ -1358,9 +1359,9 @@ __device__ __forceinline__ void column_group(const ColCtx<T, N, C>& cx, const St
     // batch (stage values, state, accumulator) is issued before its first
     // store, so the batch's loads are in flight together (stores to the state
     // could alias later loads as far as the compiler knows, which would
-    // otherwise serialise the coefficients).  Up to 256^2 one batch takes
-    // all of a lane's coefficients, and its loads are issued before the forward
-    // transforms (PRE): they wait for memory once, not twice.
+    // otherwise serialise the coefficients).  With four values per lane (64^2,
+    // 128^2, 256^2) one batch takes all of a lane's coefficients, and its loads are
+    // issued before the forward transforms (PRE): they wait for memory once, not twice.
     // For the default averaged fields (eta, zeta) the g-tilde groups take their
     // source f from the stage spectra, f = eta (h less H at k = 0) for g-tilde_h
     // and f = i kx v - i ky u for g-tilde_zeta (eq. (4.1): the rows pass formed
@@ -1647,8 +1648,9 @@ template <typename T, int N, int W>
 using StageB = StageGeo<T, N, W, RhsGeo<T, N>::THREADS, RhsGeo<T, N>::LDS>;
 
 // Resident waves per SIMD the column groups' registers leave room for: from 512
-// on in float32 4 (at most 128 registers), in float64 2; on smaller grids, which do not
-// fill the chip, they keep their whole state in registers.
+// on in float32 4 (at most 128 registers), in float64 2; smaller grids, which do not
+// fill the chip, are not held to that (with four values per lane a lane's whole state
+// is in registers).
 template <typename T, int N>
 __host__ __device__ constexpr int col_waves() {
   return N >= 512 ? (sizeof(T) == 4 ? 4 : 2) : (sizeof(T) == 4 ? 2 : 1);
