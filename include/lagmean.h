@@ -335,10 +335,10 @@ lm_status lm_batch_destroy(lm_batch* b);
  * (n, precision) can be launched in several ways that compute the same numbers
  * in the same order (results are bit-identical across schedules):
  *   col_tile   width of the column tiles of the column pass (columns per
- *              block): -1 half, 0 the default (8 columns when a transform
- *              spans at least 8 lanes), +1 twice; a width is usable when its
- *              block is whole wavefronts of at most 1024 threads and its LDS
- *              tile fits in a CU's 160 KiB;
+ *              block): 0 the default (8), -1 half, +1 twice.  The widths
+ *              offered are a fixed list, whatever the kernels hold per lane:
+ *              half from n = 192 on; twice where its tile fits in a CU's
+ *              160 KiB of LDS (not 1024 in LM_FP64);
  *   xcd_order  1: blocks renumbered so that each of the 8 XCDs (own L2)
  *              receives a contiguous range of row blocks / column tiles with
  *              all tasks of each (the default); 0: hardware dispatch order;

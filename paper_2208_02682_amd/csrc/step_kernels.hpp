@@ -1607,9 +1607,13 @@ __device__ __forceinline__ void columns_body(const StepPtrs<T>& P, const Phys& p
 // launches: 64^2 float64 59.1 -> 44.4 us, 128^2 float32 62.2 -> 53.9, 192^2 float32
 // 99.6 -> 67.8, 256^2 float64 100.4 -> 96.7, 384^2 float32 141 -> 116 (41.2, 49.4,
 // 68.7, 87.8 and 105 with the state's loads in one straight line and the tiles
-// tuned).  From 512^2 on the passes fill the chip by themselves and the larger of
-// the two parts' registers and LDS costs both (merged, 512^2 float32 130.6 -> 139.3,
-// 127.7 with narrow tiles; 1024^2 346 -> 366).
+// tuned).  512^2 and 1024^2 keep the passes apart: their passes fill the chip, and with
+// the columns as they were then the larger of the two parts' registers and LDS cost
+// both (512^2 float32 130.6 -> 139.3).  That no longer holds: with one set of buffers
+// and four waves per SIMD in the columns, merged launches would be the faster at the
+// best tile of each form (apart / merged, from one state: 512^2 float32 123.8 / 114.3,
+// float64 162.7 / 156.3, 1024^2 float32 316.6 / 308.2, float64 664.6 / 634.3, all but
+// the first with the half-width tile); the line has not been moved yet.
 template <typename T, int N>
 __host__ __device__ constexpr bool stage_merged() { return N < 512; }
 
