@@ -338,7 +338,8 @@ lm_status lm_batch_destroy(lm_batch* b);
  *              block): 0 the default (8), -1 half, +1 twice.  The widths
  *              offered are a fixed list, whatever the kernels hold per lane:
  *              half from n = 192 on; twice where its tile fits in a CU's
- *              160 KiB of LDS (not 1024 in LM_FP64);
+ *              160 KiB of LDS (not 1024 in LM_FP64).  A batch's groups of
+ *              many runs (eight at least, n < 512) take half as the default;
  *   xcd_order  1: blocks renumbered so that each of the 8 XCDs (own L2)
  *              receives a contiguous range of row blocks / column tiles with
  *              all tasks of each (the default); 0: hardware dispatch order;

@@ -305,7 +305,7 @@ void launch_batch_step_t(hipStream_t st, const RunDesc<T>* desc, int nruns, bool
     if (cubic) hipLaunchKernelGGL((k_rows_mom_b<T, N, true>), gr, bm, 0, st, desc, stage, rm);
     else hipLaunchKernelGGL((k_rows_mom_b<T, N, false>), gr, bm, 0, st, desc, stage, rm);
   };
-  with_tile<T, N>(sc.tile, [&](auto w) {
+  with_tile<T, N>(batch_tile<T, N>(nruns, sc.tile), [&](auto w) {
     constexpr int W = decltype(w)::value;
     if constexpr (stage_merged<T, N>()) {
       if (nruns <= batch_merged_runs<T, N>()) {

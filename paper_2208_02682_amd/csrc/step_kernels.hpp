@@ -1637,6 +1637,16 @@ __host__ __device__ constexpr int batch_merged_runs() {
   return (f32 ? 640 : 320) / (N / CoopGeo<T, N>::WR);
 }
 
+// Tile width of a batched group's columns for the schedule's: half-width tiles are for
+// few blocks, so a group of eight runs or more in passes apart takes at least the
+// default (half / default, us a step: 256^2 float32 5 runs 171 / 170, 8 runs 230 / 228,
+// 12 runs 312 / 306, 64 runs 1965 / 1870; 192^2 float32 12 runs 207 / 202, 64 runs
+// 967 / 920; 384^2 float32 16 runs 1016 / 980; but one run of 256^2, merged, 77 / 88).
+template <typename T, int N>
+__host__ __device__ constexpr int batch_tile(int nruns, int tile) {
+  return stage_merged<T, N>() && nruns >= 8 && nruns > batch_merged_runs<T, N>() && tile < 0 ? 0 : tile;
+}
+
 template <typename T, int N, int W, int ROW_THREADS, int ROW_LDS>
 struct StageGeo {
   static constexpr int C = col_tile<N, W>(), COL_THREADS = col_threads<N, W>();
